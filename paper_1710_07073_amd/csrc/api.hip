@@ -16,7 +16,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
   size_t tiles[2], region[2], region_list[2], region_count, tcount, tlist, partials, result,
-      status, traj_row, total;
+      status, traj_row, slab, mid, init, total;  // init: bytes lbm_init() clears
   uint32_t ntiles, nred, tnx, tny, tnz;
 };
 
@@ -36,6 +36,16 @@ bool desc_ok(const lbm_desc* d) {
   const double cells = (double)d->nx * d->ny * d->nz;
   if (cells * 19.0 >= 2147483648.0) return false;
   return true;
+}
+
+// Lattices whose method steps lbm_run() takes in pairs (step2.hip): walls on every face, 32-bit byte
+// offsets, no flag that has every cell read its force or write its velocity.
+bool pairs_ok(const lbm_desc* d) {
+  for (int f = 0; f < 6; ++f)
+    if (d->bc[f] == LBM_BC_PERIODIC) return false;
+  const size_t cells = (size_t)d->nx * d->ny * d->nz;
+  return cells >= lbm::kPairMinCells && 19 * cells * (d->precision == LBM_FP32_SHIFTED ? 4 : 8) <= 0xffffffffull &&
+         !(d->flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL));
 }
 
 Layout layout_of(const lbm_desc* d) {
@@ -61,7 +71,12 @@ Layout layout_of(const lbm_desc* d) {
   L.result = align_up(L.partials + (size_t)L.nred * 4 * sizeof(double));
   L.status = align_up(L.result + 4 * sizeof(double));
   L.traj_row = align_up(L.status + sizeof(int32_t));
-  L.total = align_up(L.traj_row + sizeof(uint32_t));
+  L.slab = align_up(L.traj_row + sizeof(uint32_t));
+  L.init = align_up(L.slab + 8 * sizeof(uint32_t));
+  // the middle buffer of pairs of method steps, for the lattices that can take them
+  L.mid = L.init;
+  const size_t elem = d->precision == LBM_FP32_SHIFTED ? 4 : 8;
+  L.total = L.init + (pairs_ok(d) ? align_up(19 * (size_t)cells * elem) : 0);
   return L;
 }
 
@@ -159,6 +174,11 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   c->traj = nullptr;
   c->traj_rows = 0;
   c->traj_row = reinterpret_cast<uint32_t*>(s + L.traj_row);
+  c->slab = reinterpret_cast<uint32_t*>(s + L.slab);
+  c->mid = pairs_ok(desc) ? s + L.mid : nullptr;
+  if (G.N < lbm::kStep2MinCells || !lbm::bb_fast_ok(G, c->elem) ||
+      !lbm::choose_tiles2(G, c->elem, &c->tiles2))
+    c->tiles2 = lbm::Tiles2{};
   c->nred = L.nred;
   c->bins_clean = false;
   c->stream = static_cast<hipStream_t>(stream);
@@ -202,7 +222,7 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   if (e == hipSuccess) e = lbm::launch_fill(pops_b, 19 * cells * c->elem, c->stream);
   if (e == hipSuccess) e = lbm::launch_fill(force, 3 * cells * c->elem, c->stream);
   if (e == hipSuccess) e = lbm::launch_fill(vel, 3 * cells * c->elem, c->stream);
-  if (e == hipSuccess) e = lbm::launch_fill(scratch, L.total, c->stream);
+  if (e == hipSuccess) e = lbm::launch_fill(scratch, L.init, c->stream);
   if (e != hipSuccess) {
     lbm_destroy(c);
     return LBM_EDEVICE;
@@ -328,9 +348,18 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x) {
 
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
   if (!ctx || nsteps < 0) return LBM_EINVAL;
-  for (int32_t i = 0; i < nsteps; ++i) {
-    const hipError_t e = lbm::launch_step(ctx);
-    if (e != hipSuccess) return LBM_EDEVICE;
+  int32_t i = 0;
+  // a force spread by a bubble half belongs to the first step
+  if (nsteps > 0 && (ctx->hs.pending || ctx->hs.forced || nsteps % 2)) {
+    if (lbm::launch_step(ctx) != hipSuccess) return LBM_EDEVICE;
+    ++i;
+  }
+  const bool pairs = lbm::can_step2(ctx);
+  while (i < nsteps) {
+    const int n = pairs && nsteps - i >= 2 ? 2 : 1;
+    if ((n == 2 ? lbm::launch_step2(ctx, nullptr) : lbm::launch_step(ctx)) != hipSuccess)
+      return LBM_EDEVICE;
+    i += n;
   }
   return LBM_OK;
 }
@@ -338,8 +367,9 @@ lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
 namespace {
 // in_run: a step of lbm_run, where no caller code runs between steps, so that an overlapped step
 // may mark the region of the next one while its bulk runs (from the bubble state it leaves).
+// slab, slab_clear: a half of a pair of steps (launch_bubbles).
 lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb,
-                       bool in_run) {
+                       bool in_run, uint32_t* slab = nullptr, uint32_t* slab_clear = nullptr) {
   if (!ctx || !p || !s || nb < 0) return LBM_EINVAL;
   if (ctx->desc.flags & LBM_FLAG_STATIC_FORCE) return LBM_EINVAL;
   if (p->n_sub < 1 || !lbm::coupling_ok(p->coupling)) return LBM_EINVAL;
@@ -356,7 +386,27 @@ lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s
   // the caller may have moved bubbles since a previous run marked ahead: mark afresh
   if (!in_run) ctx->hs.marked = false;
   const bool overlap = ctx->overlap && nb > 0 && lbm::can_overlap(ctx);
-  return from_hip(lbm::launch_bubbles(ctx, p, s, nb, overlap, in_run));
+  return from_hip(lbm::launch_bubbles(ctx, p, s, nb, overlap, in_run, slab, slab_clear));
+}
+
+// lbm_run() takes the method steps of this lattice in pairs (serial steps; the exact-time coupling
+// reads the whole state between the two).
+bool can_pair(const lbm_ctx* ctx, const bubble_params* p, int32_t nb) {
+  return ctx->mid && lbm::can_step2(ctx) && !(p->coupling & LBM_COUPLING_EXACT_TIME) &&
+         !(ctx->overlap && nb > 0 && lbm::can_overlap(ctx));
+}
+
+// Two method steps (see step2.hip).
+lbm_status step_pair(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb) {
+  uint32_t* const words = ctx->slab + 4 * ctx->hs.spar;
+  lbm_status st = bubble_half(ctx, p, s, nb, true, words, ctx->slab + 4 * (ctx->hs.spar ^ 1));
+  if (st != LBM_OK) return st;
+  if (nb > 0 && lbm::launch_slab(ctx, words) != hipSuccess) return LBM_EDEVICE;
+  st = bubble_half(ctx, p, s, nb, true, words + 2, nullptr);
+  if (st != LBM_OK) return st;
+  if (lbm::launch_step2(ctx, words) != hipSuccess) return LBM_EDEVICE;
+  if (nb > 0) ctx->hs.spar ^= 1;
+  return LBM_OK;
 }
 }  // namespace
 
@@ -456,18 +506,28 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
   // an armed step record belongs to one call of bubbles_step (a graph would replay it)
   if (ctx->arm_record) return LBM_EINVAL;
   ctx->hs.marked = false;  // the bubble state may have changed since the last call
-  auto one = [&]() -> lbm_status {
-    lbm_status st = bubble_half(ctx, p, s, nb, true);
-    if (st != LBM_OK) return st;
-    return lbm_step(ctx, 1);
-  };
-  if (graph_steps == 0 || nsteps < graph_steps || !ctx->stream) {
-    for (int32_t i = 0; i < nsteps; ++i) {
-      const lbm_status st = one();
+  // the last `single` of the n steps are not paired
+  auto steps = [&](int32_t n, int32_t single = 0) -> lbm_status {
+    const bool pairs = can_pair(ctx, p, nb);
+    for (int32_t i = 0; i < n;) {
+      const bool two = pairs && n - single - i >= 2;
+      lbm_status st;
+      if (two) {
+        st = step_pair(ctx, p, s, nb);
+      } else {
+        st = bubble_half(ctx, p, s, nb, true);
+        if (st == LBM_OK) st = lbm_step(ctx, 1);
+      }
       if (st != LBM_OK) return st;
+      i += two ? 2 : 1;
     }
     return LBM_OK;
-  }
+  };
+  if (graph_steps == 0 || nsteps < graph_steps || !ctx->stream) return steps(nsteps);
+  // A pair flips the population buffers once, so an odd number of pairs would need two graphs, one
+  // for each buffer: a graph of ten steps or more ends in two single ones instead (a shorter one
+  // is captured twice).
+  const int32_t single = graph_steps % 4 == 2 && graph_steps >= 10 ? 2 : 0;
   int32_t done = 0;
   while (nsteps - done >= graph_steps) {
     // the captured launches depend on the host step state (buffer and mask parities, which
@@ -476,7 +536,7 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     const lbm::HostState pre = ctx->hs;
     const uint32_t mode = (pre.flag_clean[0] ? 1u : 0u) | (pre.flag_clean[1] ? 2u : 0u) |
                           ((uint32_t)pre.rpar << 4) | (ctx->overlap ? 32u : 0u) |
-                          (pre.marked ? 64u : 0u) |
+                          (pre.marked ? 64u : 0u) | ((uint32_t)pre.spar << 7) |
                           ((uint32_t)ctx->step_vec << 8) | (ctx->step_bx << 12) |
                           ((uint32_t)ctx->step_wgs << 24);
     const lbm::GraphKey key = lbm::GraphKey::of(p, s, nb, pre.cur, pre.flag_cur, graph_steps, mode);
@@ -484,11 +544,8 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     bool captured = false;
     hipError_t e = ctx->graph.ensure(key, ctx->stream,
                                      [&]() -> hipError_t {
-                                       for (int i = 0; i < graph_steps; ++i) {
-                                         st_cap = one();
-                                         if (st_cap != LBM_OK) return hipErrorInvalidValue;
-                                       }
-                                       return hipSuccess;
+                                       st_cap = steps(graph_steps, single);
+                                       return st_cap == LBM_OK ? hipSuccess : hipErrorInvalidValue;
                                      },
                                      &captured);
     if (st_cap != LBM_OK || e != hipSuccess) {
@@ -501,11 +558,7 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     ctx->hs.steps = pre.steps + graph_steps;
     done += graph_steps;
   }
-  for (int32_t i = done; i < nsteps; ++i) {
-    const lbm_status st = one();
-    if (st != LBM_OK) return st;
-  }
-  return LBM_OK;
+  return steps(nsteps - done);
 }
 
 lbm_status lbm_destroy(lbm_ctx* ctx) {

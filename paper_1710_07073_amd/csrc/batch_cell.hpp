@@ -5,7 +5,7 @@
 
 #include <utility>
 
-#include "step_cell.hpp"
+#include "step2_cell.hpp"
 
 namespace lbm {
 
@@ -24,10 +24,6 @@ __device__ __forceinline__ void pull_all_g(T* g, const gmem<T>* src, const Geom&
                                            const CellNbr& nb, std::integer_sequence<int, Qs...>) {
   ((g[Qs] = src[pull_index<Qs, true>(G, lc, nb)]), ...);
 }
-
-// Faces of a batch (the liquid kernel's template parameter): every face of every column
-// bounce-back, walls only (bounce-back or free slip), or some face periodic.
-enum : int { FACES_BB = 0, FACES_WALLS = 1, FACES_GENERAL = 2 };
 
 // The liquid step of one work item of a batch (item_col names its column) by the workgroup, one
 // cell per thread per pass. The coordinates of the item's first cell are found once (uniform);

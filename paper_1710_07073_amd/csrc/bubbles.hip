@@ -368,6 +368,12 @@ __device__ void mark_tiles(const ColumnView<T>& col, const BubbleArgs& A, const 
     }
     if (a > 0)
       inside = inside && lo >= win[a].lo - 1 - kRegionMargin && hi <= win[a].hi + 1 + kRegionMargin;
+    if (a == 2 && col.slab && tid == 0) {
+      // the planes this half reaches: the force window with one to spare on either side (the
+      // two-step pass computes the plane beside the slab without force), and the velocity window
+      atomicMax(&col.slab[0], kSlabBase - (uint32_t)min(win[a].clo - 1, lo));
+      atomicMax(&col.slab[1], (uint32_t)(max(win[a].chi + 1, hi) + 1));
+    }
     tr[a] = tile_ranges(lo, hi, ext[a], (int)kTile, per);
   }
   const uint32_t* __restrict__ region = inside ? nullptr : col.region;
@@ -475,6 +481,8 @@ __device__ __forceinline__ void clear_for_step(const Geo& geo) {
     // in an overlapped step, the other parity's region list (its region launch ran before)
     // starts empty
     if (geo.clear_count) *geo.clear_count = 0u;
+    if (geo.slab_clear)
+      for (int i = 0; i < 4; ++i) geo.slab_clear[i] = 0u;
   }
   geo.clear_other_jobs();  // many columns: the next step's tile jobs start empty
 }
@@ -1453,7 +1461,7 @@ hipError_t launch_persistent_faces(const ManyColumns& geo, const BubbleArgs& A,
 }  // namespace
 
 hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb,
-                          bool overlap, bool mark_ahead) {
+                          bool overlap, bool mark_ahead, uint32_t* slab, uint32_t* slab_clear) {
   BubbleArgs A;
   A.P = *p;
   A.S = *s;
@@ -1473,7 +1481,10 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
   c->hs.flag_clean[m] = false;
   c->hs.flag_cur = m;
   if (nb == 0) return hipSuccess;
+  c->hs.forced = true;
   OneColumn geo;
+  geo.slab = slab;
+  geo.slab_clear = slab_clear;
   geo.G = c->geom;
   geo.U = c->vel;
   geo.F = c->force;

@@ -11,6 +11,12 @@
 #include "lattice.hpp"
 
 namespace lbm {
+// Tiling of a lattice by the two-step pass (step2.hip): output cells per tile along x and y, tiles
+// along x and y, and chunks of planes along z (ox 0: not taken).
+struct Tiles2 {
+  uint32_t ox, oy, ntx, nty, nchunk;
+};
+
 // Host-side step state of a context: which buffers and masks the next launches use.
 struct HostState {
   int cur;                // pops[cur] holds the current post-collision state
@@ -18,7 +24,9 @@ struct HostState {
   bool flag_clean[2];     // tile mask known to be all zero
   int rpar;               // parity of the next overlapped step (its region flags, list, counter)
   bool pending;           // bubbles_step() enqueued the bulk; lbm_step() must update the region
+  bool forced;            // a bubble half spread force the next liquid step has yet to use
   bool marked;            // the region of the next overlapped step is marked (within lbm_run)
+  int spar;               // parity of the next pair of method steps (its slab words)
   bool last_overlapped;   // the last liquid step was overlapped (its region list is current)
   int64_t steps;
 };
@@ -33,6 +41,9 @@ struct lbm_ctx {
   void* pops[2];    // population buffers; pops[hs.cur] holds the current post-collision state
   void* force;
   void* vel;
+  void* mid;  // middle buffer of a pair of method steps (step2.hip), or null
+  uint32_t* slab;  // slab words, 4 per pair parity
+  lbm::Tiles2 tiles2;
   // Two tile masks, one byte per 8^3 tile (force present / velocity needed). bubbles_step()
   // writes mask[flag_cur ^ 1] and makes it current; each liquid step reads mask[flag_cur] and
   // clears the other one for the next bubble step.
@@ -94,6 +105,7 @@ struct ColumnView {
   uint8_t* tiles;
   double nu;
   const uint32_t* region;  // region flags of an overlapped step (tiles the spread may force), or null
+  uint32_t* slab;          // slab words of a half of a pair of steps, or null
 };
 
 // A single lattice (lbm_ctx). tcount/tlist: the per-tile bubble lists of the deterministic
@@ -117,9 +129,11 @@ struct OneColumn {
   uint32_t* next_list;
   uint32_t* next_count;
   uint32_t nrows;
+  uint32_t* slab;        // slab words this half of a pair of steps notes its planes in, or null
+  uint32_t* slab_clear;  // the next pair's, cleared by k_interp (null: not here)
   template <typename T>
   __device__ ColumnView<T> view(int) const {
-    return {G, static_cast<const T*>(U), static_cast<T*>(F), tiles, nu, region};
+    return {G, static_cast<const T*>(U), static_cast<T*>(F), tiles, nu, region, slab};
   }
   // the deterministic spreading: per-tile lists of this lattice (every tile is gathered, so the
   // tiles entered need no note)
@@ -168,7 +182,7 @@ struct ManyColumns {
   template <typename T>
   __device__ ColumnView<T> view(int b) const {
     const ColumnDev& c = cols[bubble_col[b]];
-    return {c.G, static_cast<const T*>(c.U), static_cast<T*>(c.F), c.tiles[flag], c.nu, nullptr};
+    return {c.G, static_cast<const T*>(c.U), static_cast<T*>(c.F), c.tiles[flag], c.nu, nullptr, nullptr};
   }
   __device__ bool use_lists() const { return true; }
   // the bubble constants of bubble b: the shared ones with its column's g and sigma where set
@@ -233,6 +247,17 @@ constexpr int kRegionMargin = 2;
 // Lattices from this size on overlap the bubble kernels with the liquid step by default.
 constexpr uint32_t kOverlapMinCells = 1u << 22;
 
+// Slab words (uint32, zero: empty): [0] max of kSlabBase - a and [1] max of b over the bubbles, the
+// slab [a, b) of a pair's first half; [2], [3] the same of its second half.
+constexpr uint32_t kSlabBase = 1u << 30;
+
+// Lattices from these sizes on are advanced two steps per launch, alone and with bubbles. Alone, the
+// shorter chunks of a small lattice lose to their halo planes: 30 x 30 x 90 FP32 6.0 us per step
+// against 4.9 us one by one, 32 x 32 x 64 FP64 6.0 against 5.4, 48 x 48 x 144 FP32 9.1 against 12.9.
+// With bubbles the slab launch comes on top (about 5 us per pair).
+constexpr uint32_t kStep2MinCells = 1u << 17;
+constexpr uint32_t kPairMinCells = 1u << 19;
+
 // A valid bubble_params.coupling: known bits and a known reaction.
 inline bool coupling_ok(int32_t c) {
   const int32_t known = LBM_REACTION_MASK | LBM_COUPLING_POINT_KERNEL | LBM_COUPLING_EXACT_TIME;
@@ -249,11 +274,21 @@ hipError_t launch_step(lbm_ctx* c);
 bool can_overlap(const lbm_ctx* c);
 // Bulk part of the liquid step of an overlapped step (on the caller's stream).
 hipError_t launch_bulk(lbm_ctx* c);
+// step2.hip
+bool choose_tiles2(const Geom& G, size_t elem, Tiles2* best);
+// The liquid can be advanced two steps per launch.
+bool can_step2(const lbm_ctx* c);
+// Two liquid steps in one launch. slab (null: no bubbles, no force but a static one): the slab
+// words of the pair of method steps this launch ends.
+hipError_t launch_step2(lbm_ctx* c, const uint32_t* slab);
+// The first liquid step of a pair of method steps, of the planes the bubbles reach.
+hipError_t launch_slab(lbm_ctx* c, const uint32_t* slab);
 // bubbles.hip
 // mark_ahead (overlapped steps of lbm_run only): also mark the region of the next step, after the
-// bubble update, on the side stream
+// bubble update, on the side stream. slab: a half of a pair of steps (serial), see OneColumn
 hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb,
-                          bool overlap, bool mark_ahead);
+                          bool overlap, bool mark_ahead, uint32_t* slab = nullptr,
+                          uint32_t* slab_clear = nullptr);
 hipError_t launch_bubbles_batch(const ManyColumns& geo, size_t elem, const bubble_params* p,
                                 const bubble_soa* s, int32_t nb, int32_t* status,
                                 hipStream_t stream);
@@ -270,6 +305,17 @@ hipError_t launch_populations(lbm_ctx* c, void* out);
 hipError_t launch_fill(void* ptr, size_t bytes, hipStream_t s);
 
 inline uint32_t div_up(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
+
+// Records the caller's timing events (if any) around one launch on stream s.
+template <class F>
+hipError_t timed(lbm_ctx* c, hipStream_t s, F&& launch) {
+  hipEvent_t a = c->t_start, b = c->t_end;
+  c->t_start = c->t_end = nullptr;
+  hipError_t e = a ? hipEventRecord(a, s) : hipSuccess;
+  if (e == hipSuccess) e = launch();
+  if (e == hipSuccess && b) e = hipEventRecord(b, s);
+  return e;
+}
 
 // Default launch shape of the liquid step: whole rows per workgroup where they fit.
 // Workgroups per compute unit the liquid-step launches are held to by default: fewer waves in

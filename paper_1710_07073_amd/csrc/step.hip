@@ -274,17 +274,6 @@ hipError_t launch_vec(lbm_ctx* c) {
   }
 }
 
-// Records the caller's timing events (if any) around one launch on stream s.
-template <class F>
-hipError_t timed(lbm_ctx* c, hipStream_t s, F&& launch) {
-  hipEvent_t a = c->t_start, b = c->t_end;
-  c->t_start = c->t_end = nullptr;
-  hipError_t e = a ? hipEventRecord(a, s) : hipSuccess;
-  if (e == hipSuccess) e = launch();
-  if (e == hipSuccess && b) e = hipEventRecord(b, s);
-  return e;
-}
-
 template <typename T, bool FS>
 hipError_t launch_bulk_typed(lbm_ctx* c) {
   const Geom& G = c->geom;
@@ -361,6 +350,7 @@ hipError_t launch_step(lbm_ctx* c) {
     c->hs.cur ^= 1;
     c->hs.flag_clean[c->hs.flag_cur ^ 1] = true;
     c->hs.last_overlapped = overlapped;
+    c->hs.forced = false;
     ++c->hs.steps;
   }
   return e;
