@@ -3,16 +3,19 @@
 //             polynomial kernel (eq. (18)-(19)) and the forward coupling (eq. (20)) of the
 //             liquid velocity and of its curl, reduced across the workgroup in double precision;
 //             with several bubbles it also enters the bubble in the per-tile lists;
-//   k_ode     (one lane per bubble) the force closures of Table 1 and n_sub explicit sub-steps
+//   k_ode     (four lanes per bubble) the force closures of Table 1 and n_sub explicit sub-steps
 //             of eq. (4), in double precision; with several bubbles it flags the tiles the
 //             liquid step must force, or must write the velocity in;
-//   k_spread  (one bubble: one workgroup) the backward coupling (eq. (21)) of the reaction into
-//             the force field with the same weights (atomic adds) and the tile flags, or
+//   k_spread  (one bubble, exact-time variant: one workgroup) the backward coupling (eq. (21)) of the
+//             reaction into the force field with the same weights (atomic adds) and the tile flags, or
 //   k_spread_gather (several bubbles: one wavefront per tile) the same sums per cell in bubble
 //             order from the lists, so that the force field is bit-reproducible.
 // Up to 256 bubbles on one lattice and 512 over many columns (not in the exact-time variant)
-// k_interp's workgroup also runs k_ode's update of its bubble on one lane and flags the bubble's
-// tiles, and k_ode is not launched.
+// k_interp's workgroup also runs k_ode's update of its bubble and flags the bubble's tiles, and k_ode is
+// not launched; a lattice's only bubble is spread there as well, so its bubble half is one launch.
+// What bounds k_interp then is latency: 30 x 30 x 90, one bubble d = 0.8, 20.4 us and 5.4 us for k_spread
+// before, 13.8 us now, of which the sub-steps take 5 us (14 us with a lane and the library's log, exp,
+// tanh and square root), the weights 2.6 us, most of it instruction fetches of code that runs once.
 // The coupling variants of bubble_params.coupling (reaction, point-sampled weights, exact-time
 // forward coupling) are modes of these kernels. k_mark marks the region of an overlapped step.
 //
@@ -80,9 +83,38 @@ __device__ __forceinline__ double kernel_Z(double r, double n) {
   return 15.0 / 16.0 * (s2 * s2 - 2.0 * s2 + 1.0) / n;
 }
 
+// v from the lane N positions on in the row of 16 lanes (rotation).
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// v plus v of the lane 32 (or 16) away.
+template <bool HALF>
+__device__ __forceinline__ double swap_add(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+  const auto a = HALF ? __builtin_amdgcn_permlane32_swap(l, l, false, false)
+                      : __builtin_amdgcn_permlane16_swap(l, l, false, false);
+  const auto b = HALF ? __builtin_amdgcn_permlane32_swap(h, h, false, false)
+                      : __builtin_amdgcn_permlane16_swap(h, h, false, false);
+  return __longlong_as_double((long long)(((uint64_t)b[0] << 32) | a[0])) +
+         __longlong_as_double((long long)(((uint64_t)b[1] << 32) | a[1]));
+}
+
+// Sum over the wavefront by the butterfly of distances 32, 16, 8, 4, 2, 1, in the vector registers
+// (through LDS permutes the six sums of a workgroup took 1.7 us). Once the values repeat every 2d
+// lanes, a rotation by d reads the lane at distance d.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  v = swap_add<true>(v);
+  v = swap_add<false>(v);
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
   return v;
 }
 
@@ -108,115 +140,112 @@ __device__ __forceinline__ bool axis_window(double x, double n, int ext, bool pe
   return true;
 }
 
-// Weights of one axis (eq. (19)): cell integrals of the kernel over the clipped window [clo, chi],
-// indexed by (cell - lo + 1), renormalised to a sum of one when a wall clips the window. One full
-// wavefront (lane = 0..63) computes; the renormalising sum is taken in a fixed order. point: the
+// Weights of axis AX (eq. (19)) into w[AX] and, with dw, its curl weights into dw[AX]: cell
+// integrals of the kernel over the clipped window [clo, chi], indexed by (cell - lo + 1),
+// renormalised to a sum of one when a wall clips the window. One full wavefront (lane = 0..63)
+// computes, without a barrier: lane l holds entry l and, for a window that needs them, lanes 0 and 1
+// entries 64 and 65; neighbours come by shuffles. The renormalising sum is taken in a fixed order.
+// AX is a constant, so the window and the face conditions of the axis are plain registers. point: the
 // point-sampled variant, Z at the cell centres renormalised on every axis. Returns false if a
 // point-sampled window holds no cell centre inside the kernel's support.
-__device__ bool wave_axis_weights(const Axis& A, double xa, double n, bool per, bool point, int lane,
-                                  double* s_w_a) {
-  double part = 0.0;
-  for (int i = lane; i < kSpan; i += 64) {
-    const int v = A.lo - 1 + i;
-    double w = 0.0;
-    if (v >= A.clo && v <= A.chi)
-      w = point ? kernel_Z(v - xa, n) : kernel_P((v + 0.5 - xa) / n) - kernel_P((v - 0.5 - xa) / n);
-    s_w_a[i] = w;
-    part += w;
-  }
-  if (!per || point) {
-    const double sum = wave_sum(part);
-    if (sum > 0.0)
-      for (int i = lane; i < kSpan; i += 64) s_w_a[i] /= sum;
-    return sum > 0.0 || !point;
-  }
-  return true;
-}
-
-// The weights of axis AX into s_w[AX] (one wavefront), and their derivative weights into
-// s_dw[AX] once every wavefront's weights are in LDS. AX is a constant, so the window and the
-// face conditions of the axis are plain registers.
 template <int AX>
-__device__ __forceinline__ bool axis_weights_wave(const Geom& G, const double xb[3], double n,
-                                                  bool point, int lane, const Axis win[3],
-                                                  double (*s_w)[kSpan]) {
-  return wave_axis_weights(win[AX], xb[AX], n, G.bc[2 * AX] == BC_PER, point, lane, s_w[AX]);
-}
-
-template <int AX>
-__device__ __forceinline__ void axis_dweights_wave(const Geom& G, int lane, const Axis win[3],
-                                                   const double (*s_w)[kSpan],
-                                                   double (*s_dw)[kSpan]) {
-  const int e = AX == 0 ? G.nx : (AX == 1 ? G.ny : G.nz);
-  const bool per = G.bc[2 * AX] == BC_PER;
-  const double s_lo = G.bc[2 * AX] == BC_FS ? 1.0 : -1.0;
-  const double s_hi = G.bc[2 * AX + 1] == BC_FS ? 1.0 : -1.0;
+__device__ __forceinline__ bool axis_weights(const Geom& G, const double xb[3], double n, bool point,
+                                             int lane, const Axis win[3], double (*s_w)[kSpan],
+                                             double (*s_dw)[kSpan]) {
+  static_assert(kSpan == 66, "a lane holds an entry, lanes 0 and 1 a second one");
   const Axis& A = win[AX];
-  for (int i = lane; i < kSpan; i += 64) {
-    const int v = A.lo - 1 + i;
-    const double wm = i > 0 ? s_w[AX][i - 1] : 0.0;
-    const double wp = i + 1 < kSpan ? s_w[AX][i + 1] : 0.0;
-    double dw = 0.5 * (wm - wp);
-    if (!per) {
-      if (v == 0) dw -= 0.5 * s_lo * s_w[AX][i];       // ghost below cell 0
-      if (v == e - 1) dw += 0.5 * s_hi * s_w[AX][i];  // ghost above the last cell
+  const int ext = AX == 0 ? G.nx : (AX == 1 ? G.ny : G.nz);
+  const bool per = G.bc[2 * AX] == BC_PER;
+  const double xa = xb[AX];
+  const bool wide = A.hi - A.lo + 3 > 64;  // entries 64 and 65 hold cells or their neighbours
+  const int v0 = A.lo - 1 + lane, v1 = v0 + 64;
+  const bool in0 = v0 >= A.clo && v0 <= A.chi, in1 = wide && lane < 2 && v1 >= A.clo && v1 <= A.chi;
+  double w0 = 0.0, w1 = 0.0;
+  if (point) {
+    if (in0) w0 = kernel_Z(v0 - xa, n);
+    if (in1) w1 = kernel_Z(v1 - xa, n);
+  } else {
+    // the upper edge of a cell is the lower edge of the next: one evaluation per entry
+    const double p0 = kernel_P((v0 + 0.5 - xa) / n);
+    const double below = __shfl_up(p0, 1, 64);
+    if (in0) w0 = p0 - below;  // entry 0 lies outside the window
+    if (wide) {
+      const double p63 = __shfl(p0, 63, 64);
+      if (in1) w1 = kernel_P((v1 + 0.5 - xa) / n) - (lane == 0 ? p63 : kernel_P((v1 - 0.5 - xa) / n));
     }
-    s_dw[AX][i] = dw;
   }
+  bool ok = true;
+  if (!per || point) {
+    const double sum = wave_sum(w0 + w1);
+    if (sum > 0.0) {
+      w0 /= sum;
+      w1 /= sum;
+    }
+    ok = sum > 0.0 || !point;
+  }
+  s_w[AX][lane] = w0;
+  if (lane < 2) s_w[AX][lane + 64] = w1;
+  if (s_dw) {
+    const double s_lo = G.bc[2 * AX] == BC_FS ? 1.0 : -1.0;
+    const double s_hi = G.bc[2 * AX + 1] == BC_FS ? 1.0 : -1.0;
+    auto curl = [&](int v, double w, double wm, double wp) {
+      double d = 0.5 * (wm - wp);
+      if (!per) {
+        if (v == 0) d -= 0.5 * s_lo * w;        // ghost below cell 0
+        if (v == ext - 1) d += 0.5 * s_hi * w;  // ghost above the last cell
+      }
+      return d;
+    };
+    const double up = __shfl_up(w0, 1, 64), dn = __shfl_down(w0, 1, 64);
+    const double w64 = wide ? __shfl(w1, 0, 64) : 0.0;
+    s_dw[AX][lane] = curl(v0, w0, lane > 0 ? up : 0.0, lane < 63 ? dn : w64);
+    double d1 = 0.0;
+    if (wide) {
+      const double w63 = __shfl(w0, 63, 64), w65 = __shfl(w1, 1, 64);
+      d1 = curl(v1, w1, lane == 0 ? w63 : w64, lane == 0 ? w65 : 0.0);
+    }
+    if (lane < 2) s_dw[AX][lane + 64] = d1;
+  }
+  return ok;
 }
 
-// Weights w and derivative weights dw of the bubble at xb along the three axes, into LDS,
-// indexed by (cell - lo + 1). Called by the whole workgroup; wavefront a computes axis a, the
-// three side by side. point: the point-sampled variant of the weights.
-__device__ bool build_weights(const Geom& G, const double xb[3], double n, int tid,
-                              double (*s_w)[kSpan], double (*s_dw)[kSpan], Axis win[3],
-                              bool point) {
-  static_assert(kBlock >= 192, "one wavefront per axis");
-  __shared__ int s_bad[3];
+// The windows of the bubble at xb along the three axes; false if one is too large or holds no cell
+// of the lattice.
+__device__ __forceinline__ bool windows(const Geom& G, const double xb[3], double n, Axis win[3]) {
   const int ext[3] = {G.nx, G.ny, G.nz};
-  for (int a = 0; a < 3; ++a) {
-    const bool per = G.bc[2 * a] == BC_PER;
-    if (!axis_window(xb[a], n, ext[a], per, win[a])) return false;
-  }
+  bool ok = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) ok = axis_window(xb[a], n, ext[a], G.bc[2 * a] == BC_PER, win[a]) && ok;
+  return ok;
+}
+
+// Weights (and curl weights, if s_dw) of the bubble at xb along the three axes into LDS. Called by the
+// whole workgroup; wavefront a computes axis a, the three side by side; s_bad[a] tells whether the
+// axis has none. The caller's barrier follows.
+__device__ __forceinline__ void build_weights(const Geom& G, const double xb[3], double n, int tid,
+                                              double (*s_w)[kSpan], double (*s_dw)[kSpan],
+                                              const Axis win[3], bool point, int* s_bad) {
+  static_assert(kBlock >= 192, "one wavefront per axis");
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: a scalar branch
   const int lane = tid & 63;
   if (wave < 3) {
     bool ok;
     if (wave == 0)
-      ok = axis_weights_wave<0>(G, xb, n, point, lane, win, s_w);
+      ok = axis_weights<0>(G, xb, n, point, lane, win, s_w, s_dw);
     else if (wave == 1)
-      ok = axis_weights_wave<1>(G, xb, n, point, lane, win, s_w);
+      ok = axis_weights<1>(G, xb, n, point, lane, win, s_w, s_dw);
     else
-      ok = axis_weights_wave<2>(G, xb, n, point, lane, win, s_w);
+      ok = axis_weights<2>(G, xb, n, point, lane, win, s_w, s_dw);
     if (lane == 0) s_bad[wave] = ok ? 0 : 1;
   }
-  __syncthreads();
-  if (wave == 0)
-    axis_dweights_wave<0>(G, lane, win, s_w, s_dw);
-  else if (wave == 1)
-    axis_dweights_wave<1>(G, lane, win, s_w, s_dw);
-  else if (wave == 2)
-    axis_dweights_wave<2>(G, lane, win, s_w, s_dw);
-  __syncthreads();
-  return (s_bad[0] | s_bad[1] | s_bad[2]) == 0;
 }
 
 // Bubble handled by a workgroup: consecutive workgroups on one XCD take consecutive bubbles, so
 // a caller that orders its bubbles in space keeps each XCD's share of the force field in its L2.
 __device__ __forceinline__ int bubble_of_block(int nb) { return (int)xcd_remap(blockIdx.x, nb); }
 
-__device__ __forceinline__ double block_sum(double v, double* s_red, int tid) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((tid & 63) == 0) s_red[tid >> 6] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int w = 0; w < kBlockWaves; ++w) t += s_red[w];
-  return t;
-}
-
-// block_sum of six values at once, behind one barrier: the same butterfly in each wavefront and
-// the same order over the wavefronts, so each sum has the bits block_sum gives it.
+// Sums of six values over the workgroup behind one barrier: a butterfly in each wavefront, then the
+// wavefronts in order.
 __device__ __forceinline__ void block_sum6(double v[6], double (*s_red6)[kBlockWaves], int tid) {
 #pragma unroll
   for (int m = 0; m < 6; ++m) v[m] = wave_sum(v[m]);
@@ -277,27 +306,21 @@ __device__ TileRanges tile_ranges(int vlo, int vhi, int ext, int tile, bool peri
   return t;
 }
 
-// Force window of a bubble at x0 (the clipped stencil window [clo, chi] of each axis).
-__device__ bool force_windows(const Geom& G, const double x0[3], double n, Axis win[3]) {
-  const int ext[3] = {G.nx, G.ny, G.nz};
-  for (int a = 0; a < 3; ++a)
-    if (!axis_window(x0[a], n, ext[a], G.bc[2 * a] == BC_PER, win[a])) return false;
-  return true;
-}
-
 // Calls f(tile) for every tile of the ranges tr, over the threads of the workgroup.
 template <class Fn>
 __device__ void for_tiles(const Geom& G, const TileRanges tr[3], int tid, int nthreads, Fn&& f) {
   for (int rz = 0; rz < tr[2].n; ++rz)
     for (int ry = 0; ry < tr[1].n; ++ry)
       for (int rx = 0; rx < tr[0].n; ++rx) {
-        const int nx_ = tr[0].hi[rx] - tr[0].lo[rx] + 1;
-        const int ny_ = tr[1].hi[ry] - tr[1].lo[ry] + 1;
-        const int nz_ = tr[2].hi[rz] - tr[2].lo[rz] + 1;
+        // selected, not indexed: the ranges stay in registers
+        const int x0 = rx ? tr[0].lo[1] : tr[0].lo[0], x1 = rx ? tr[0].hi[1] : tr[0].hi[0];
+        const int y0 = ry ? tr[1].lo[1] : tr[1].lo[0], y1 = ry ? tr[1].hi[1] : tr[1].hi[0];
+        const int z0 = rz ? tr[2].lo[1] : tr[2].lo[0], z1 = rz ? tr[2].hi[1] : tr[2].hi[0];
+        const int nx_ = x1 - x0 + 1, ny_ = y1 - y0 + 1, nz_ = z1 - z0 + 1;
         for (int k = tid; k < nx_ * ny_ * nz_; k += nthreads) {
-          const int tx = tr[0].lo[rx] + k % nx_;
-          const int ty = tr[1].lo[ry] + (k / nx_) % ny_;
-          const int tz = tr[2].lo[rz] + k / (nx_ * ny_);
+          const int tx = x0 + k % nx_;
+          const int ty = y0 + (k / nx_) % ny_;
+          const int tz = z0 + k / (nx_ * ny_);
           f(((uint32_t)tz * G.tny + ty) * G.tnx + tx);
         }
       }
@@ -419,13 +442,15 @@ __device__ __forceinline__ void state_velocity(const T* __restrict__ src, const 
 // (20 000 bubbles with the earlier cell-by-cell loop: 394 us against 1289 us with 8 beside the
 // bulk launch; with the column sums, alone on the chip, 154 us with 4 against 177 us with 1).
 // FUSE (few bubbles on one lattice): the workgroup then also runs its bubble's update (k_ode's
-// arithmetic, one lane) and flags its tiles, so the step has one launch less. The fourth wavefront,
+// arithmetic, four lanes) and flags its tiles, so the step has one launch less. The fourth wavefront,
 // idle while the other three compute the weights, prepares the update's closure constants and
 // loads, and the update takes the sums from registers instead of reading them back.
 // Per-bubble constants of the Table 1 closures (they depend on the diameter only).
 struct BubbleConst {
   double V, r2pi, fb, inv_meff, va;  // volume, pi r^2, buoyancy, 1/m_eff, (1 + C_A) rho_l V
   double visc24, visc48, re_sat;     // 24 nu/d, 48 nu/d, Re beyond which 48/Re wins
+  double re_scale, cd_k;             // d / nu, k of the drag law
+  double drag, lift;                 // -1/2 s_D rho_l pi r^2 and -s_L rho_l V
   double shape;                      // 8/3 Eo/(Eo + 4)
   double f_lift;                     // f(Eo_d)
   double Eod;
@@ -442,6 +467,10 @@ __device__ BubbleConst bubble_constants(const bubble_params& P, double nu, doubl
   k.va = (1.0 + P.c_a) * P.rho_l * k.V;
   k.visc24 = 24.0 * nu / d;
   k.visc48 = 48.0 * nu / d;
+  k.re_scale = d / nu;
+  k.cd_k = P.cd_k;
+  k.drag = -0.5 * P.drag_scale * P.rho_l * k.r2pi;
+  k.lift = -P.lift_scale * P.rho_l * k.V;
   // 1 + k Re^0.687 >= 2 for Re >= (1/k)^(1/0.687): there the min{} of C_D is 48/Re
   k.re_sat = P.cd_k > 0.0 ? exp(log(1.0 / P.cd_k) / 0.687) : INFINITY;
   const double Eo = (P.rho_l - P.rho_b) * P.g * d * d / P.sigma;
@@ -452,11 +481,22 @@ __device__ BubbleConst bubble_constants(const bubble_params& P, double nu, doubl
   return k;
 }
 
-// The inputs of one bubble's update: its state before the step and the coupling sums of eq. (20).
+// The bubble update runs on a quad of lanes: lanes 0 to 2 hold the components x, y, z of every vector
+// (lane 3 repeats z), so that a component's arithmetic is one instruction for the three; scalars are
+// the same in every lane. One bubble's sub-steps are a chain that a single wavefront issues at four
+// cycles per instruction at best, so the number of instructions is what they cost.
+
+// Inputs of one bubble's update in lane q of its quad: its state before the step and the coupling sums
+// of eq. (20).
 struct OdeIn {
   int st;
   double valid, d;
-  double ul[3], wl[3], ulp[3], ub[3], xn[3];
+  double ul, wl, ulp, ub, xn;  // component min(q, 2)
+};
+// What the update leaves for the flags and the spreading: component min(q, 2) of the position at the
+// start and now, and of the reaction; the half-width.
+struct OdeOut3 {
+  double x0, xn, psi, n;
 };
 
 // What the fused update takes from the start of its workgroup: the closure constants and the
@@ -467,12 +507,13 @@ struct FusePre {
 };
 
 template <typename Geo>
-__device__ bool ode_lane(const Geo& geo, const BubbleArgs& A, int b, double x0[3], double xn_out[3],
-                         double& n_out);
+__device__ bool ode_load_update(const Geo& geo, const BubbleArgs& A, int b, int q, OdeOut3& out);
 template <typename Geo>
-__device__ bool ode_update(const Geo& geo, const BubbleArgs& A, int b, const OdeIn& in,
-                           const BubbleConst* kc_in, const double* x0_in, double x0[3],
-                           double xn_out[3], double& n_out);
+__device__ bool ode_update(const Geo& geo, const BubbleArgs& A, int b, int q, const OdeIn& in,
+                           const BubbleConst* kc_in, OdeOut3& out);
+template <typename T>
+__device__ void spread_atomic(const Geom& G, T* __restrict__ F, const Axis win[3],
+                              double (*s_w)[kSpan], const double psi[3], int tid);
 
 // What the first workgroup of a step's first bubble kernel clears for the step.
 template <typename Geo>
@@ -501,48 +542,126 @@ __device__ void interp_bubble(const Geo& geo, const BubbleArgs& A, const int b) 
   // the bubble update of a bubble without a valid window: nothing but its cleared reaction
   auto ode_skip = [&] {
     if constexpr (FUSE) {
-      double x0[3], xn[3], m;
-      ode_lane(geo, A, b, x0, xn, m);
+      OdeOut3 o;
+      ode_load_update(geo, A, b, tid, o);
     }
   };
+  // the loads of the bubble at once (one round trip; the empty statement keeps them above the branch)
   const int st = A.S.state[b];
+  const double xb[3] = {A.S.x[b], A.S.y[b], A.S.z[b]};
+  const double d = A.S.d[b];
+  asm volatile("" ::"v"(xb[0]), "v"(xb[1]), "v"(xb[2]), "v"(d));
   if (st == 0) {
-    if (tid == 0) {
+    if (tid < 4) {
       work[W_VALID] = 0.0;
       ode_skip();
     }
     return;
   }
-  const double xb[3] = {A.S.x[b], A.S.y[b], A.S.z[b]};
-  const double d = A.S.d[b];
   const double n = A.P.kernel_factor * d;
   Axis win[3];
   const bool finite = isfinite(xb[0]) && isfinite(xb[1]) && isfinite(xb[2]) && d > 0.0;
   const bool point = A.P.coupling & LBM_COUPLING_POINT_KERNEL;
   __shared__ FusePre s_pre;
+  __shared__ int s_bad[3];
+  auto invalid = [&] {  // no window, or no weights: the bubble is skipped
+    if (tid < 4) {
+      work[W_VALID] = 0.0;
+      if (tid == 0) atomicOr(A.status, (int32_t)STATUS_STENCIL_TOO_LARGE);
+      ode_skip();
+    }
+  };
+  if (!finite || !windows(G, xb, n, win)) {
+    invalid();
+    return;
+  }
   if constexpr (FUSE) {
     // wavefront 3 has no axis to weigh: it prepares the update's constants and loads meanwhile
     static_assert(kBlock >= 256, "a fourth wavefront");
     if (tid == 192) {
-      s_pre.kc = bubble_constants(geo.params(A.P, b), col.nu, d);
       s_pre.ub[0] = A.S.ux[b];
       s_pre.ub[1] = A.S.uy[b];
       s_pre.ub[2] = A.S.uz[b];
       s_pre.ulp[0] = A.S.ulx[b];
       s_pre.ulp[1] = A.S.uly[b];
       s_pre.ulp[2] = A.S.ulz[b];
+      s_pre.kc = bubble_constants(geo.params(A.P, b), col.nu, d);
     }
   }
-  if (!finite || !build_weights(G, xb, n, tid, s_w, s_dw, win, point)) {
-    if (tid == 0) {
-      work[W_VALID] = 0.0;
-      atomicOr(A.status, (int32_t)STATUS_STENCIL_TOO_LARGE);
-      ode_skip();
+  const int Dx = win[0].dhi - win[0].dlo + 1;
+  const int Dy = win[1].dhi - win[1].dlo + 1;
+  const int Dz = win[2].dhi - win[2].dlo + 1;
+  const bool px = G.bc[0] == BC_PER, py = G.bc[2] == BC_PER, pz = G.bc[4] == BC_PER;
+  const T* __restrict__ S = nullptr;  // exact-time coupling: the current state
+  if constexpr (EXACT) S = static_cast<const T*>(geo.state);
+  // Separable sums by window column: a thread takes the column (i, j) of the window over a slab of z
+  // (one slab unless the window has fewer columns than the workgroup has threads) and sums along z
+  // the velocity times the z weight and times the z derivative weight; the column's x and y weights
+  // then enter once:
+  //   sum_k wa wb wc_k u = wa wb Sw,  curl terms from wa db Sw, wa wb Sd and da wb Sw,
+  // with Sw = sum_k wc_k u_k and Sd = sum_k dc_k u_k. Consecutive lanes take consecutive x, and the
+  // three components are read at one 32-bit offset from their planes' bases. The loads of GATHER z
+  // cells are issued together, the sums then taken in z order; with few bubbles a thread's first
+  // loads are issued before the weights are computed, so that their round trip overlaps it.
+  constexpr int kZ = GATHER;
+  constexpr bool kEarly = !EXACT && GATHER >= 8;
+  const int cols = Dx * Dy;
+  const int slabs = min(max(1, kBlock / cols), Dz);
+  const uint32_t plane = (uint32_t)G.nx * (uint32_t)G.ny;
+  const uint32_t wrap_back = (uint32_t)G.nz * plane;
+  const T* __restrict__ Ux = U;
+  const T* __restrict__ Uy = U + G.N;
+  const T* __restrict__ Uz = U + 2 * (size_t)G.N;
+  struct Column {
+    int ci, cj, k, k1, z;  // column, next and last z cell of the slab, lattice z
+    uint32_t c;
+  };
+  auto column = [&](int t) {
+    Column w;
+    const int colm = t % cols, slab = t / cols;
+    w.ci = colm % Dx;
+    w.cj = colm / Dx;
+    w.k = slab * Dz / slabs;
+    w.k1 = (slab + 1) * Dz / slabs;
+    const int vx = win[0].dlo + w.ci, vy = win[1].dlo + w.cj, vz = win[2].dlo + w.k;
+    const int x = px ? wrapi(vx, G.nx) : vx;
+    const int y = py ? wrapi(vy, G.ny) : vy;
+    w.z = pz ? wrapi(vz, G.nz) : vz;
+    w.c = ((uint32_t)w.z * G.ny + y) * G.nx + x;
+    return w;
+  };
+  auto fetch = [&](Column& w, T (*u)[3]) {
+#pragma clang loop unroll(full)
+    for (int s = 0; s < kZ; ++s) {
+      if (w.k + s < w.k1) {
+        u[s][0] = Ux[w.c];
+        u[s][1] = Uy[w.c];
+        u[s][2] = Uz[w.c];
+        w.c += plane;
+        if (++w.z == G.nz) {  // periodic z only: a clipped window ends inside the domain
+          w.z = 0;
+          w.c -= wrap_back;
+        }
+      }
     }
+  };
+  Column first = {0, 0, 0, 0, 0, 0u};
+  T u0[kZ][3];
+  if constexpr (kEarly) {
+    if (tid < cols * slabs) {
+      first = column(tid);
+      fetch(first, u0);
+    }
+  }
+  build_weights(G, xb, n, tid, s_w, s_dw, win, point, s_bad);
+  __syncthreads();
+  if (s_bad[0] | s_bad[1] | s_bad[2]) {
+    invalid();
     return;
   }
-  // the weights at x0 for the spreading of this step
-  for (int i = tid; i < 3 * kSpan; i += kBlock) work[W_WGT + i] = s_w[i / kSpan][i % kSpan];
+  // the weights at x0 for the spreading of this step (used by other kernels: several bubbles)
+  if (geo.use_lists())
+    for (int i = tid; i < 3 * kSpan; i += kBlock) work[W_WGT + i] = s_w[i / kSpan][i % kSpan];
   // enter the bubble in the list of every tile of its force window: the slot of each thread's
   // first tile is taken now and written after the gather, so the atomic is in flight meanwhile
   uint32_t t0 = 0, slot0 = kTileCap;
@@ -564,15 +683,9 @@ __device__ void interp_bubble(const Geo& geo, const BubbleArgs& A, const int b) 
       if (slot < kTileCap) tlist[(size_t)t * kTileCap + slot] = (uint32_t)b;
     }
   }
-  const int Dx = win[0].dhi - win[0].dlo + 1;
-  const int Dy = win[1].dhi - win[1].dlo + 1;
-  const int Dz = win[2].dhi - win[2].dlo + 1;
-  const int total = Dx * Dy * Dz;
-  const bool px = G.bc[0] == BC_PER, py = G.bc[2] == BC_PER, pz = G.bc[4] == BC_PER;
-  const T* __restrict__ S = nullptr;  // exact-time coupling: the current state
-  if constexpr (EXACT) S = static_cast<const T*>(geo.state);
   double acc[6] = {0, 0, 0, 0, 0, 0};
   if constexpr (EXACT) {
+    const int total = cols * Dz;
     // The thread's window entries f = tid, tid + kBlock, ... as f = i + Dx (j + Dy k), stepped by
     // kBlock entries with carries (one division per thread); each cell's velocity (from the
     // state) times its weight and curl weights into the six sums.
@@ -611,60 +724,35 @@ __device__ void interp_bubble(const Geo& geo, const BubbleArgs& A, const int b) 
       ck += dk;
     }
   } else {
-    // Separable sums by window column: a thread takes the column (i, j) of the window over a
-    // slab of z (one slab unless the window has fewer columns than the workgroup has threads)
-    // and sums along z the velocity times the z weight and times the z derivative weight; the
-    // column's x and y weights then enter once:
-    //   sum_k wa wb wc_k u = wa wb Sw,  curl terms from wa db Sw, wa wb Sd and da wb Sw,
-    // with Sw = sum_k wc_k u_k and Sd = sum_k dc_k u_k. Consecutive lanes take consecutive x, and
-    // the three components are read at one 32-bit offset from their planes' bases. The loads of
-    // GATHER z cells are issued together, the sums then taken in z order.
-    constexpr int kZ = GATHER;
-    const int cols = Dx * Dy;
-    const int slabs = min(max(1, kBlock / cols), Dz);
-    const uint32_t plane = (uint32_t)G.nx * (uint32_t)G.ny;
-    const uint32_t wrap_back = (uint32_t)G.nz * plane;
-    const T* __restrict__ Ux = U;
-    const T* __restrict__ Uy = U + G.N;
-    const T* __restrict__ Uz = U + 2 * (size_t)G.N;
     const int iz_base = win[2].dlo - win[2].lo + 1;
     for (int t = tid; t < cols * slabs; t += kBlock) {
-      const int colm = t % cols, slab = t / cols;
-      const int ci = colm % Dx, cj = colm / Dx;
-      const int k0 = slab * Dz / slabs, k1 = (slab + 1) * Dz / slabs;
-      const int vx = win[0].dlo + ci, vy = win[1].dlo + cj, vz = win[2].dlo + k0;
-      const int x = px ? wrapi(vx, G.nx) : vx;
-      const int y = py ? wrapi(vy, G.ny) : vy;
-      int z = pz ? wrapi(vz, G.nz) : vz;
-      uint32_t c = ((uint32_t)z * G.ny + y) * G.nx + x;
+      Column w = first;
+      T u[kZ][3];
+      if (kEarly && t == tid) {
+#pragma clang loop unroll(full)
+        for (int s = 0; s < kZ; ++s)
+          for (int m = 0; m < 3; ++m) u[s][m] = u0[s][m];
+      } else {
+        w = column(t);
+        fetch(w, u);
+      }
       double sw[3] = {0.0, 0.0, 0.0}, sd[3] = {0.0, 0.0, 0.0};
-      for (int k = k0; k < k1; k += kZ) {
-        T u[kZ][3];
+      for (;;) {
 #pragma clang loop unroll(full)
         for (int s = 0; s < kZ; ++s) {
-          if (k + s < k1) {
-            u[s][0] = Ux[c];
-            u[s][1] = Uy[c];
-            u[s][2] = Uz[c];
-            c += plane;
-            if (++z == G.nz) {  // periodic z only: a clipped window ends inside the domain
-              z = 0;
-              c -= wrap_back;
-            }
-          }
-        }
-#pragma clang loop unroll(full)
-        for (int s = 0; s < kZ; ++s) {
-          if (k + s < k1) {
-            const double wc = s_w[2][iz_base + k + s], dc = s_dw[2][iz_base + k + s];
+          if (w.k + s < w.k1) {
+            const double wc = s_w[2][iz_base + w.k + s], dc = s_dw[2][iz_base + w.k + s];
             for (int m = 0; m < 3; ++m) {
               sw[m] += wc * (double)u[s][m];
               sd[m] += dc * (double)u[s][m];
             }
           }
         }
+        w.k += kZ;
+        if (w.k >= w.k1) break;
+        fetch(w, u);
       }
-      const int ix = vx - win[0].lo + 1, iy = vy - win[1].lo + 1;
+      const int ix = win[0].dlo + w.ci - win[0].lo + 1, iy = win[1].dlo + w.cj - win[1].lo + 1;
       const double wa = s_w[0][ix], da = s_dw[0][ix];
       const double wb = s_w[1][iy], db = s_dw[1][iy];
       const double w_ab = wa * wb, w_adb = wa * db, w_dab = da * wb;
@@ -688,307 +776,319 @@ __device__ void interp_bubble(const Geo& geo, const BubbleArgs& A, const int b) 
   if constexpr (FUSE) {
     // the update's inputs are at hand: the sums (in every thread), the position, a valid window
     // and what wavefront 3 prepared; the force window at x0 is win
-    __shared__ double s_xn[3];
+    __shared__ double s_xn[3], s_psi[3];
     __shared__ int s_flag;
-    if (tid == 0) {
+    if (tid < 4) {
+      const int c = tid < 2 ? tid : 2;
       OdeIn in;
       in.st = st;
       in.valid = 1.0;
       in.d = d;
-      for (int a = 0; a < 3; ++a) {
-        in.ul[a] = acc[a];
-        in.wl[a] = acc[3 + a];
-        in.ulp[a] = s_pre.ulp[a];
-        in.ub[a] = s_pre.ub[a];
-        in.xn[a] = xb[a];
-      }
-      double x0[3], xn[3], m = 0.0;
-      s_flag = ode_update(geo, A, b, in, &s_pre.kc, xb, x0, xn, m) ? 1 : 0;
-      for (int a = 0; a < 3; ++a) s_xn[a] = xn[a];
+      in.ul = c == 0 ? acc[0] : c == 1 ? acc[1] : acc[2];
+      in.wl = c == 0 ? acc[3] : c == 1 ? acc[4] : acc[5];
+      in.ulp = s_pre.ulp[c];
+      in.ub = s_pre.ub[c];
+      in.xn = c == 0 ? xb[0] : c == 1 ? xb[1] : xb[2];
+      OdeOut3 o;
+      const bool moved = ode_update(geo, A, b, tid, in, &s_pre.kc, o);
+      s_flag = moved ? 1 : 0;
+      s_xn[c] = o.xn;
+      s_psi[c] = o.psi;
     }
     __syncthreads();
     if (s_flag) {
       const double xn[3] = {s_xn[0], s_xn[1], s_xn[2]};
+      // one bubble on the lattice: its weights are at hand, so the workgroup also spreads its force
+      if (!geo.use_lists()) {
+        const double psi[3] = {s_psi[0], s_psi[1], s_psi[2]};
+        spread_atomic<T>(G, col.F, win, s_w, psi, tid);
+      }
       mark_tiles<T>(col, A, win, xn, n, tid, kBlock);
     }
   }
 }
 
 template <typename T, typename Geo, bool EXACT = false, int GATHER = 1, bool FUSE = false>
-__global__ __launch_bounds__(kBlock) void k_interp(Geo geo, BubbleArgs A) {
+__global__ __launch_bounds__(kBlock, FUSE ? 2 : 1) void k_interp(Geo geo, BubbleArgs A) {
   if (blockIdx.x == 0 && threadIdx.x == 0) clear_for_step(geo);
   interp_bubble<T, Geo, EXACT, GATHER, FUSE>(geo, A, bubble_of_block(A.nb));
+  if (FUSE && !geo.use_lists()) advance_traj_row(A);  // no spreading kernel follows
 }
 
 // ---------------------------------------------------------------------------------------------
 // Bubble dynamics, one lane per bubble.
 // ---------------------------------------------------------------------------------------------
 
-// Drag and lift of Table 1 on a bubble moving at ub in liquid of velocity ul and vorticity wl,
-// with Re = |u_r| d / nu (eq. (3)). C_D is used multiplied by |u_r| so that the viscous
-// branches stay finite at u_r = 0: 24/Re |u_r| = 24 nu / d.
-__device__ __forceinline__ void drag_lift(const bubble_params& P, const BubbleConst& k, double d,
-                                          double nu, const double ub[3], const double ul[3],
-                                          const double wl[3], double FD[3], double FL[3]) {
-  const double ur[3] = {ub[0] - ul[0], ub[1] - ul[1], ub[2] - ul[2]};
-  const double mag = sqrt(ur[0] * ur[0] + ur[1] * ur[1] + ur[2] * ur[2]);
-  const double Re = mag * d / nu;
-  double visc = k.visc48;
-  if (Re < k.re_sat && Re > 0.0)
-    visc = fmin(k.visc24 * (1.0 + P.cd_k * exp(0.687 * log(Re))), k.visc48);
-  else if (Re == 0.0)
-    visc = fmin(k.visc24, k.visc48);
-  const double cdu = fmax(visc, k.shape * mag);
-  double cl;
-  if (k.Eod < 4.0)
-    cl = fmin(0.288 * tanh(0.121 * Re), k.f_lift);
-  else if (k.Eod <= 10.0)
-    cl = k.f_lift;
-  else
-    cl = -0.29;
-  const double dpre = -0.5 * P.drag_scale * cdu * P.rho_l * k.r2pi;
-  for (int a = 0; a < 3; ++a) FD[a] = dpre * ur[a];
-  const double cr[3] = {ur[1] * wl[2] - ur[2] * wl[1], ur[2] * wl[0] - ur[0] * wl[2],
-                        ur[0] * wl[1] - ur[1] * wl[0]};
-  const double lpre = -P.lift_scale * cl * P.rho_l * k.V;
-  for (int a = 0; a < 3; ++a) FL[a] = lpre * cr[a];
+// The transcendental functions of the closures for one lane, whose latency is all they cost: ordinary
+// arguments only (positive and normal, or handled by the caller), short chains (polynomials in pairs
+// of terms), no branches. With the library's log, exp, tanh, division and square root a sub-step took
+// 2.2 us of the lane's time, most of it these.
+
+// a / b and sqrt(a): the hardware approximation, two Newton steps and a residual correction.
+__device__ __forceinline__ double quick_div(double a, double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(r, fma(-b, r, 1.0), r);
+  r = fma(r, fma(-b, r, 1.0), r);
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double quick_sqrt(double a) {
+  const double y = __builtin_amdgcn_rsq(fmax(a, 1e-300));  // roots below 1e-150 come out smaller, 0 as 0
+  double g = a * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, a), h, g);
+  return fma(fma(-g, g, a), h, g);
 }
 
-// The bubble update of one lane's bubble. Returns true when the bubble's tiles are left to flag
-// (several bubbles on one lattice), with its start position x0, new position xn and half-width n.
+// exp(f) - 1 for |f| <= ln(2)/2 by its Taylor series to f^14 (the next term is below 1e-18 of f).
+__device__ __forceinline__ double expm1_small(double f) {
+  const double f2 = f * f, f4 = f2 * f2;
+  const double a0 = fma(f, 1.0 / 6.0, 0.5), a1 = fma(f, 1.0 / 120.0, 1.0 / 24.0);
+  const double a2 = fma(f, 1.0 / 5040.0, 1.0 / 720.0), a3 = fma(f, 1.0 / 362880.0, 1.0 / 40320.0);
+  const double a4 = fma(f, 1.0 / 39916800.0, 1.0 / 3628800.0);
+  const double a5 = fma(f, 1.0 / 6227020800.0, 1.0 / 479001600.0);
+  const double b0 = fma(a1, f2, a0), b1 = fma(a3, f2, a2);
+  const double b2 = fma(fma(f2, 1.0 / 87178291200.0, a5), f2, a4);
+  return fma(f2, fma(fma(b2, f4, b1), f4, b0), f);
+}
+
+// log(a): with a = 2^e m, m in [sqrt(1/2), sqrt(2)), log m is the series of 2 atanh((m - 1)/(m + 1)).
+__device__ __forceinline__ double quick_log(double a) {
+  int e = __builtin_amdgcn_frexp_exp(a);
+  double m = __builtin_amdgcn_frexp_mant(a);  // [1/2, 1)
+  const bool low = m < 0.70710678118654752440;
+  m = low ? m + m : m;
+  e = low ? e - 1 : e;
+  const double s = quick_div(m - 1.0, m + 1.0), t = s * s, t2 = t * t, t4 = t2 * t2;
+  const double a0 = fma(t, 2.0 / 5.0, 2.0 / 3.0), a1 = fma(t, 2.0 / 9.0, 2.0 / 7.0);
+  const double a2 = fma(t, 2.0 / 13.0, 2.0 / 11.0), a3 = fma(t, 2.0 / 17.0, 2.0 / 15.0);
+  const double a4 = fma(t, 2.0 / 21.0, 2.0 / 19.0);
+  const double b0 = fma(a1, t2, a0), b1 = fma(a3, t2, a2);
+  const double series = fma(fma(a4, t4, b1), t4, b0);  // log m = 2 s + s t series
+  constexpr double ln2_hi = 0x1.62e42fefa3800p-1, ln2_lo = 0x1.ef35793c76730p-45;
+  return fma((double)e, ln2_hi, fma((double)e, ln2_lo, fma(s * t, series, s + s)));
+}
+
+// v of the lanes of the quad that SEL names (two bits per lane).
+template <int SEL>
+__device__ __forceinline__ double quad(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, SEL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), SEL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+template <int SEL>
+__device__ __forceinline__ uint32_t quad_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, SEL, 0xf, 0xf, true);
+}
+constexpr int kQuad0 = 0x00, kQuad1 = 0x55, kQuad2 = 0xaa;  // component x, y, z in every lane
+constexpr int kQuadNext = 1 | 2 << 2, kQuadAfter = 2 | 0 << 2 | 1 << 4 | 1 << 6;  // component a + 1, a + 2
+
+// Drag and lift of Table 1 (component min(q, 2)) on a bubble moving at ub in liquid of velocity ul and
+// vorticity wl, with Re = |u_r| d / nu (eq. (3)); wl1, wl2: components a + 1, a + 2 of wl. C_D is used
+// multiplied by |u_r| so that the viscous branches stay finite at u_r = 0: 24/Re |u_r| = 24 nu / d.
+// Re^0.687 = 2^(0.687 log2 Re) is lane 0's and tanh(0.121 Re) = w/(w + 2), w = exp(0.242 Re) - 1,
+// lane 1's: they share the exponential.
+__device__ __forceinline__ void drag_lift(const BubbleConst& k, int q, double ub, double ul, double wl1,
+                                          double wl2, double& FD, double& FL) {
+  const double ur = ub - ul;
+  const double ux = quad<kQuad0>(ur), uy = quad<kQuad1>(ur), uz = quad<kQuad2>(ur);
+  const double mag = quick_sqrt(fma(ux, ux, fma(uy, uy, uz * uz)));
+  const double Re = mag * k.re_scale;
+  constexpr double ln2_hi = 0x1.62e42fefa3800p-1, ln2_lo = 0x1.ef35793c76730p-45;
+  // exponents: 0.687 log Re, and 0.242 Re up to where tanh rounds to 1
+  const double y = q == 1 ? 2.0 * fmin(0.121 * Re, 25.0) : 0.687 * quick_log(fmax(Re, 1e-290));
+  const double n = rint(y * 1.4426950408889634074);
+  const double f = fma(-n, ln2_lo, fma(-n, ln2_hi, y));
+  const double p = __builtin_amdgcn_ldexp(1.0, (int)n), e = expm1_small(f);
+  const double w = fma(p, e, p - 1.0);
+  const double value = q == 1 ? quick_div(w, w + 2.0) : fma(p, e, p);
+  const double pw = quad<kQuad0>(value), th = quad<kQuad1>(value);
+  const double viscous = fmin(k.visc24 * fma(k.cd_k, pw, 1.0), k.visc48);
+  const double visc = Re < k.re_sat ? viscous : k.visc48;
+  const double cdu = fmax(visc, k.shape * mag);
+  const double rising = fmin(0.288 * th, k.f_lift);
+  const double cl = k.Eod < 4.0 ? rising : (k.Eod <= 10.0 ? k.f_lift : -0.29);
+  FD = k.drag * cdu * ur;
+  FL = k.lift * cl * (quad<kQuadNext>(ur) * wl2 - quad<kQuadAfter>(ur) * wl1);
+}
+
+// The bubble update of a quad whose bubble's inputs are in memory. Returns true when the bubble moved.
 template <typename Geo>
-__device__ bool ode_lane(const Geo& geo, const BubbleArgs& A, int b, double x0[3], double xn_out[3],
-                         double& n_out) {
+__device__ bool ode_load_update(const Geo& geo, const BubbleArgs& A, int b, int q, OdeOut3& out) {
   const double* work = A.S.work + (size_t)b * kWork;
+  const int c = q < 2 ? q : 2;
+  auto pick = [&](const double* x, const double* y, const double* z) {
+    return (c == 0 ? x : c == 1 ? y : z)[b];
+  };
   // every load of the update at once (one round trip; all in bounds for b < nb)
   OdeIn in;
   in.st = A.S.state[b];
   in.valid = work[W_VALID];
   in.d = A.S.d[b];
-  for (int a = 0; a < 3; ++a) {
-    in.ul[a] = work[W_UL + a];
-    in.wl[a] = work[W_WL + a];
-  }
-  in.ulp[0] = A.S.ulx[b];
-  in.ulp[1] = A.S.uly[b];
-  in.ulp[2] = A.S.ulz[b];
-  in.ub[0] = A.S.ux[b];
-  in.ub[1] = A.S.uy[b];
-  in.ub[2] = A.S.uz[b];
-  in.xn[0] = A.S.x[b];
-  in.xn[1] = A.S.y[b];
-  in.xn[2] = A.S.z[b];
+  in.ul = work[W_UL + c];
+  in.wl = work[W_WL + c];
+  in.ulp = pick(A.S.ulx, A.S.uly, A.S.ulz);
+  in.ub = pick(A.S.ux, A.S.uy, A.S.uz);
+  in.xn = pick(A.S.x, A.S.y, A.S.z);
   // the values as operands of an empty statement: the compiler keeps the loads above the branch
   // of the update instead of moving them into the branch's live path (a second round trip)
-  asm volatile("" ::"v"(in.d), "v"(in.ul[0]), "v"(in.ul[1]), "v"(in.ul[2]), "v"(in.wl[0]),
-               "v"(in.wl[1]), "v"(in.wl[2]), "v"(in.ulp[0]), "v"(in.ulp[1]), "v"(in.ulp[2]),
-               "v"(in.ub[0]), "v"(in.ub[1]), "v"(in.ub[2]), "v"(in.xn[0]), "v"(in.xn[1]),
-               "v"(in.xn[2]));
-  return ode_update(geo, A, b, in, nullptr, nullptr, x0, xn_out, n_out);
+  asm volatile("" ::"v"(in.d), "v"(in.ul), "v"(in.wl), "v"(in.ulp), "v"(in.ub), "v"(in.xn));
+  return ode_update(geo, A, b, q, in, nullptr, out);
 }
 
-// The update itself from its inputs; kc_in and x0_in, when given, are the closure constants and
-// the window position already at hand (otherwise computed, and read from the bubble's work area).
+// The update itself by lane q of the bubble's quad; kc_in, when given, are the closure constants
+// already at hand.
 template <typename Geo>
-__device__ bool ode_update(const Geo& geo, const BubbleArgs& A, int b, const OdeIn& in,
-                           const BubbleConst* kc_in, const double* x0_in, double x0[3],
-                           double xn_out[3], double& n_out) {
+__device__ bool ode_update(const Geo& geo, const BubbleArgs& A, int b, int q, const OdeIn& in,
+                           const BubbleConst* kc_in, OdeOut3& out) {
   const ColumnView<float> col = geo.template view<float>(b);
   const Geom& G = col.G;
-  const double nu = col.nu;
   const bubble_params P = geo.params(A.P, b);
   double* work = A.S.work + (size_t)b * kWork;
+  const int c = q < 2 ? q : 2;       // this lane's component
+  const bool store = q < 3;          // lane 3 repeats lane 2
   const int st = in.st;
-  const double valid = in.valid;
-  const double d = in.d;
-  const double ul[3] = {in.ul[0], in.ul[1], in.ul[2]};
-  const double wl[3] = {in.wl[0], in.wl[1], in.wl[2]};
-  const double ulp[3] = {in.ulp[0], in.ulp[1], in.ulp[2]};
-  double ub[3] = {in.ub[0], in.ub[1], in.ub[2]};
-  double xn[3] = {in.xn[0], in.xn[1], in.xn[2]};
+  const double ul = in.ul;
+  double ub = in.ub, xn = in.xn;
+  out.x0 = out.xn = xn;
+  out.psi = 0.0;
+  out.n = P.kernel_factor * in.d;
+  auto put = [&](double* x, double* y, double* z, double v) {
+    if (store) (c == 0 ? x : c == 1 ? y : z)[b] = v;
+  };
   // the armed step record: the state before the update (what k_record's two stages copy)
   double* rec = A.rec ? A.rec + (size_t)b * R_SIZE : nullptr;
   if (rec) {
-    for (int a = 0; a < 3; ++a) {
-      rec[R_X + a] = xn[a];
-      rec[R_UB + a] = ub[a];
-      rec[R_ULP + a] = ulp[a];
-      rec[R_UL + a] = ul[a];
-      rec[R_WL + a] = wl[a];
+    if (store) {
+      rec[R_X + c] = xn;
+      rec[R_UB + c] = ub;
+      rec[R_ULP + c] = in.ulp;
+      rec[R_UL + c] = ul;
+      rec[R_WL + c] = in.wl;
     }
-    rec[R_STATE] = (double)st;
-    rec[R_D] = d;
-    rec[R_VALID] = valid;
-    rec[R_SUB] = 0.0;
+    if (q == 0) {
+      rec[R_STATE] = (double)st;
+      rec[R_D] = in.d;
+      rec[R_VALID] = in.valid;
+      rec[R_SUB] = 0.0;
+    }
   }
-  auto record_position = [&](const double* xp) {
+  auto record_position = [&](double xp) {
     if (A.traj) {
       const uint32_t row = *A.traj_row;
-      if (row < (uint32_t)A.traj_rows)
-        for (int a = 0; a < 3; ++a) A.traj[(size_t)row * 3 * A.nb + (size_t)a * A.nb + b] = xp[a];
+      if (row < (uint32_t)A.traj_rows && store) A.traj[(size_t)row * 3 * A.nb + (size_t)c * A.nb + b] = xp;
     }
   };
-  if (st == 0 || valid == 0.0) {
+  if (st == 0 || in.valid == 0.0) {
     record_position(xn);  // unchanged
-    if (rec)
-      for (int a = 0; a < 3; ++a) rec[R_PSI + a] = work[W_PSI + a];
-    if (A.S.psix) {
-      A.S.psix[b] = 0.0;
-      A.S.psiy[b] = 0.0;
-      A.S.psiz[b] = 0.0;
-    }
+    if (rec && store) rec[R_PSI + c] = work[W_PSI + c];
+    if (A.S.psix) put(A.S.psix, A.S.psiy, A.S.psiz, 0.0);
     return false;
   }
-  const int ext[3] = {G.nx, G.ny, G.nz};
-  double dul[3] = {0.0, 0.0, 0.0};
-  if (st == 2) {  // material derivative of u_l along the path, dt_l = 1
-    dul[0] = ul[0] - ulp[0];
-    dul[1] = ul[1] - ulp[1];
-    dul[2] = ul[2] - ulp[2];
-  }
+  // material derivative of u_l along the path, dt_l = 1
+  const double dul = st == 2 ? ul - in.ulp : 0.0;
   BubbleConst kc;
   if (kc_in)
     kc = *kc_in;
   else
-    kc = bubble_constants(P, nu, d);
-  const double dt = 1.0 / P.n_sub;
+    kc = bubble_constants(P, col.nu, in.d);
+  const double dt = 1.0 / P.n_sub, dt_m = dt * kc.inv_meff;
   const int reaction = P.coupling & LBM_REACTION_MASK;
   const double m_b = P.rho_b * kc.V;
+  // the force that does not change over the sub-steps: stress gradient and buoyancy
+  const double steady = kc.va * dul, fb = c == 2 ? kc.fb : 0.0;
+  const double wl1 = quad<kQuadNext>(in.wl), wl2 = quad<kQuadAfter>(in.wl);
   // sums over the sub-steps of F_D + F_L and of the net force m_b du_b/dt (reaction variants)
-  double s_dl[3] = {0.0, 0.0, 0.0}, s_net[3] = {0.0, 0.0, 0.0};
+  double s_dl = 0.0, s_net = 0.0;
   // the record keeps the velocity at the start of each sub-step and the clamp flags
   double* rec_ubs = rec && P.n_sub <= kRecordMaxSub ? rec + R_UBS : nullptr;
   uint32_t clamp0 = 0u, clamp1 = 0u, clamp2 = 0u;  // bits 0-31, 32-63, 64-95
-  for (int k = 0; k < P.n_sub; ++k) {
-    if (rec_ubs)
-      for (int a = 0; a < 3; ++a) rec_ubs[3 * k + a] = ub[a];
+  const int ext = c == 0 ? G.nx : c == 1 ? G.ny : G.nz;
+  const bool per = (c == 0 ? G.bc[0] : c == 1 ? G.bc[2] : G.bc[4]) == BC_PER;
+  const bool any_per = G.bc[0] == BC_PER || G.bc[2] == BC_PER || G.bc[4] == BC_PER;
+  // walls: x and y are held to [0, ext - 1], z from below (the top stops the bubble instead)
+  const double top = c == 2 ? INFINITY : ext - 1.0;
+  double FD, FL;
+  // the pass after the last sub-step evaluates the forces at the velocity it left (in the loop: code
+  // that runs once is bound by its instruction fetches)
+#pragma unroll 1
+  for (int k = 0;; ++k) {
+    if (rec_ubs && store) rec_ubs[3 * k + c] = ub;
+    drag_lift(kc, q, ub, ul, wl1, wl2, FD, FL);
+    if (k == P.n_sub) break;
     // (m_b + C_A rho_l V) du_b/dt = F_B + F_D + F_L + (1 + C_A) rho_l V D_t u_l
-    double FD[3], FL[3];
-    drag_lift(P, kc, d, nu, ub, ul, wl, FD, FL);
-    for (int a = 0; a < 3; ++a) {
-      double f = FD[a] + FL[a] + kc.va * dul[a];
-      if (a == 2) f += kc.fb;
-      s_dl[a] += FD[a] + FL[a];
-      s_net[a] += m_b * (f * kc.inv_meff);
-      ub[a] += dt * f * kc.inv_meff;
+    const double f = FD + FL + steady + fb;
+    s_dl += FD + FL;
+    s_net += m_b * (f * kc.inv_meff);
+    ub = fma(f, dt_m, ub);
+    xn = fma(dt, ub, xn);
+    if (any_per && per) {
+      xn = fmod(xn, (double)ext);
+      if (xn < 0.0) xn += (double)ext;
     }
-    for (int a = 0; a < 3; ++a) {
-      xn[a] += dt * ub[a];
-      if (G.bc[2 * a] == BC_PER) {
-        const double L = (double)ext[a];
-        xn[a] = fmod(xn[a], L);
-        if (xn[a] < 0.0) xn[a] += L;
-      } else {
-        bool clamped = false;
-        if (xn[a] < 0.0) {
-          xn[a] = 0.0;
-          ub[a] = 0.0;
-          clamped = true;
-        }
-        if (a != 2 && xn[a] > ext[a] - 1.0) {
-          xn[a] = ext[a] - 1.0;
-          ub[a] = 0.0;
-          clamped = true;
-        }
-        if (clamped) {
-          const int bit = 3 * k + a;
-          const uint32_t m = 1u << (bit & 31);
-          if (bit < 32)
-            clamp0 |= m;
-          else if (bit < 64)
-            clamp1 |= m;
-          else
-            clamp2 |= m;
-        }
-      }
+    const bool lo = xn < 0.0, hi = xn > top, clamped = !per && (lo || hi);
+    xn = clamped ? (lo ? 0.0 : top) : xn;
+    ub = clamped ? 0.0 : ub;
+    if (rec_ubs) {
+      const int bit = 3 * k + c;
+      const uint32_t m = clamped ? 1u << (bit & 31) : 0u;
+      clamp0 |= bit < 32 ? m : 0u;
+      clamp1 |= bit >= 32 && bit < 64 ? m : 0u;
+      clamp2 |= bit >= 64 ? m : 0u;
     }
   }
   if (rec_ubs) {
-    for (int a = 0; a < 3; ++a) rec_ubs[3 * P.n_sub + a] = ub[a];
-    rec[R_CLAMP] = (double)clamp0;
-    rec[R_CLAMP + 1] = (double)clamp1;
-    rec[R_CLAMP + 2] = (double)clamp2;
-    rec[R_SUB] = 1.0;
+    auto all = [](uint32_t v) { return quad_u<kQuad0>(v) | quad_u<kQuad1>(v) | quad_u<kQuad2>(v); };
+    clamp0 = all(clamp0);
+    clamp1 = all(clamp1);
+    clamp2 = all(clamp2);
+    if (q == 0) {
+      rec[R_CLAMP] = (double)clamp0;
+      rec[R_CLAMP + 1] = (double)clamp1;
+      rec[R_CLAMP + 2] = (double)clamp2;
+      rec[R_SUB] = 1.0;
+    }
   }
   // the reaction spread into the liquid (Algorithm 1, or a coupling variant)
-  double psi[3];
-  if (reaction == LBM_REACTION_SUBSTEP_MEAN) {
-    for (int a = 0; a < 3; ++a) psi[a] = -s_dl[a] / P.n_sub;
-  } else if (reaction == LBM_REACTION_NET_FORCE) {
-    for (int a = 0; a < 3; ++a) psi[a] = -s_net[a] / P.n_sub;
-  } else {
-    double FD[3], FL[3];
-    drag_lift(P, kc, d, nu, ub, ul, wl, FD, FL);
-    for (int a = 0; a < 3; ++a) psi[a] = -(FD[a] + FL[a]);
-  }
-  A.S.x[b] = xn[0];
-  A.S.y[b] = xn[1];
-  A.S.z[b] = xn[2];
+  double psi = -(FD + FL);
+  if (reaction == LBM_REACTION_SUBSTEP_MEAN) psi = -s_dl / P.n_sub;
+  if (reaction == LBM_REACTION_NET_FORCE) psi = -s_net / P.n_sub;
+  put(A.S.x, A.S.y, A.S.z, xn);
   record_position(xn);
-  A.S.ux[b] = ub[0];
-  A.S.uy[b] = ub[1];
-  A.S.uz[b] = ub[2];
-  A.S.ulx[b] = ul[0];
-  A.S.uly[b] = ul[1];
-  A.S.ulz[b] = ul[2];
-  int nst = 2;
-  if (G.bc[4] != BC_PER && xn[2] >= ext[2] - 1.0) nst = 0;  // reached the top layer
-  A.S.state[b] = nst;
-  for (int a = 0; a < 3; ++a) work[W_PSI + a] = psi[a];
-  if (rec)
-    for (int a = 0; a < 3; ++a) rec[R_PSI + a] = psi[a];
-  if (A.S.psix) {
-    A.S.psix[b] = psi[0];
-    A.S.psiy[b] = psi[1];
-    A.S.psiz[b] = psi[2];
-  }
-  if (geo.use_lists()) {  // the spreading gathers per tile: the tiles are flagged by the wavefront
-    for (int a = 0; a < 3; ++a) {
-      x0[a] = x0_in ? x0_in[a] : work[W_X0 + a];
-      xn_out[a] = xn[a];
-    }
-    n_out = P.kernel_factor * d;
-    return true;
-  }
-  return false;
+  put(A.S.ux, A.S.uy, A.S.uz, ub);
+  put(A.S.ulx, A.S.uly, A.S.ulz, ul);
+  // lane 2 holds z: 0 once the bubble reached the top layer
+  if (q == 2) A.S.state[b] = !per && xn >= ext - 1.0 ? 0 : 2;
+  if (store) work[W_PSI + c] = psi;
+  if (rec && store) rec[R_PSI + c] = psi;
+  if (A.S.psix) put(A.S.psix, A.S.psiy, A.S.psiz, psi);
+  out.xn = xn;
+  out.psi = psi;
+  return true;
 }
 
-// Bubble dynamics, one lane per bubble (Table 1, eq. (1)-(4)). With several bubbles on one
-// lattice the tiles of each bubble (its force window at x0 and velocity window at the new
-// position) are then flagged: each lane its own bubble's when the wavefront holds many bubbles
-// (the lanes' loops run side by side), the whole wavefront one bubble after the other when it
-// holds a few (the tiles of one bubble then spread over the lanes).
-constexpr int kWaveFlagMaxBubbles = 16;
+// Bubble dynamics, a quad of lanes per bubble (Table 1, eq. (1)-(4)). With several bubbles on one
+// lattice each quad then flags its bubble's tiles (the force window at x0 and the velocity window at
+// the new position). 20 000 bubbles are 1250 wavefronts, about one per SIMD: as with one lane per bubble
+// the latency of a wavefront is the kernel's, and the quads' is less than half.
+constexpr int kOdeBubbles = 16;  // per wavefront
 
 template <typename Geo>
 __global__ __launch_bounds__(64) void k_ode(Geo geo, BubbleArgs A) {
-  const int b = blockIdx.x * 64 + threadIdx.x;
-  double x0[3] = {0.0, 0.0, 0.0}, xn[3] = {0.0, 0.0, 0.0}, n = 0.0;
-  const bool flag = b < A.nb && ode_lane(geo, A, b, x0, xn, n);
-  if (!geo.use_lists()) return;
-  const int lane = threadIdx.x;
-  uint64_t todo = __ballot(flag);
-  if (__popcll(todo) > kWaveFlagMaxBubbles) {
-    Axis win[3];
-    if (flag) {
-      const ColumnView<float> col = geo.template view<float>(b);
-      if (force_windows(col.G, x0, n, win)) mark_tiles<float>(col, A, win, xn, n, 0, 1);
-    }
-    return;
-  }
-  while (todo) {
-    const int l = __ffsll((unsigned long long)todo) - 1;
-    todo &= todo - 1;
-    double y0[3], yn[3];
-    for (int a = 0; a < 3; ++a) {
-      y0[a] = __shfl(x0[a], l, 64);
-      yn[a] = __shfl(xn[a], l, 64);
-    }
-    const double m = __shfl(n, l, 64);
-    const ColumnView<float> col = geo.template view<float>((int)(blockIdx.x * 64) + l);
-    Axis win[3];
-    if (force_windows(col.G, y0, m, win)) mark_tiles<float>(col, A, win, yn, m, lane, 64);
-  }
+  const int lane = threadIdx.x, q = lane & 3;
+  const int b = blockIdx.x * kOdeBubbles + (lane >> 2);
+  if (b >= A.nb) return;  // whole quads
+  OdeOut3 o;
+  const bool flag = ode_load_update(geo, A, b, q, o);
+  if (!geo.use_lists() || !flag) return;
+  const double x0[3] = {quad<kQuad0>(o.x0), quad<kQuad1>(o.x0), quad<kQuad2>(o.x0)};
+  const double xn[3] = {quad<kQuad0>(o.xn), quad<kQuad1>(o.xn), quad<kQuad2>(o.xn)};
+  const ColumnView<float> col = geo.template view<float>(b);
+  Axis win[3];
+  if (windows(col.G, x0, o.n, win)) mark_tiles<float>(col, A, win, xn, o.n, q, 4);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -997,8 +1097,7 @@ __global__ __launch_bounds__(64) void k_ode(Geo geo, BubbleArgs A) {
 // Backward coupling by atomic adds: F(j) += psi W_j over the force window (eq. (21)).
 template <typename T>
 __device__ void spread_atomic(const Geom& G, T* __restrict__ F, const Axis win[3],
-                              double (*s_w)[kSpan], const double* work, int tid) {
-  const double psi0 = work[W_PSI], psi1 = work[W_PSI + 1], psi2 = work[W_PSI + 2];
+                              double (*s_w)[kSpan], const double psi[3], int tid) {
   const int Kx = win[0].chi - win[0].clo + 1;
   const int Ky = win[1].chi - win[1].clo + 1;
   const int Kz = win[2].chi - win[2].clo + 1;
@@ -1014,9 +1113,9 @@ __device__ void spread_atomic(const Geom& G, T* __restrict__ F, const Axis win[3
     const int y = py ? wrapi(vy, G.ny) : vy;
     const int z = pz ? wrapi(vz, G.nz) : vz;
     const uint32_t c = ((uint32_t)z * G.ny + y) * G.nx + x;
-    atomicAdd(&F[c], (T)(psi0 * W));
-    atomicAdd(&F[G.N + c], (T)(psi1 * W));
-    atomicAdd(&F[2 * (size_t)G.N + c], (T)(psi2 * W));
+    atomicAdd(&F[c], (T)(psi[0] * W));
+    atomicAdd(&F[G.N + c], (T)(psi[1] * W));
+    atomicAdd(&F[2 * (size_t)G.N + c], (T)(psi[2] * W));
   }
 }
 
@@ -1024,7 +1123,7 @@ __device__ void spread_atomic(const Geom& G, T* __restrict__ F, const Axis win[3
 template <typename T, typename Geo>
 __global__ __launch_bounds__(kBlock) void k_spread(Geo geo, BubbleArgs A) {
   __shared__ double s_w[3][kSpan];
-  __shared__ double s_dw[3][kSpan];
+  __shared__ int s_bad[3];
   advance_traj_row(A);
   const int b = bubble_of_block(A.nb);
   const int tid = threadIdx.x;
@@ -1034,10 +1133,11 @@ __global__ __launch_bounds__(kBlock) void k_spread(Geo geo, BubbleArgs A) {
   const double x0[3] = {work[W_X0], work[W_X0 + 1], work[W_X0 + 2]};
   const double n = A.P.kernel_factor * A.S.d[b];
   Axis win[3];
-  // validated by k_interp
-  if (!build_weights(col.G, x0, n, tid, s_w, s_dw, win, A.P.coupling & LBM_COUPLING_POINT_KERNEL))
-    return;
-  spread_atomic<T>(col.G, col.F, win, s_w, work, tid);
+  if (!windows(col.G, x0, n, win)) return;  // validated by k_interp
+  build_weights(col.G, x0, n, tid, s_w, nullptr, win, A.P.coupling & LBM_COUPLING_POINT_KERNEL, s_bad);
+  __syncthreads();
+  const double psi[3] = {work[W_PSI], work[W_PSI + 1], work[W_PSI + 2]};
+  spread_atomic<T>(col.G, col.F, win, s_w, psi, tid);
   const double xn[3] = {A.S.x[b], A.S.y[b], A.S.z[b]};
   mark_tiles<T>(col, A, win, xn, n, tid, kBlock);
 }
@@ -1129,7 +1229,7 @@ __device__ __forceinline__ GatherLane gather_lane(const Geom& G, const BubbleArg
   const double x0[3] = {work[W_X0], work[W_X0 + 1], work[W_X0 + 2]};
   s.psi = work[W_PSI + i % 3];
   Axis win[3];
-  force_windows(G, x0, A.P.kernel_factor * A.S.d[b], win);  // valid: the bubble was listed
+  windows(G, x0, A.P.kernel_factor * A.S.d[b], win);  // valid: the bubble was listed
   s.wx = axis_weight_at(win[0], work + W_WGT, org[0] + i, G.nx, per[0]);
   s.wy = axis_weight_at(win[1], work + W_WGT + kSpan, org[1] + i, G.ny, per[1]);
   s.wz = axis_weight_at(win[2], work + W_WGT + 2 * kSpan, org[2] + i, G.nz, per[2]);
@@ -1209,7 +1309,7 @@ __device__ void gather_tiles(const Geo& geo, const BubbleArgs& A, uint32_t first
           if (work[W_VALID] != 0.0) {
             const double x0[3] = {work[W_X0], work[W_X0 + 1], work[W_X0 + 2]};
             Axis win[3];
-            if (force_windows(G, x0, A.P.kernel_factor * A.S.d[b], win)) {
+            if (windows(G, x0, A.P.kernel_factor * A.S.d[b], win)) {
               TileRanges tr[3];
               force_tiles(G, win, tr);
               cov = in_tile_ranges(tr[0], (int)tx) && in_tile_ranges(tr[1], (int)ty) &&
@@ -1270,11 +1370,12 @@ __global__ __launch_bounds__(64) void k_mark(Geo geo, BubbleArgs A, uint32_t* __
   }
   for (int rz = 0; rz < tr[2].n; ++rz)
     for (int ry = 0; ry < tr[1].n; ++ry) {
-      const int ny_ = tr[1].hi[ry] - tr[1].lo[ry] + 1;
-      const int nz_ = tr[2].hi[rz] - tr[2].lo[rz] + 1;
+      const int y0 = ry ? tr[1].lo[1] : tr[1].lo[0], y1 = ry ? tr[1].hi[1] : tr[1].hi[0];
+      const int z0 = rz ? tr[2].lo[1] : tr[2].lo[0], z1 = rz ? tr[2].hi[1] : tr[2].hi[0];
+      const int ny_ = y1 - y0 + 1, nz_ = z1 - z0 + 1;
       for (int k = threadIdx.x; k < ny_ * nz_; k += 64) {
-        const int ty = tr[1].lo[ry] + k % ny_;
-        const int tz = tr[2].lo[rz] + k / ny_;
+        const int ty = y0 + k % ny_;
+        const int tz = z0 + k / ny_;
         const uint32_t u = (uint32_t)tz * G.tny + ty;
         if (atomicExch(&region[u], 1u) == 0u) {
           const uint32_t i = atomicAdd(count, 1u);
@@ -1321,7 +1422,7 @@ hipError_t launch_bubble_kernels(const Geo& geo, const BubbleArgs& A, hipStream_
   if (e != hipSuccess) return e;
   const bool fused = !exact && nb <= fuse_max_bubbles<Geo>();
   if (!fused) {
-    hipLaunchKernelGGL((k_ode<Geo>), dim3(div_up(nb, 64)), dim3(64), 0, stream, geo, A);
+    hipLaunchKernelGGL((k_ode<Geo>), dim3(div_up(nb, kOdeBubbles)), dim3(64), 0, stream, geo, A);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1340,6 +1441,7 @@ hipError_t launch_bubble_kernels(const Geo& geo, const BubbleArgs& A, hipStream_
                          geo, A);
       return hipGetLastError();
     }
+    if (fused) return hipSuccess;  // k_interp spread the one bubble's force itself
     hipLaunchKernelGGL((k_spread<T, Geo>), dim3(nb), dim3(kBlock), 0, stream, geo, A);
     return hipGetLastError();
   } else {
