@@ -8,8 +8,8 @@
 //             liquid step must force, or must write the velocity in;
 //   k_spread  (one bubble, exact-time variant: one workgroup) the backward coupling (eq. (21)) of the
 //             reaction into the force field with the same weights (atomic adds) and the tile flags, or
-//   k_spread_gather (several bubbles: one wavefront per tile) the same sums per cell in bubble
-//             order from the lists, so that the force field is bit-reproducible.
+//   k_spread_gather (several bubbles: one wavefront per tile, or k_spread_gather_wide: one
+//             workgroup per tile of a small lattice) the same sums per cell in bubble order from the lists, so that the force field is bit-reproducible.
 // Up to 256 bubbles on one lattice and 512 over many columns (not in the exact-time variant)
 // k_interp's workgroup also runs k_ode's update of its bubble and flags the bubble's tiles, and k_ode is
 // not launched; a lattice's only bubble is spread there as well, so its bubble half is one launch.
@@ -1346,6 +1346,117 @@ __global__ __launch_bounds__(kBlock) void k_spread_gather(Geo geo, BubbleArgs A)
   gather_tiles<T, Geo>(geo, A, blockIdx.x * kBlockWaves + threadIdx.x / 64, gridDim.x * kBlockWaves);
 }
 
+// The same sums with a workgroup per tile, for lattices of few tiles (kGatherWideTiles): a wavefront per
+// tile leaves most of the chip idle there, and with crowded tiles its chain of staged chunks, two
+// round trips to memory for 8 bubbles, is the kernel (30 x 30 x 90 with 384
+// bubbles, 192 tiles: 67 us, 26 us this way).
+// Here 32 bubbles are staged at a time through LDS, and each of the four wavefronts sums two of the
+// tile's eight layers along z. The terms of a cell and their order are the same.
+constexpr int kWideChunk = kBlock / (int)kTile;  // bubbles staged at a time
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_spread_gather_wide(OneColumn geo, BubbleArgs A) {
+  static_assert(kTile == 8 && kBlockWaves == 4, "two layers of the tile per wavefront");
+  __shared__ double s_wt[3][kWideChunk][kTile], s_psi[kWideChunk][3];
+  __shared__ uint32_t s_ids[kBlock];
+  __shared__ uint32_t s_n[kBlockWaves];
+  advance_traj_row(A);
+  const GatherJob<T> J = gather_job<T>(geo, A, blockIdx.x);
+  const Geom& G = J.G;
+  const uint32_t t = J.t, cnt = J.tcount[t];
+  if (cnt == 0u) return;  // uniform over the workgroup
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t tx = t % (uint32_t)G.tnx, rr = t / (uint32_t)G.tnx;
+  const uint32_t ty = rr % (uint32_t)G.tny, tz = rr / (uint32_t)G.tny;
+  const int org[3] = {(int)(tx * kTile), (int)(ty * kTile), (int)(tz * kTile)};
+  const bool per[3] = {G.bc[0] == BC_PER, G.bc[2] == BC_PER, G.bc[4] == BC_PER};
+  const int lx = lane % (int)kTile, ly = lane / (int)kTile;
+  double acc[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+  // adds the terms of the n bubbles in s_ids, in that order
+  auto add = [&](uint32_t n) {
+    for (uint32_t k0 = 0; k0 < n; k0 += kWideChunk) {
+      const int m = (int)min(n - k0, (uint32_t)kWideChunk);
+      const int k = tid / (int)kTile, i = tid % (int)kTile;
+      const GatherLane st = gather_lane(G, A, s_ids[min(k0 + k, n - 1u)], k < m, i, org, per);
+      s_wt[0][k][i] = st.wx;
+      s_wt[1][k][i] = st.wy;
+      s_wt[2][k][i] = st.wz;
+      if (i < 3) s_psi[k][i] = st.psi;
+      __syncthreads();
+      for (int j = 0; j < m; ++j) {
+        const double wx = s_wt[0][j][lx], wy = s_wt[1][j][ly];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const double wz = s_wt[2][j][2 * wave + c];
+          const double W = wx * wy * wz;
+          for (int q = 0; q < 3; ++q) acc[c][q] += s_psi[j][q] * W;
+        }
+      }
+      __syncthreads();
+    }
+  };
+  if (cnt <= kTileCap) {
+    if (wave == 0) {  // the list sorted by bubble index
+      const uint32_t v = (uint32_t)lane < cnt ? J.tlist[(size_t)t * kTileCap + lane] : 0xffffffffu;
+      uint32_t r = 0;
+      for (uint32_t i = 0; i < cnt; ++i) {
+        const uint32_t vi = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)i);
+        r += (vi < v || (vi == v && i < (uint32_t)lane)) ? 1u : 0u;
+      }
+      if ((uint32_t)lane < cnt) s_ids[r] = v;
+    }
+    __syncthreads();
+    add(cnt);
+  } else {
+    // the list overflowed: the lattice's bubbles whose force window holds this tile, in index order
+    for (int base = J.b0; base < J.b1; base += kBlock) {
+      const int b = base + tid;
+      bool cov = false;
+      if (b < J.b1) {
+        const double* work = A.S.work + (size_t)b * kWork;
+        if (work[W_VALID] != 0.0) {
+          const double x0[3] = {work[W_X0], work[W_X0 + 1], work[W_X0 + 2]};
+          Axis win[3];
+          if (windows(G, x0, A.P.kernel_factor * A.S.d[b], win)) {
+            TileRanges tr[3];
+            force_tiles(G, win, tr);
+            cov = in_tile_ranges(tr[0], (int)tx) && in_tile_ranges(tr[1], (int)ty) &&
+                  in_tile_ranges(tr[2], (int)tz);
+          }
+        }
+      }
+      const uint64_t mask = __ballot(cov);
+      if (lane == 0) s_n[wave] = (uint32_t)__popcll(mask);
+      __syncthreads();
+      uint32_t at = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull)), n = 0;
+      for (int w = 0; w < kBlockWaves; ++w) {
+        if (w < wave) at += s_n[w];
+        n += s_n[w];
+      }
+      if (cov) s_ids[at] = (uint32_t)b;
+      __syncthreads();
+      add(n);
+      __syncthreads();  // s_n and s_ids are free for the next pass (also when n is zero)
+    }
+  }
+  const int x = org[0] + lx, y = org[1] + ly;
+  if (x < G.nx && y < G.ny) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int z = org[2] + 2 * wave + c;
+      if (z < G.nz) {
+        const uint32_t at = ((uint32_t)z * G.ny + y) * G.nx + x;
+        J.F[at] = (T)acc[c][0];
+        J.F[G.N + at] = (T)acc[c][1];
+        J.F[2 * (size_t)G.N + at] = (T)acc[c][2];
+      }
+    }
+  }
+  // every thread has read the count (before the barriers above)
+  if (tid == 0) J.tcount[t] = 0u;
+}
+
 // Region of an overlapped step (one wavefront per bubble): the tile rows (y, z) of the bubble's
 // stencil window at its current position widened by the curl ring and by kRegionMargin cells.
 // They hold every tile k_spread flags in this step (the force window at this position, the
@@ -1384,6 +1495,10 @@ __global__ __launch_bounds__(64) void k_mark(Geo geo, BubbleArgs A, uint32_t* __
       }
     }
 }
+
+// Tiles up to which a lattice's gather takes a workgroup per tile: four of them per compute unit. (On
+// 256 x 256 x 768 with 20 000 bubbles, 98 304 tiles, a workgroup per tile took 212 us against 79 us.)
+constexpr uint32_t kGatherWideTiles = 1024;
 
 // Workgroups of the many-column gather (their wavefronts take the noted tiles in turn).
 constexpr uint32_t kGatherMaxBlocks = 2048;
@@ -1436,6 +1551,10 @@ hipError_t launch_bubble_kernels(const Geo& geo, const BubbleArgs& A, hipStream_
     }
     if (geo.lists) {  // several bubbles: the lists k_interp filled, summed per tile
       const uint32_t ntiles = (uint32_t)geo.G.tnx * geo.G.tny * div_up(geo.G.nz, kTile);
+      if (ntiles <= kGatherWideTiles) {
+        hipLaunchKernelGGL((k_spread_gather_wide<T>), dim3(ntiles), dim3(kBlock), 0, stream, geo, A);
+        return hipGetLastError();
+      }
       hipLaunchKernelGGL((k_spread_gather<T, OneColumn>), dim3(div_up(ntiles, kBlockWaves)),
                          dim3(kBlock), 0, stream,
                          geo, A);
