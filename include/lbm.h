@@ -181,7 +181,10 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x);
  * widened by the curl ring and two cells), runs the bubble kernels on a library-owned side stream
  * while the liquid update of every other tile (the bulk) runs on the caller's stream, and makes the
  * caller's stream wait for the bubble kernels; lbm_step() then updates the region. Within
- * lbm_run() each overlapped step also marks the region of the next one on the side stream. Work
+ * lbm_run() each overlapped step also marks the region of the next one on the side stream; where
+ * lbm_run() takes steps in pairs, an overlapped pair of up to 256 bubbles runs both bubble halves and the
+ * first step of the rows and planes they reach beside the two steps of everything else, and with
+ * more bubbles the parts of a pair run one after the other. Work
  * enqueued on the caller's stream after bubbles_step() sees the bubble results. Results are identical to the
  * serial step bit for bit. A bubble that moves more than two cells in one step would leave the region; that
  * is reported by lbm_check() / moments() with sums as LBM_EUNSUPPORTED. Not allowed while a
@@ -196,8 +199,9 @@ lbm_status lbm_get_overlap(lbm_ctx* ctx, int32_t* enabled, int32_t* available);
  * whole liquid step). One-shot: the events are forgotten after that launch. The caller owns the events. */
 lbm_status lbm_time_next_step(lbm_ctx* ctx, void* start, void* end);
 
-/* Cells in the region of the last overlapped step (0 if none since the last serial step); the bulk
- * launch of that step updated the other N - cells. Synchronises the stream. */
+/* Cells in the region of the last overlapped step or pair of steps (0 if none since the last serial
+ * step); the bulk launch updated the other N - cells (a pair's took them two steps). Synchronises the
+ * stream. */
 lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells);
 
 /* nsteps liquid steps (Sec. 2.2, eq. (13)-(16) with the face conditions of Sec. 3.3): first
@@ -265,11 +269,10 @@ lbm_status lbm_check(lbm_ctx* ctx);
 /* nsteps method steps (bubbles_step then lbm_step(ctx, 1), Algorithm 1) with the launches of
  * graph_steps consecutive steps captured once into a HIP graph and replayed; the graph is kept
  * while params, soa and nb stay the same. graph_steps must be even (the step alternates two
- * population buffers), 0 runs every step eagerly. Graph capture needs a non-NULL stream. Where the
- * step is not overlapped, lattices of 2^19 cells or more with walls on every face (no flag but
- * LBM_FLAG_PLAIN_SOA, one cell per thread, not the exact-time coupling) take their steps in pairs:
- * the planes the bubbles reach one step at a time, the others both steps in one launch; same results
- * bit for bit. */
+ * population buffers), 0 runs every step eagerly. Graph capture needs a non-NULL stream. Lattices of
+ * 2^19 cells or more with walls on every face (no flag but LBM_FLAG_PLAIN_SOA, one cell per thread,
+ * not the exact-time coupling) take their steps in pairs: the rows and planes the bubbles reach one
+ * step at a time, the others both steps in one launch; same results bit for bit. */
 lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* params, const bubble_soa* soa, int32_t nb,
                    int32_t nsteps, int32_t graph_steps);
 

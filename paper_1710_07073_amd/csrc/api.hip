@@ -72,7 +72,7 @@ Layout layout_of(const lbm_desc* d) {
   L.status = align_up(L.result + 4 * sizeof(double));
   L.traj_row = align_up(L.status + sizeof(int32_t));
   L.slab = align_up(L.traj_row + sizeof(uint32_t));
-  L.init = align_up(L.slab + 8 * sizeof(uint32_t));
+  L.init = align_up(L.slab + 2 * lbm::kSlabWords * sizeof(uint32_t));
   // the middle buffer of pairs of method steps, for the lattices that can take them
   L.mid = L.init;
   const size_t elem = d->precision == LBM_FP32_SHIFTED ? 4 : 8;
@@ -177,8 +177,9 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   c->slab = reinterpret_cast<uint32_t*>(s + L.slab);
   c->mid = pairs_ok(desc) ? s + L.mid : nullptr;
   if (G.N < lbm::kStep2MinCells || !lbm::bb_fast_ok(G, c->elem) ||
-      !lbm::choose_tiles2(G, c->elem, &c->tiles2))
-    c->tiles2 = lbm::Tiles2{};
+      !lbm::choose_tiles2(G, c->elem, lbm::kCus, &c->tiles2) ||
+      !lbm::choose_tiles2(G, c->elem, lbm::kCusBeside, &c->tiles2_beside))
+    c->tiles2 = c->tiles2_beside = lbm::Tiles2{};
   c->nred = L.nred;
   c->bins_clean = false;
   c->stream = static_cast<hipStream_t>(stream);
@@ -282,6 +283,22 @@ lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells) {
   *cells = 0;
   if (ctx->hs.pending) return LBM_EINVAL;
   if (!ctx->hs.last_overlapped) return LBM_OK;  // a serial step came after it
+  if (ctx->hs.last_pair) {  // the box of the last pair
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (hipMemcpyAsync(w, ctx->slab + lbm::kSlabWords * (ctx->hs.spar ^ 1), sizeof(w), hipMemcpyDeviceToHost,
+                       ctx->stream) != hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess)
+      return LBM_EDEVICE;
+    if (w[1] == 0) return LBM_OK;
+    // as slab_box() has it: whole force tiles, rows in multiples of the pass's tiles
+    const int64_t t = lbm::kTile, oy = ctx->tiles2_beside.oy;
+    const int64_t za = std::max<int64_t>(0, (int32_t)(lbm::kSlabBase - w[0])) / t * t;
+    const int64_t zb = std::min<int64_t>(ctx->geom.nz, ((int64_t)w[1] + t - 1) / t * t);
+    const int64_t ya = std::max<int64_t>(0, (int32_t)(lbm::kSlabBase - w[2])) / t * t / oy * oy;
+    const int64_t yb = std::min<int64_t>(ctx->geom.ny, (((int64_t)w[3] + t - 1) / t * t + oy - 1) / oy * oy);
+    *cells = (zb - za) * (yb - ya) * ctx->geom.nx;
+    return LBM_OK;
+  }
   // the list of the last overlapped step stays until the next step of the same parity
   const int r = ctx->hs.rpar ^ 1;
   uint32_t count = 0;
@@ -365,11 +382,8 @@ lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
 }
 
 namespace {
-// in_run: a step of lbm_run, where no caller code runs between steps, so that an overlapped step
-// may mark the region of the next one while its bulk runs (from the bubble state it leaves).
-// slab, slab_clear: a half of a pair of steps (launch_bubbles).
-lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb,
-                       bool in_run, uint32_t* slab = nullptr, uint32_t* slab_clear = nullptr) {
+// Argument checks of a bubble half.
+lbm_status check_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb) {
   if (!ctx || !p || !s || nb < 0) return LBM_EINVAL;
   if (ctx->desc.flags & LBM_FLAG_STATIC_FORCE) return LBM_EINVAL;
   if (p->n_sub < 1 || !lbm::coupling_ok(p->coupling)) return LBM_EINVAL;
@@ -383,26 +397,39 @@ lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s
     if (any_psi && !all_psi) return LBM_EINVAL;
   }
   if (ctx->hs.pending) return LBM_EINVAL;  // the previous bubble half still awaits its lbm_step
+  return LBM_OK;
+}
+
+// in_run: a step of lbm_run, where no caller code runs between steps, so that an overlapped step
+// may mark the region of the next one while its bulk runs (from the bubble state it leaves).
+// slab, slab_clear: a half of a pair of steps (launch_bubbles).
+lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb,
+                       bool in_run, uint32_t* slab = nullptr, uint32_t* slab_clear = nullptr) {
+  const lbm_status st = check_half(ctx, p, s, nb);
+  if (st != LBM_OK) return st;
   // the caller may have moved bubbles since a previous run marked ahead: mark afresh
   if (!in_run) ctx->hs.marked = false;
-  const bool overlap = ctx->overlap && nb > 0 && lbm::can_overlap(ctx);
+  const bool overlap = ctx->overlap && nb > 0 && lbm::can_overlap(ctx) && !slab;
   return from_hip(lbm::launch_bubbles(ctx, p, s, nb, overlap, in_run, slab, slab_clear));
 }
 
-// lbm_run() takes the method steps of this lattice in pairs (serial steps; the exact-time coupling
-// reads the whole state between the two).
-bool can_pair(const lbm_ctx* ctx, const bubble_params* p, int32_t nb) {
-  return ctx->mid && lbm::can_step2(ctx) && !(p->coupling & LBM_COUPLING_EXACT_TIME) &&
-         !(ctx->overlap && nb > 0 && lbm::can_overlap(ctx));
+// lbm_run() takes the method steps of this lattice in pairs (the exact-time coupling reads the whole
+// state between the two).
+bool can_pair(const lbm_ctx* ctx, const bubble_params* p) {
+  return ctx->mid && lbm::can_step2(ctx) && !(p->coupling & LBM_COUPLING_EXACT_TIME);
 }
 
 // Two method steps (see step2.hip).
 lbm_status step_pair(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb) {
-  uint32_t* const words = ctx->slab + 4 * ctx->hs.spar;
-  lbm_status st = bubble_half(ctx, p, s, nb, true, words, ctx->slab + 4 * (ctx->hs.spar ^ 1));
+  uint32_t* const words = ctx->slab + lbm::kSlabWords * ctx->hs.spar;
+  if (ctx->overlap && nb > 0 && nb <= lbm::kPairBesideMaxBubbles && lbm::can_overlap(ctx)) {
+    const lbm_status ok = check_half(ctx, p, s, nb);
+    return ok != LBM_OK ? ok : from_hip(lbm::launch_pair_overlapped(ctx, p, s, nb));
+  }
+  lbm_status st = bubble_half(ctx, p, s, nb, true, words, ctx->slab + lbm::kSlabWords * (ctx->hs.spar ^ 1));
   if (st != LBM_OK) return st;
   if (nb > 0 && lbm::launch_slab(ctx, words) != hipSuccess) return LBM_EDEVICE;
-  st = bubble_half(ctx, p, s, nb, true, words + 2, nullptr);
+  st = bubble_half(ctx, p, s, nb, true, words + 4, nullptr);
   if (st != LBM_OK) return st;
   if (lbm::launch_step2(ctx, words) != hipSuccess) return LBM_EDEVICE;
   if (nb > 0) ctx->hs.spar ^= 1;
@@ -505,10 +532,10 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
   if (graph_steps < 0 || graph_steps % 2 || ctx->hs.pending) return LBM_EINVAL;
   // an armed step record belongs to one call of bubbles_step (a graph would replay it)
   if (ctx->arm_record) return LBM_EINVAL;
-  ctx->hs.marked = false;  // the bubble state may have changed since the last call
+  ctx->hs.marked = ctx->hs.slab_marked = false;  // the bubble state may have changed since the last call
   // the last `single` of the n steps are not paired
   auto steps = [&](int32_t n, int32_t single = 0) -> lbm_status {
-    const bool pairs = can_pair(ctx, p, nb);
+    const bool pairs = can_pair(ctx, p);
     for (int32_t i = 0; i < n;) {
       const bool two = pairs && n - single - i >= 2;
       lbm_status st;
@@ -537,6 +564,7 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     const uint32_t mode = (pre.flag_clean[0] ? 1u : 0u) | (pre.flag_clean[1] ? 2u : 0u) |
                           ((uint32_t)pre.rpar << 4) | (ctx->overlap ? 32u : 0u) |
                           (pre.marked ? 64u : 0u) | ((uint32_t)pre.spar << 7) |
+                          (pre.slab_marked ? 4u : 0u) |
                           ((uint32_t)ctx->step_vec << 8) | (ctx->step_bx << 12) |
                           ((uint32_t)ctx->step_wgs << 24);
     const lbm::GraphKey key = lbm::GraphKey::of(p, s, nb, pre.cur, pre.flag_cur, graph_steps, mode);

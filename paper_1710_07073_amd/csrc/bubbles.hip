@@ -368,6 +368,13 @@ __device__ void force_tiles(const Geom& G, const Axis win[3], TileRanges tr[3]) 
     tr[a] = tile_ranges(win[a].clo, win[a].chi, ext[a], (int)kTile, G.bc[2 * a] == BC_PER);
 }
 
+// Notes cells [lo, hi] along axis a (1 or 2) in the words of a box.
+__device__ __forceinline__ void slab_note(uint32_t* slab, int a, int lo, int hi) {
+  uint32_t* w = slab + (a == 2 ? 0 : 2);
+  atomicMax(&w[0], kSlabBase - (uint32_t)lo);
+  atomicMax(&w[1], (uint32_t)max(hi + 1, 1));
+}
+
 // Flags the tiles the liquid step must force (the force window now) or write the velocity in (the
 // velocity window, with the curl ring, that the next interpolation reads at the new position).
 template <typename T>
@@ -391,12 +398,19 @@ __device__ void mark_tiles(const ColumnView<T>& col, const BubbleArgs& A, const 
     }
     if (a > 0)
       inside = inside && lo >= win[a].lo - 1 - kRegionMargin && hi <= win[a].hi + 1 + kRegionMargin;
-    if (a == 2 && col.slab && tid == 0) {
-      // the planes this half reaches: the force window with one to spare on either side (the
-      // two-step pass computes the plane beside the slab without force), and the velocity window
-      atomicMax(&col.slab[0], kSlabBase - (uint32_t)min(win[a].clo - 1, lo));
-      atomicMax(&col.slab[1], (uint32_t)(max(win[a].chi + 1, hi) + 1));
+    if (a > 0 && col.slab && tid == 0) {
+      // the rows and planes this half reaches: the force window with one to spare on either side (the
+      // two-step pass computes what lies beside the box without force), and the velocity window
+      slab_note(col.slab, a, min(win[a].clo - 1, lo), max(win[a].chi + 1, hi));
     }
+    if (a > 0 && col.slab_in && tid == 0) {
+      // an overlapped pair: the launch beside this one updates everything outside the box
+      const Box box = slab_box(col.slab_in, G, true, 1);
+      const int b0 = a == 1 ? box.ya : box.za, b1 = a == 1 ? box.yb : box.zb;
+      if (max(lo, 0) < b0 || min(hi, ext[a] - 1) >= b1) atomicOr(A.status, (int32_t)STATUS_REGION_MISS);
+    }
+    if (a > 0 && col.slab_out && tid == 0 && axis_window(xn[a], n, ext[a], per, nw))
+      slab_note(col.slab_out, a, nw.lo - 1 - 2 * kRegionMargin, nw.hi + 1 + 2 * kRegionMargin);
     tr[a] = tile_ranges(lo, hi, ext[a], (int)kTile, per);
   }
   const uint32_t* __restrict__ region = inside ? nullptr : col.region;
@@ -523,7 +537,7 @@ __device__ __forceinline__ void clear_for_step(const Geo& geo) {
     // starts empty
     if (geo.clear_count) *geo.clear_count = 0u;
     if (geo.slab_clear)
-      for (int i = 0; i < 4; ++i) geo.slab_clear[i] = 0u;
+      for (int i = 0; i < kSlabWords; ++i) geo.slab_clear[i] = 0u;
   }
   geo.clear_other_jobs();  // many columns: the next step's tile jobs start empty
 }
@@ -816,13 +830,13 @@ __global__ __launch_bounds__(kBlock, FUSE ? 2 : 1) void k_interp(Geo geo, Bubble
 }
 
 // ---------------------------------------------------------------------------------------------
-// Bubble dynamics, one lane per bubble.
+// Bubble dynamics, a quad of lanes per bubble.
 // ---------------------------------------------------------------------------------------------
 
-// The transcendental functions of the closures for one lane, whose latency is all they cost: ordinary
-// arguments only (positive and normal, or handled by the caller), short chains (polynomials in pairs
-// of terms), no branches. With the library's log, exp, tanh, division and square root a sub-step took
-// 2.2 us of the lane's time, most of it these.
+// The transcendental functions of the closures, whose latency is all they cost: ordinary arguments only
+// (positive and normal, or handled by the caller), short chains (polynomials in pairs of terms), no
+// branches. With the library's log, exp, tanh, division and square root, in one lane, a sub-step took
+// 1.2 us, most of it these; it takes 0.5 us.
 
 // a / b and sqrt(a): the hardware approximation, two Newton steps and a residual correction.
 __device__ __forceinline__ double quick_div(double a, double b) {
@@ -1496,6 +1510,20 @@ __global__ __launch_bounds__(64) void k_mark(Geo geo, BubbleArgs A, uint32_t* __
     }
 }
 
+// The box of an overlapped pair from the bubbles at its start (a lane per bubble): their windows widened
+// by the curl ring and kRegionMargin cells of movement per step.
+__global__ __launch_bounds__(256) void k_mark_slab(OneColumn geo, BubbleArgs A, uint32_t* slab) {
+  const int b = blockIdx.x * 256 + threadIdx.x;
+  if (b >= A.nb || A.S.state[b] == 0) return;
+  const double n = A.P.kernel_factor * A.S.d[b];
+  Axis wy, wz;
+  if (!axis_window(A.S.y[b], n, geo.G.ny, geo.G.bc[2] == BC_PER, wy) ||
+      !axis_window(A.S.z[b], n, geo.G.nz, geo.G.bc[4] == BC_PER, wz))
+    return;  // reported by k_interp
+  slab_note(slab, 1, wy.lo - 1 - 2 * kRegionMargin, wy.hi + 1 + 2 * kRegionMargin);
+  slab_note(slab, 2, wz.lo - 1 - 2 * kRegionMargin, wz.hi + 1 + 2 * kRegionMargin);
+}
+
 // Tiles up to which a lattice's gather takes a workgroup per tile: four of them per compute unit. (On
 // 256 x 256 x 768 with 20 000 bubbles, 98 304 tiles, a workgroup per tile took 212 us against 79 us.)
 constexpr uint32_t kGatherWideTiles = 1024;
@@ -1681,9 +1709,10 @@ hipError_t launch_persistent_faces(const ManyColumns& geo, const BubbleArgs& A,
 
 }  // namespace
 
-hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb,
-                          bool overlap, bool mark_ahead, uint32_t* slab, uint32_t* slab_clear) {
-  BubbleArgs A;
+// The arguments of one bubble half of a lattice, whose mask is the one the last liquid step cleared
+// (cleared here, on the caller's stream, if none ran).
+static hipError_t begin_half(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb,
+                             OneColumn& geo, BubbleArgs& A) {
   A.P = *p;
   A.S = *s;
   A.nb = nb;
@@ -1693,7 +1722,6 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
   A.traj = c->traj;
   A.traj_rows = c->traj_rows;
   A.traj_row = c->traj_row;
-  // this step's mask: the one the last liquid step cleared (cleared here if no liquid step ran)
   const int m = c->hs.flag_cur ^ 1;
   if (!c->hs.flag_clean[m]) {
     const hipError_t e = launch_fill(c->tiles[m], c->ntiles, c->stream);
@@ -1701,11 +1729,6 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
   }
   c->hs.flag_clean[m] = false;
   c->hs.flag_cur = m;
-  if (nb == 0) return hipSuccess;
-  c->hs.forced = true;
-  OneColumn geo;
-  geo.slab = slab;
-  geo.slab_clear = slab_clear;
   geo.G = c->geom;
   geo.U = c->vel;
   geo.F = c->force;
@@ -1721,6 +1744,62 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
   geo.next_list = nullptr;
   geo.next_count = nullptr;
   geo.nrows = c->nrows;
+  geo.slab = nullptr;
+  geo.slab_clear = nullptr;
+  geo.slab_in = nullptr;
+  geo.slab_out = nullptr;
+  return hipSuccess;
+}
+
+static hipError_t bubble_kernels(const lbm_ctx* c, const OneColumn& geo, const BubbleArgs& A, hipStream_t s) {
+  return c->elem == 4 ? launch_bubble_kernels<float>(geo, A, s) : launch_bubble_kernels<double>(geo, A, s);
+}
+
+hipError_t launch_pair_overlapped(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb) {
+  // The slab is known before the pair begins: the bubble kernels and the slab's step n run on the side
+  // stream while the planes outside it take both steps on the caller's, which then waits and takes
+  // the slab's step n + 1. Each pair's second half marks the slab of the next one.
+  uint32_t* const words = c->slab + kSlabWords * c->hs.spar;
+  uint32_t* const next = c->slab + kSlabWords * (c->hs.spar ^ 1);
+  OneColumn geo;
+  BubbleArgs A;
+  hipError_t e = begin_half(c, p, s, nb, geo, A);
+  if (e != hipSuccess) return e;
+  if (!c->hs.slab_marked) {
+    hipLaunchKernelGGL(k_mark_slab, dim3(div_up((uint32_t)nb, 256u)), dim3(256), 0, c->stream, geo, A, words);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipEventRecord(c->ev_fork, c->stream);
+  if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->ev_fork, 0);
+  geo.slab_in = words;
+  geo.slab_clear = next;
+  if (e == hipSuccess) e = bubble_kernels(c, geo, A, c->side);
+  if (e == hipSuccess) e = launch_pair_first(c, words, c->side);
+  if (e == hipSuccess) e = begin_half(c, p, s, nb, geo, A);
+  geo.slab_in = words;
+  geo.slab_out = next;
+  if (e == hipSuccess) e = bubble_kernels(c, geo, A, c->side);
+  if (e == hipSuccess) e = hipEventRecord(c->ev_join, c->side);
+  if (e == hipSuccess) e = launch_pair_bulk(c, words);
+  if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, c->ev_join, 0);
+  if (e == hipSuccess) e = launch_pair_second(c, words);
+  if (e != hipSuccess) return e;
+  c->hs.slab_marked = true;
+  c->hs.marked = false;  // single steps mark their region afresh
+  c->hs.spar ^= 1;
+  return hipSuccess;
+}
+
+hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb,
+                          bool overlap, bool mark_ahead, uint32_t* slab, uint32_t* slab_clear) {
+  OneColumn geo;
+  BubbleArgs A;
+  const hipError_t begun = begin_half(c, p, s, nb, geo, A);
+  if (begun != hipSuccess || nb == 0) return begun;
+  c->hs.forced = true;
+  c->hs.slab_marked = false;
+  geo.slab = slab;
+  geo.slab_clear = slab_clear;
   if (overlap) {
     // Region of this step (unless the previous step of this run marked it), then fork: the
     // bubble kernels run on the side stream while the bulk of the liquid step runs on the
@@ -1745,8 +1824,7 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
       geo.next_count = c->region_count + (r ^ 1);
     }
     c->hs.marked = mark_ahead;
-    e = c->elem == 4 ? launch_bubble_kernels<float>(geo, A, c->side)
-                     : launch_bubble_kernels<double>(geo, A, c->side);
+    e = bubble_kernels(c, geo, A, c->side);
     if (e == hipSuccess) e = hipEventRecord(c->ev_join, c->side);
     if (e == hipSuccess) e = launch_bulk(c);
     if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, c->ev_join, 0);
@@ -1755,8 +1833,7 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
     c->pending_nb = nb;
     return hipSuccess;
   }
-  if (c->elem == 4) return launch_bubble_kernels<float>(geo, A, c->stream);
-  return launch_bubble_kernels<double>(geo, A, c->stream);
+  return bubble_kernels(c, geo, A, c->stream);
 }
 
 hipError_t launch_bubbles_batch(const ManyColumns& geo, size_t elem, const bubble_params* p,

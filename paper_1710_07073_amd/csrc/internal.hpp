@@ -26,6 +26,8 @@ struct HostState {
   bool pending;           // bubbles_step() enqueued the bulk; lbm_step() must update the region
   bool forced;            // a bubble half spread force the next liquid step has yet to use
   bool marked;            // the region of the next overlapped step is marked (within lbm_run)
+  bool slab_marked;       // the slab of the next overlapped pair is marked (within lbm_run)
+  bool last_pair;         // the last overlapped step was a pair
   int spar;               // parity of the next pair of method steps (its slab words)
   bool last_overlapped;   // the last liquid step was overlapped (its region list is current)
   int64_t steps;
@@ -42,8 +44,8 @@ struct lbm_ctx {
   void* force;
   void* vel;
   void* mid;  // middle buffer of a pair of method steps (step2.hip), or null
-  uint32_t* slab;  // slab words, 4 per pair parity
-  lbm::Tiles2 tiles2;
+  uint32_t* slab;  // slab words, kSlabWords per pair parity
+  lbm::Tiles2 tiles2, tiles2_beside;  // with the chip to itself, and beside the bubble kernels
   // Two tile masks, one byte per 8^3 tile (force present / velocity needed). bubbles_step()
   // writes mask[flag_cur ^ 1] and makes it current; each liquid step reads mask[flag_cur] and
   // clears the other one for the next bubble step.
@@ -106,6 +108,8 @@ struct ColumnView {
   double nu;
   const uint32_t* region;  // region flags of an overlapped step (tiles the spread may force), or null
   uint32_t* slab;          // slab words of a half of a pair of steps, or null
+  const uint32_t* slab_in; // overlapped pair: its slab, which must hold what this half reaches, or null
+  uint32_t* slab_out;      // overlapped pair: the next one's slab, marked ahead, or null
 };
 
 // A single lattice (lbm_ctx). tcount/tlist: the per-tile bubble lists of the deterministic
@@ -131,9 +135,11 @@ struct OneColumn {
   uint32_t nrows;
   uint32_t* slab;        // slab words this half of a pair of steps notes its planes in, or null
   uint32_t* slab_clear;  // the next pair's, cleared by k_interp (null: not here)
+  const uint32_t* slab_in;
+  uint32_t* slab_out;
   template <typename T>
   __device__ ColumnView<T> view(int) const {
-    return {G, static_cast<const T*>(U), static_cast<T*>(F), tiles, nu, region, slab};
+    return {G, static_cast<const T*>(U), static_cast<T*>(F), tiles, nu, region, slab, slab_in, slab_out};
   }
   // the deterministic spreading: per-tile lists of this lattice (every tile is gathered, so the
   // tiles entered need no note)
@@ -182,7 +188,8 @@ struct ManyColumns {
   template <typename T>
   __device__ ColumnView<T> view(int b) const {
     const ColumnDev& c = cols[bubble_col[b]];
-    return {c.G, static_cast<const T*>(c.U), static_cast<T*>(c.F), c.tiles[flag], c.nu, nullptr, nullptr};
+    return {c.G, static_cast<const T*>(c.U), static_cast<T*>(c.F), c.tiles[flag], c.nu, nullptr, nullptr, nullptr,
+            nullptr};
   }
   __device__ bool use_lists() const { return true; }
   // the bubble constants of bubble b: the shared ones with its column's g and sigma where set
@@ -244,11 +251,20 @@ struct PersistArgs {
 // curl ring: covers the bubble's displacement in one step.
 constexpr int kRegionMargin = 2;
 
+// Compute units of the chip, and those an overlapped pair's bulk launch takes: it holds a compute unit
+// with one workgroup from beginning to end, and the bubble update's registers do not fit beside it.
+constexpr uint32_t kCus = 256;
+constexpr uint32_t kCusBeside = 240;
+// Bubbles up to which an overlapped pair runs its bubble kernels beside the bulk launch, on the compute
+// units left to them. (20 000 on 256 x 256 x 768: 1406 us per step, 1363 us one after the other.)
+constexpr int kPairBesideMaxBubbles = 256;
+
 // Lattices from this size on overlap the bubble kernels with the liquid step by default.
 constexpr uint32_t kOverlapMinCells = 1u << 22;
 
-// Slab words (uint32, zero: empty): [0] max of kSlabBase - a and [1] max of b over the bubbles, the
-// slab [a, b) of a pair's first half; [2], [3] the same of its second half.
+// Slab: the box of rows and planes the bubbles reach in a pair of steps. Its words (uint32, zero: empty),
+// for either half of the pair: the maxima over the bubbles of kSlabBase - za, zb, kSlabBase - ya, yb.
+constexpr int kSlabWords = 8;
 constexpr uint32_t kSlabBase = 1u << 30;
 
 // Lattices from these sizes on are advanced two steps per launch, alone and with bubbles. Alone, the
@@ -275,7 +291,8 @@ bool can_overlap(const lbm_ctx* c);
 // Bulk part of the liquid step of an overlapped step (on the caller's stream).
 hipError_t launch_bulk(lbm_ctx* c);
 // step2.hip
-bool choose_tiles2(const Geom& G, size_t elem, Tiles2* best);
+// Tiles for a launch on so many compute units.
+bool choose_tiles2(const Geom& G, size_t elem, uint32_t cus, Tiles2* best);
 // The liquid can be advanced two steps per launch.
 bool can_step2(const lbm_ctx* c);
 // Two liquid steps in one launch. slab (null: no bubbles, no force but a static one): the slab
@@ -283,12 +300,20 @@ bool can_step2(const lbm_ctx* c);
 hipError_t launch_step2(lbm_ctx* c, const uint32_t* slab);
 // The first liquid step of a pair of method steps, of the planes the bubbles reach.
 hipError_t launch_slab(lbm_ctx* c, const uint32_t* slab);
+// The parts of an overlapped pair: both steps outside the slab; step n of the slab, on stream s; step
+// n + 1 of the slab, which ends the pair.
+hipError_t launch_pair_bulk(lbm_ctx* c, const uint32_t* slab);
+hipError_t launch_pair_first(lbm_ctx* c, const uint32_t* slab, hipStream_t s);
+hipError_t launch_pair_second(lbm_ctx* c, const uint32_t* slab);
 // bubbles.hip
 // mark_ahead (overlapped steps of lbm_run only): also mark the region of the next step, after the
 // bubble update, on the side stream. slab: a half of a pair of steps (serial), see OneColumn
 hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb,
                           bool overlap, bool mark_ahead, uint32_t* slab = nullptr,
                           uint32_t* slab_clear = nullptr);
+// An overlapped pair of method steps: marks its slab unless the previous pair did, and enqueues both bubble
+// halves and the slab's two steps beside (the first) and after (the second) the rest of the lattice.
+hipError_t launch_pair_overlapped(lbm_ctx* c, const bubble_params* p, const bubble_soa* s, int32_t nb);
 hipError_t launch_bubbles_batch(const ManyColumns& geo, size_t elem, const bubble_params* p,
                                 const bubble_soa* s, int32_t nb, int32_t* status,
                                 hipStream_t stream);

@@ -350,6 +350,7 @@ hipError_t launch_step(lbm_ctx* c) {
     c->hs.cur ^= 1;
     c->hs.flag_clean[c->hs.flag_cur ^ 1] = true;
     c->hs.last_overlapped = overlapped;
+    c->hs.last_pair = false;
     c->hs.forced = false;
     ++c->hs.steps;
   }

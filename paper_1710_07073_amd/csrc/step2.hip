@@ -1,12 +1,15 @@
 // Two liquid steps per launch (step2_cell.hpp) of a single lattice, alone or coupled to bubbles.
 //
 // With bubbles, a pair of method steps is
-//   bubble half n; k_slab: step n of the planes the bubbles reach, into the middle buffer;
-//   bubble half n + 1; k_step2: both steps of every other plane, and step n + 1 of those planes.
-// The planes the bubbles reach in the pair are the slab [a, b): every force window of step n with a
-// plane to spare on either side, and the velocity windows the second half reads (which hold its
-// force windows). The bubble update finds a and b on the device as it moves each bubble. Outside the
-// slab no cell holds force in either step, nor is its velocity read.
+//   bubble half n; k_slab: step n of the cells the bubbles reach, into the middle buffer;
+//   bubble half n + 1; k_step2: both steps of every other cell, and step n + 1 of those.
+// The cells the bubbles reach in the pair are a box, the slab, of rows and planes across all x: every
+// force window of step n with a cell to spare on either side, and the velocity windows the second half
+// reads (which hold its force windows). The bubble update finds it on the device as it moves each bubble.
+// Outside it no cell holds force in either step, nor is its velocity read.
+//
+// An overlapped pair knows its slab beforehand (windows widened by the cells a bubble may move, reported
+// if one moves further) and runs the bubble halves and k_slab beside the launch of everything else.
 #include <algorithm>
 #include <utility>
 
@@ -15,28 +18,15 @@
 namespace lbm {
 namespace {
 
-// Compute units of the chip: the workgroups of this pass that run at a time.
-constexpr uint32_t kStep2Cus = 256;
 
-// The slab [a, b) from its words; empty without bubbles.
-__device__ __forceinline__ void slab_range(const uint32_t* words, int nz, int& a, int& b) {
-  a = b = 0;
-  if (words && words[1] != 0u) {
-    a = max(0, (int)(kSlabBase - words[0]));
-    b = min(nz, (int)words[1]);
-  }
-}
-
-// One step of one cell by flat index, inside a loop over cells. The strides are made opaque in every
+// One step of one cell, inside a loop over cells. The strides are made opaque in every
 // iteration: hoisted out of the loop, the 38 offsets that follow from them fill the registers.
 template <typename T, bool FS>
 __device__ __forceinline__ void step_one(const gchar* src, gchar* dst, gchar* F, gchar* U,
                                          const gchar* tiles, const Geom& G0, T omega, int flags,
-                                         uint32_t cell, uint32_t fs) {
+                                         uint32_t x, uint32_t y, uint32_t z, uint32_t fs) {
   Geom G = G0;
   asm volatile("" : "+s"(G.qs), "+s"(G.zs), "+s"(G.nx));
-  const uint32_t z = cell / G.plane, rem = cell - z * G.plane;
-  const uint32_t y = rem / (uint32_t)G.nx, x = rem - y * (uint32_t)G.nx;
   const uint32_t tile = ((z >> 3) * G.tny + (y >> 3)) * G.tnx + (x >> 3);
   step_cell_bb<T, FS>(src, dst, F, U, tiles, tile, G, omega, flags, (int)x, (int)y, z, fs);
 }
@@ -57,10 +47,12 @@ struct Step2Args {
   uint32_t ntiles;
   int flags;
   int dirty;  // no slab: some tile of the mask may be set
+  int bulk;   // an overlapped pair's planes outside the slab (whole tiles) and nothing else
 };
 
-// A workgroup per (tile, chunk of the planes outside the slab); each then takes its share of the
-// slab's cells, so the launch stays balanced whatever the slab holds.
+// A workgroup per (tile, chunk of its planes); of a tile whose rows the slab holds, the planes outside the
+// slab in two steps and as many parts of those inside in one, so that the launch stays balanced
+// whatever the slab holds.
 template <typename T, int FACES, bool FORCE>
 __global__ __launch_bounds__(step2_threads<T>()) void k_step2(Step2Args<T> A) {
   constexpr int NT = step2_threads<T>();
@@ -70,8 +62,10 @@ __global__ __launch_bounds__(step2_threads<T>()) void k_step2(Step2Args<T> A) {
   const uint32_t b = xcd_remap(blockIdx.x, nblocks);
   const uint32_t txi = b % A.L.ntx, r = b / A.L.ntx;
   const uint32_t tyi = r % A.L.nty, ch = r / A.L.nty;
-  int sa, sb;
-  slab_range(A.slab, G.nz, sa, sb);
+  const Box box = slab_box(A.slab, G, A.bulk, A.L.oy);
+  const int y0 = (int)(tyi * A.L.oy), y1 = min(y0 + (int)A.L.oy, G.ny);
+  const bool in_slab = y0 < box.yb && y1 > box.ya;  // the box holds whole tiles of rows
+  const int sa = in_slab ? box.za : 0, sb = in_slab ? box.zb : 0;
   Lattice2 D;
   D.src = gbytes<T>(A.src);
   D.dst = gbytes<T>(A.dst);
@@ -79,10 +73,12 @@ __global__ __launch_bounds__(step2_threads<T>()) void k_step2(Step2Args<T> A) {
   D.U = gbytes<T>(A.U);
   D.tiles = gbytes<uint8_t>(A.tiles);
   D.u_all = A.flags & LBM_FLAG_WRITE_U_ALL;
-  if (A.slab) {
-    slab_range(A.slab + 2, G.nz, D.fa, D.fb);  // planes of the second half's windows: whole tiles
-    D.fa &= ~(int)(kTile - 1);
-    D.fb = (D.fb + (int)kTile - 1) & ~(int)(kTile - 1);
+  if (A.bulk) {
+    D.fa = D.fb = 0;  // every flagged tile lies in the slab
+  } else if (A.slab) {
+    const Box f = slab_box(A.slab + 4, G, true, 1);  // planes of the second half's windows
+    D.fa = f.za;
+    D.fb = f.zb;
   } else {
     D.fa = 0;
     D.fb = A.dirty ? G.nz : 0;
@@ -93,40 +89,51 @@ __global__ __launch_bounds__(step2_threads<T>()) void k_step2(Step2Args<T> A) {
   if (c0 < min(c1, sa)) march2<T, FACES, FORCE, NT>(s, G, D, A.omega, A.L, txi, tyi, c0, min(c1, sa));
   if (max(c0, sa) < c1)
     march2<T, FACES, FORCE, NT>(s, G, D, A.omega, A.L, txi, tyi, max(c0, sa) + (sb - sa), c1 + (sb - sa));
+  if (A.bulk) return;
   if constexpr (FACES != FACES_GENERAL && !FORCE) {
-    const uint32_t cells = (uint32_t)(sb - sa) * G.plane, first = (uint32_t)sa * G.plane;
+    const uint32_t nzs = (uint32_t)(sb - sa);
+    const int p0 = sa + (int)(ch * nzs / A.L.nchunk), p1 = sa + (int)((ch + 1) * nzs / A.L.nchunk);
+    const int x0 = (int)(txi * A.L.ox), x1 = min(x0 + (int)A.L.ox, G.nx);
     const uint32_t fs = FACES == FACES_WALLS ? free_slip_faces(G) : 0u;
+    const uint32_t w = (uint32_t)(x1 - x0), wh = w * (uint32_t)(y1 - y0), cells = wh * (uint32_t)(p1 - p0);
 #pragma unroll 1
-    for (uint32_t k = blockIdx.x * NT + threadIdx.x; k < cells; k += nblocks * NT) {
+    for (uint32_t k = threadIdx.x; k < cells; k += NT) {
+      const uint32_t z = k / wh, rem = k - z * wh, y = rem / w, x = rem - y * w;
       step_one<T, FACES == FACES_WALLS>(gbytes<T>(A.mid), D.dst, gbytes<T>(A.F), D.U, D.tiles, G, A.omega,
-                                        A.flags, first + k, fs);
+                                        A.flags, (uint32_t)x0 + x, (uint32_t)y0 + y, (uint32_t)p0 + z, fs);
     }
   }
   for (uint32_t k = blockIdx.x * NT + threadIdx.x; k < A.ntiles; k += nblocks * NT) A.tiles_next[k] = 0;
 }
 
-// Step n of the slab's planes and one beside it on either side, from the current state into the
-// middle buffer, with the force of the first bubble half. The planes are widened to whole tiles, so
-// that the velocity is written in every tile that half flagged.
+// One step of a slab's cells from src into dst. SLAB_FIRST: step n of a pair, from the current state into
+// the middle buffer, with one row and plane beside the slab on every side; widened to whole force
+// tiles, so that the velocity is written in every tile the first bubble half flagged. SLAB_FIRST_WHOLE:
+// the same of an overlapped pair, whose slab is whole tiles. SLAB_SECOND: its step n + 1.
+enum : int { SLAB_FIRST = 0, SLAB_FIRST_WHOLE = 1, SLAB_SECOND = 2 };
+
 template <typename T, bool FS>
-__global__ __launch_bounds__(256) void k_slab(const T* __restrict__ src, T* __restrict__ mid,
+__global__ __launch_bounds__(256) void k_slab(const T* __restrict__ src, T* __restrict__ dst,
                                               T* __restrict__ F, T* __restrict__ U,
                                               const uint8_t* __restrict__ tiles,
                                               uint8_t* __restrict__ tiles_next,
                                               const uint32_t* __restrict__ slab, Geom G, T omega,
-                                              int flags, uint32_t ntiles) {
-  int a, b;
-  slab_range(slab, G.nz, a, b);
-  if (a < b) {
-    a = max(0, min(a - 1, a & ~(int)(kTile - 1)));
-    b = min(G.nz, max(b + 1, (b + (int)kTile - 1) & ~(int)(kTile - 1)));
+                                              int flags, uint32_t ntiles, uint32_t oy, int part) {
+  Box b = slab_box(slab, G, part != SLAB_FIRST, oy);
+  if (b.zb > b.za && part != SLAB_SECOND) {
+    constexpr int m = (int)kTile - 1;
+    b.za = max(0, min(b.za - 1, b.za & ~m));
+    b.ya = max(0, min(b.ya - 1, b.ya & ~m));
+    b.zb = min(G.nz, max(b.zb + 1, (b.zb + m) & ~m));
+    b.yb = min(G.ny, max(b.yb + 1, (b.yb + m) & ~m));
   }
-  const uint32_t cells = (uint32_t)(b - a) * G.plane, first = (uint32_t)a * G.plane;
+  const uint32_t rows = (uint32_t)(b.yb - b.ya) * (uint32_t)G.nx, cells = rows * (uint32_t)(b.zb - b.za);
   const uint32_t fs = FS ? free_slip_faces(G) : 0u;
 #pragma unroll 1
   for (uint32_t k = blockIdx.x * 256 + threadIdx.x; k < cells; k += gridDim.x * 256) {
-    step_one<T, FS>(gbytes<T>(src), gbytes<T>(mid), gbytes<T>(F), gbytes<T>(U), gbytes<uint8_t>(tiles), G,
-                    omega, flags, first + k, fs);
+    const uint32_t z = k / rows, rem = k - z * rows, y = rem / (uint32_t)G.nx, x = rem - y * (uint32_t)G.nx;
+    step_one<T, FS>(gbytes<T>(src), gbytes<T>(dst), gbytes<T>(F), gbytes<T>(U), gbytes<uint8_t>(tiles), G,
+                    omega, flags, x, (uint32_t)b.ya + y, (uint32_t)b.za + z, fs);
   }
   for (uint32_t k = blockIdx.x * 256 + threadIdx.x; k < ntiles; k += gridDim.x * 256) tiles_next[k] = 0;
 }
@@ -145,12 +152,14 @@ uint32_t tile_threads(const Geom& G, uint32_t ox, uint32_t oy) {
 // Tiles and chunks of a lattice for the two-step pass. A compute unit holds one workgroup, so a
 // launch takes time in proportion to the planes a workgroup marches, two of them beside its chunk,
 // times its rows, two of them beside its tile (most of a halo row's loads hit the L2, so this
-// counts it too high; measured within 5 % of the best of a sweep on eleven lattices from 30 x 30 x
-// 90 to 256 x 256 x 256). Pieces of rows cost a quarter more than whole ones, whose loads and stores
-// are contiguous over the tile: 128 x 128 x 512 FP32 122 us per step in whole rows of 6, 132 us in
-// tiles of 64 x 13; 256 x 256 x 256 253 us in whole rows of 2 (every intermediate row computed
-// twice), 284 us in tiles of 64 x 13, 264 us in tiles of 128 x 5.
-bool choose_tiles2(const Geom& G, size_t elem, Tiles2* best) {
+// counts it too high; within 6 % of the best of a sweep on eleven lattices from 30 x 30 x 90 to
+// 256 x 256 x 256). Pieces of rows cost more than whole ones, whose loads and stores are contiguous
+// over the tile, a piece of 512 bytes a quarter, of 128 bytes twice as much: 128 x 128 x 512 FP32
+// 122 us per step in whole rows of 6, 132 us in tiles of 64 x 13, 144 us of 32 x 16; 256 x 256 x 256
+// 253 us in whole rows of 2 (every intermediate row computed twice), 264 us in tiles of 128 x 5, 284 us
+// of 64 x 13, 304 us of 32 x 16; 128 x 128 x 512 FP64 249 us in whole rows of 2, 264 us in tiles of
+// 64 x 5, 299 us of 16 x 16.
+bool choose_tiles2(const Geom& G, size_t elem, uint32_t cus, Tiles2* best) {
   const uint32_t threads = elem == 4 ? step2_threads<float>() : step2_threads<double>();
   const uint32_t align = 128u / (uint32_t)elem;  // cells of a cache line
   const uint32_t nx = (uint32_t)G.nx, ny = (uint32_t)G.ny, nz = (uint32_t)G.nz;
@@ -158,9 +167,9 @@ bool choose_tiles2(const Geom& G, size_t elem, Tiles2* best) {
   for (uint32_t ox = nx; ox >= 1; ox = ox == nx ? (nx - 1) / align * align : ox - align) {
     for (uint32_t oy = 1; oy <= ny && oy <= threads && tile_threads(G, ox, oy) <= threads; ++oy) {
       const uint32_t ntx = div_up(nx, ox), nty = div_up(ny, oy), nt = ntx * nty;
-      const uint32_t nc = std::max(1u, std::min(nz, kStep2Cus / nt));
-      const double v = (double)div_up(nt * nc, kStep2Cus) * ((double)nz / nc + 2.0) * ox * (oy + 2.0) *
-                       (ox == nx ? 1.0 : 1.25);
+      const uint32_t nc = std::max(1u, std::min(nz, cus / nt));
+      const double v = (double)div_up(nt * nc, cus) * ((double)nz / nc + 2.0) * ox * (oy + 2.0) *
+                       (ox == nx ? 1.0 : 1.0 + 128.0 / ((double)ox * elem));
       if (v < cost) {
         cost = v;
         *best = {ox, oy, ntx, nty, nc};
@@ -174,7 +183,7 @@ bool choose_tiles2(const Geom& G, size_t elem, Tiles2* best) {
 namespace {
 
 template <typename T, int FACES, bool FORCE>
-hipError_t launch_typed(lbm_ctx* c, const uint32_t* slab) {
+hipError_t launch_typed(lbm_ctx* c, const uint32_t* slab, bool bulk) {
   const Geom& G = c->geom;
   Step2Args<T> A;
   A.src = static_cast<const T*>(c->pops[c->hs.cur]);
@@ -190,30 +199,48 @@ hipError_t launch_typed(lbm_ctx* c, const uint32_t* slab) {
   A.flags = c->desc.flags;
   A.ntiles = c->ntiles;
   A.dirty = c->hs.flag_clean[c->hs.flag_cur] ? 0 : 1;
-  A.L = c->tiles2;
+  A.bulk = bulk ? 1 : 0;
+  A.L = bulk ? c->tiles2_beside : c->tiles2;
   const uint32_t n = A.L.ntx * A.L.nty * A.L.nchunk;
   hipLaunchKernelGGL((k_step2<T, FACES, FORCE>), dim3(n), dim3(step2_threads<T>()), 0, c->stream, A);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_faces(lbm_ctx* c, const uint32_t* slab) {
+hipError_t launch_faces(lbm_ctx* c, const uint32_t* slab, bool bulk) {
   const bool force = c->desc.flags & LBM_FLAG_STATIC_FORCE;
   if (c->periodic)
-    return force ? launch_typed<T, FACES_GENERAL, true>(c, slab) : launch_typed<T, FACES_GENERAL, false>(c, slab);
+    return force ? launch_typed<T, FACES_GENERAL, true>(c, slab, bulk)
+                 : launch_typed<T, FACES_GENERAL, false>(c, slab, bulk);
   if (c->general)
-    return force ? launch_typed<T, FACES_WALLS, true>(c, slab) : launch_typed<T, FACES_WALLS, false>(c, slab);
-  return force ? launch_typed<T, FACES_BB, true>(c, slab) : launch_typed<T, FACES_BB, false>(c, slab);
+    return force ? launch_typed<T, FACES_WALLS, true>(c, slab, bulk)
+                 : launch_typed<T, FACES_WALLS, false>(c, slab, bulk);
+  return force ? launch_typed<T, FACES_BB, true>(c, slab, bulk) : launch_typed<T, FACES_BB, false>(c, slab, bulk);
 }
 
 template <typename T, bool FS>
-hipError_t launch_slab_typed(lbm_ctx* c, const uint32_t* slab) {
+hipError_t launch_slab_typed(lbm_ctx* c, const uint32_t* slab, int part, hipStream_t s) {
   const Geom& G = c->geom;
-  hipLaunchKernelGGL((k_slab<T, FS>), dim3(std::min(div_up(G.N, 256), 2048u)), dim3(256), step_lds(c),
-                     c->stream, static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->mid),
-                     static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
-                     c->tiles[c->hs.flag_cur ^ 1], slab, G, (T)c->desc.omega, c->desc.flags, c->ntiles);
+  const bool second = part == SLAB_SECOND;
+  const void* src = second ? c->mid : c->pops[c->hs.cur];
+  void* dst = second ? c->pops[c->hs.cur ^ 1] : c->mid;
+  hipLaunchKernelGGL((k_slab<T, FS>), dim3(std::min(div_up(G.N, 256), 2048u)), dim3(256),
+                     part == SLAB_FIRST_WHOLE ? 0 : step_lds(c), s, static_cast<const T*>(src),
+                     static_cast<T*>(dst), static_cast<T*>(c->force), static_cast<T*>(c->vel),
+                     c->tiles[c->hs.flag_cur], c->tiles[c->hs.flag_cur ^ 1], slab, G, (T)c->desc.omega,
+                     c->desc.flags, c->ntiles, part == SLAB_FIRST ? c->tiles2.oy : c->tiles2_beside.oy, part);
   return hipGetLastError();
+}
+
+hipError_t launch_slab_part(lbm_ctx* c, const uint32_t* slab, int part, hipStream_t s) {
+  hipError_t e;
+  if (c->elem == 4)
+    e = c->general ? launch_slab_typed<float, true>(c, slab, part, s) : launch_slab_typed<float, false>(c, slab, part, s);
+  else
+    e = c->general ? launch_slab_typed<double, true>(c, slab, part, s)
+                   : launch_slab_typed<double, false>(c, slab, part, s);
+  if (e == hipSuccess) c->hs.flag_clean[c->hs.flag_cur ^ 1] = true;
+  return e;
 }
 
 }  // namespace
@@ -224,7 +251,7 @@ bool can_step2(const lbm_ctx* c) {
 
 hipError_t launch_step2(lbm_ctx* c, const uint32_t* slab) {
   const hipError_t e = timed(c, c->stream, [&] {
-    return c->elem == 4 ? launch_faces<float>(c, slab) : launch_faces<double>(c, slab);
+    return c->elem == 4 ? launch_faces<float>(c, slab, false) : launch_faces<double>(c, slab, false);
   });
   if (e == hipSuccess) {
     c->hs.cur ^= 1;
@@ -237,12 +264,27 @@ hipError_t launch_step2(lbm_ctx* c, const uint32_t* slab) {
 }
 
 hipError_t launch_slab(lbm_ctx* c, const uint32_t* slab) {
-  hipError_t e;
-  if (c->elem == 4)
-    e = c->general ? launch_slab_typed<float, true>(c, slab) : launch_slab_typed<float, false>(c, slab);
-  else
-    e = c->general ? launch_slab_typed<double, true>(c, slab) : launch_slab_typed<double, false>(c, slab);
-  if (e == hipSuccess) c->hs.flag_clean[c->hs.flag_cur ^ 1] = true;
+  return launch_slab_part(c, slab, SLAB_FIRST, c->stream);
+}
+
+hipError_t launch_pair_bulk(lbm_ctx* c, const uint32_t* slab) {
+  return timed(c, c->stream, [&] {
+    return c->elem == 4 ? launch_faces<float>(c, slab, true) : launch_faces<double>(c, slab, true);
+  });
+}
+
+hipError_t launch_pair_first(lbm_ctx* c, const uint32_t* slab, hipStream_t s) {
+  return launch_slab_part(c, slab, SLAB_FIRST_WHOLE, s);
+}
+
+hipError_t launch_pair_second(lbm_ctx* c, const uint32_t* slab) {
+  const hipError_t e = launch_slab_part(c, slab, SLAB_SECOND, c->stream);
+  if (e == hipSuccess) {
+    c->hs.cur ^= 1;
+    c->hs.last_overlapped = c->hs.last_pair = true;
+    c->hs.forced = false;
+    c->hs.steps += 2;
+  }
   return e;
 }
 

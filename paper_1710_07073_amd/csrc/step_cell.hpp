@@ -59,6 +59,34 @@ __device__ __forceinline__ uint32_t free_slip_faces(const Geom& G) {
   return fs;
 }
 
+// Rows [ya, yb) of planes [za, zb), across all x.
+struct Box {
+  int ya, yb, za, zb;
+};
+
+// The box of a half of a pair of steps from its words (internal.hpp), in whole force tiles if asked,
+// its rows widened to multiples of oy (the rows of the two-step pass's tiles); empty without bubbles.
+__device__ __forceinline__ Box slab_box(const uint32_t* words, const Geom& G, bool whole, uint32_t oy) {
+  Box b = {0, 0, 0, 0};
+  if (words && words[1] != 0u) {
+    constexpr int m = (int)kTile - 1;
+    b.za = max(0, (int)(kSlabBase - words[0]));
+    b.zb = (int)words[1];
+    b.ya = max(0, (int)(kSlabBase - words[2]));
+    b.yb = (int)words[3];
+    if (whole) {
+      b.za &= ~m;
+      b.ya &= ~m;
+      b.zb = (b.zb + m) & ~m;
+      b.yb = (b.yb + m) & ~m;
+    }
+    b.ya = (int)((uint32_t)b.ya / oy * oy);
+    b.yb = min(G.ny, (int)(((uint32_t)b.yb + oy - 1) / oy * oy));
+    b.zb = min(G.nz, b.zb);
+  }
+  return b;
+}
+
 // Byte pointers into device global memory: loads and stores through them are global
 // instructions (a scalar base plus a 32-bit lane offset where the base is uniform), also when the
 // base comes from a table in memory rather than a kernel argument.

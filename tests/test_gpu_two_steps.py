@@ -120,6 +120,50 @@ def test_method_step_pairs_equal_single_steps(nb, d, z, bc, precision):
         _same(*sims)
 
 
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+@pytest.mark.parametrize("bc", [WALLS, TOP, MIXED], ids=["walls", "top", "mixed"])
+@pytest.mark.parametrize("nb,d,z", [(1, 3.0, (0.3, 0.5)), (1, 2.0, (0.0, 0.02)), (7, 2.0, (0.0, 1.0)),
+                                    (300, 2.0, (0.4, 0.9))])
+def test_overlapped_pairs_equal_single_steps(nb, d, z, bc, precision):
+    """The same with the bubble kernels and the slab's first step beside the rest of the lattice, single
+    overlapped steps in between (odd counts, calls of one step) and bubbles moved from the host."""
+    shape = (96, 80, 70)
+    pos, dd, _ = _bubbles(shape, nb, d, 3, z)
+    for steps, graph in ((8, 0), (12, 4), (31, 10)):
+        stream = torch.cuda.Stream()
+        sims = []
+        for paired in (False, True):
+            torch.cuda.synchronize()
+            sim = _sim(shape, precision, bc, stream=stream)
+            sim.add_bubbles(pos, dd, S.bubble_params(g=1e-4, sigma=1e-3))
+            L.lbm_set_overlap(sim.ctx, paired)
+            torch.cuda.synchronize()
+            for n in (steps, 3):
+                if paired:
+                    sim.run(n, graph_steps=graph)
+                else:
+                    sim.step(n)
+                with torch.cuda.stream(stream):
+                    sim.bubbles.t["z"].copy_(torch.from_numpy(pos[2][::-1].copy()))
+            sim.run(1) if paired else sim.step(1)
+            sim.check()
+            sims.append(sim)
+        _same(*sims)
+
+
+def test_overlapped_pair_reports_a_bubble_beyond_its_slab():
+    """A bubble thrown further than the slab's margin is reported, as by an overlapped step."""
+    sim = _sim((96, 80, 70), "f32", WALLS)
+    sim.add_bubbles([[40.0], [40.0], [20.0]], [2.0], S.bubble_params(g=1e-4, sigma=1e-3),
+                    vel=np.array([[0.0], [0.0], [24.0]]))
+    L.lbm_set_overlap(sim.ctx, True)
+    sim.run(2)
+    with pytest.raises(L.LbmError) as e:
+        sim.check()
+    assert e.value.code == L.LBM_EUNSUPPORTED
+    sim.close()
+
+
 @pytest.mark.parametrize("speed", [0.5, 3.0, 20.0])
 @pytest.mark.parametrize("nb", [1, 5, 300])
 def test_pairs_follow_fast_bubbles(nb, speed):
