@@ -140,6 +140,8 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   G.N = (uint32_t)desc->nx * desc->ny * desc->nz;
   G.plane = (uint32_t)desc->nx * desc->ny;
   lbm::set_layout(G, (desc->flags & LBM_FLAG_PLAIN_SOA) != 0);
+  const size_t elem = desc->precision == LBM_FP32_SHIFTED ? 4 : 8;
+  lbm::set_stores(G, elem, 19 * (size_t)G.N * elem);
   for (int f = 0; f < 6; ++f) G.bc[f] = desc->bc[f];
   G.tnx = (int)L.tnx;
   G.tny = (int)L.tny;

@@ -413,6 +413,8 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
   std::vector<int32_t> bcol(L.nb_total > 0 ? L.nb_total : 1, 0);
   hipError_t e = launch_fill(pool, L.pool, b->stream);
   if (e == hipSuccess) e = launch_fill(scratch, L.scratch, b->stream);
+  size_t cells = 0;
+  for (int c = 0; c < ncols; ++c) cells += (size_t)cols[c].nx * cols[c].ny * cols[c].nz;
   for (int c = 0; c < ncols && e == hipSuccess; ++c) {
     const lbm_column& k = cols[c];
     ColumnDev& D = b->host[c];
@@ -423,6 +425,7 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
     D.G.N = (uint32_t)k.nx * k.ny * k.nz;
     D.G.plane = (uint32_t)k.nx * k.ny;
     set_layout(D.G, (flags & LBM_FLAG_PLAIN_SOA) != 0);
+    set_stores(D.G, elem, 19 * cells * elem);
     for (int f = 0; f < 6; ++f) {
       D.G.bc[f] = k.bc[f];
       if (k.bc[f] != LBM_BC_BOUNCE_BACK) b->general = true;

@@ -49,12 +49,33 @@ struct Geom {
   uint32_t zs;     // element stride between z-planes of one population
   int bc[6];       // -x, +x, -y, +y, -z, +z
   int tnx, tny;    // tile grid (8^3 tiles) in x and y
+  bool stream1, stream2;  // one and two steps per launch store past the caches (set_stores)
 };
 
 inline void set_layout(Geom& G, bool plain_soa) {
   G.qs = plain_soa ? G.N : G.plane;
   G.zs = plain_soa ? G.plane : 19u * G.plane;
 }
+
+// The stores of a liquid step go past the caches (nontemporal) where that is the faster way:
+//   - the states the launch reads and writes do not both fit in the 256 MB last-level cache (the next
+//     launch then reads from there what this one stored): FP32 per step, two steps per launch, past the
+//     caches and through them: 96 x 80 x 200 (117 MB) 28.8 us and 24.3, one step 45.9 and 39.1;
+//     64 x 64 x 192 16.6 and 15.1, 22.2 and 19.3; FP64 28.1 and 23.7, 40.8 and 36.2; but
+//     128 x 128 x 128 (159 MB) 34.5 and 36.0;
+//   - and a wavefront's stores cover whole 64-byte pieces, which needs rows of such: a piece two wavefronts
+//     share goes out in two parts, unless the L2 joins them. 120 x 120 x 360 110 us past the caches and 94
+//     through, 101 x 67 x 251 38.5 and 25.6 (one step 71 and 57). Not so one step in FP64 (101 x 67 x 251
+//     113 and 136).
+// state_bytes: the populations of every lattice the launch covers.
+inline void set_stores(Geom& G, size_t elem, size_t state_bytes) {
+  const bool large = state_bytes > (size_t)128 << 20, rows = (size_t)G.nx * elem % 64 == 0;
+  G.stream1 = large && (rows || elem == 8);
+  G.stream2 = large && rows;
+}
+
+// Keeps the two branches of such a choice apart (merged, the stores lose the hint).
+__device__ __forceinline__ void keep_branch() { asm volatile(""); }
 
 // Layout index of the cell with flat index cell = x + nx * (y + ny * z).
 __device__ __forceinline__ uint32_t layout_cell(const Geom& G, uint32_t cell, uint32_t z) {

@@ -175,6 +175,7 @@ __device__ void march2(Plane2<T, NT>* s, const Geom& G, const Lattice2& A, T ome
   };
   const uint32_t xy4 = ((uint32_t)y * G.nx + (uint32_t)x) * esz;
   const uint32_t zs4 = G.zs * esz, n4 = G.N * esz, plane4 = G.plane * esz;
+  const bool stream = G.stream2;
 
   // the 19 populations arriving at the cell in plane k of the source buffer (and its force)
   auto load = [&](int k, T* g, T* f) {
@@ -351,10 +352,17 @@ __device__ void march2(Plane2<T, NT>* s, const Geom& G, const Lattice2& A, T ome
         collide<T, FORCE>(f, f1[0], f1[1], f1[2], omega, ux, uy, uz);
         const int zo = k - 1;
         const uint32_t lc4 = xy4 + (uint32_t)zo * zs4;
+        if (stream) {
+          keep_branch();
 #pragma unroll
-        for (int q = 0; q < 19; ++q)
-          __builtin_nontemporal_store(
-              f[q], reinterpret_cast<gmem<T>*>(A.dst + (int64_t)q * G.qs * (int)esz + lc4));
+          for (int q = 0; q < 19; ++q)
+            __builtin_nontemporal_store(
+                f[q], reinterpret_cast<gmem<T>*>(A.dst + (int64_t)q * G.qs * (int)esz + lc4));
+          keep_branch();
+        } else {
+#pragma unroll
+          for (int q = 0; q < 19; ++q) store_at<T>(A.dst + (int64_t)q * G.qs * (int)esz, lc4, f[q]);
+        }
         const bool flagged_planes = zo >= A.fa && zo < A.fb;
         if (FORCE || A.u_all || flagged_planes) {
           bool write = FORCE || A.u_all;

@@ -170,9 +170,16 @@ __device__ __forceinline__ void step_cell_bb(const gchar* sb, gchar* db, gchar* 
   }
   // one scalar base and a 32-bit offset per store (a 32-bit sum cannot be widened by the compiler)
   const uint32_t qs4 = G.qs * esz;
+  if (G.stream1) {
+    keep_branch();
 #pragma unroll
-  for (int q = 0; q < 19; ++q)
-    __builtin_nontemporal_store(g[q], reinterpret_cast<gmem<T>*>(db + (lc4 + (uint32_t)q * qs4)));
+    for (int q = 0; q < 19; ++q)
+      __builtin_nontemporal_store(g[q], reinterpret_cast<gmem<T>*>(db + (lc4 + (uint32_t)q * qs4)));
+    keep_branch();
+  } else {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) store_at<T>(db, lc4 + (uint32_t)q * qs4, g[q]);
+  }
   if (forced || (flags & LBM_FLAG_WRITE_U_ALL)) {
     store_at<T>(Ub, c4, ux);
     store_at<T>(Ub, c4 + n4, uy);
