@@ -438,6 +438,8 @@ typedef struct {
 
 typedef struct lbm_batch lbm_batch;
 
+/* Batches of 2^20 cells or more with walls on every face also take a middle buffer as large as one
+ * state in scratch (two steps per launch, see lbm_batch_step). */
 lbm_status lbm_batch_bytes_required(const lbm_column* cols, int32_t ncols, int32_t precision,
                                     size_t* pool_bytes, size_t* scratch_bytes);
 /* Lay the columns out in pool, initialise every population to g = 0 and the fields to 0. The call
@@ -445,7 +447,8 @@ lbm_status lbm_batch_bytes_required(const lbm_column* cols, int32_t ncols, int32
 lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precision, int32_t flags,
                           void* pool, void* scratch, void* stream, lbm_batch** out);
 /* Cells per work item of each column in the batched liquid step (multiple of 256, at most 65536):
- * the tuning knob of the batch autotuner; results do not depend on it. */
+ * the tuning knob of the batch autotuner; results do not depend on it. Neither it nor the occupancy
+ * below applies to steps taken in pairs. */
 lbm_status lbm_batch_set_items(lbm_batch* batch, const int32_t* item_cells);
 lbm_status lbm_batch_get_items(lbm_batch* batch, int32_t* item_cells);
 /* Occupancy of the batched liquid step (as lbm_set_step_occupancy): at most workgroups_per_cu of
@@ -463,7 +466,10 @@ lbm_status lbm_batch_get_step_occupancy(lbm_batch* batch, int32_t* workgroups_pe
  * LBM_EDEVICE. grid (nullable) receives the workgroups of the last persistent launch. */
 lbm_status lbm_batch_set_persistent(lbm_batch* batch, int32_t enable);
 lbm_status lbm_batch_get_persistent(lbm_batch* batch, int32_t* enabled, int32_t* grid);
-/* nsteps method steps of every column (eager launches). nb must equal the total bubble count. */
+/* nsteps method steps of every column (eager launches). nb must equal the total bubble count. Where
+ * every face is a wall and the batch holds 2^20 cells or more, steps are taken in pairs (two liquid
+ * steps per launch, the same results), an odd last one by itself; a pair swaps the state buffers
+ * once (lbm_batch_column names the current one). */
 lbm_status lbm_batch_step(lbm_batch* batch, const bubble_params* params, const bubble_soa* soa,
                           int32_t nb, int32_t nsteps);
 /* As lbm_batch_step, with graph_steps steps captured into a HIP graph and replayed (see lbm_run). */

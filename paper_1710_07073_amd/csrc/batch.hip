@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <functional>
 #include <new>
 #include <string.h>
 #include <vector>
@@ -14,7 +15,19 @@
 #include "collide.hpp"
 #include "graph.hpp"
 
+namespace lbm {
+// Host-side step state of a batch, the same for all columns.
+struct BatchState {
+  int cur;         // population buffer holding the current state
+  int flag_cur;    // current tile mask
+  bool flag_clean[2];
+  int spar;        // parity of the next pair of steps (its slab words)
+  int64_t steps;
+};
+}  // namespace lbm
+
 struct lbm_batch {
+  lbm::BatchState hs;
   int ncols;
   int32_t precision;
   size_t elem;
@@ -29,9 +42,6 @@ struct lbm_batch {
   int32_t* bubble_col;                // bubble -> column (scratch)
   int32_t nb_total;
   uint32_t nitems;
-  int cur;          // population buffer holding the current state, same for all columns
-  int flag_cur;     // current tile mask, same for all columns
-  bool flag_clean[2];
   int32_t* status;
   bool persistent;      // method steps as persistent launches (lbm_batch_set_persistent)
   uint32_t* barrier;    // grid-barrier words of the persistent launch
@@ -43,10 +53,12 @@ struct lbm_batch {
   double* result;
   uint32_t nred;
   hipStream_t stream;
-  int64_t steps;
   int32_t step_wgs;     // at most this many liquid-step workgroups per compute unit (0: no cap)
   uint32_t lds_per_cu;  // LDS bytes of one compute unit
-  lbm::StepGraph graph;
+  uint32_t* blocks2;    // workgroups of the two-step launch: (column, block within it) (scratch)
+  uint32_t nblocks2;    // 0: steps are not taken in pairs
+  uint32_t nblocks_slab;  // those of the slab launch, behind them
+  lbm::GraphCache<lbm::BatchState> graph;  // two: an odd number of pairs flips the buffers
 };
 
 namespace lbm {
@@ -55,6 +67,7 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
+constexpr uint32_t kNoColumn = ~0u;  // a two-step workgroup without work
 constexpr uint32_t kSumBlocks = 16;  // workgroups per column of the per-column sums
 
 // One liquid step of every column: a workgroup per work item.
@@ -65,6 +78,52 @@ __global__ __launch_bounds__(256) void k_batch_step(const ColumnDev* __restrict_
   // each XCD takes a contiguous range of items (measured faster here than launch order, unlike
   // the single-lattice step)
   batch_item<T, FACES>(cols, item_col, xcd_remap(blockIdx.x, nitems), cur, flag, flags);
+}
+
+// Two liquid steps of every column in one launch (step2_cell.hpp), with the slab of each: see step2.hip.
+// What a column's launches of a pair name.
+template <typename T>
+__device__ __forceinline__ Step2Args<T> pair_args(const ColumnDev& C, int cur, int flag, int spar) {
+  Step2Args<T> A;
+  A.src = static_cast<const T*>(C.pops[cur]);
+  A.mid = static_cast<const T*>(C.mid);
+  A.dst = static_cast<T*>(C.pops[cur ^ 1]);
+  A.F = static_cast<T*>(C.F);
+  A.U = static_cast<T*>(C.U);
+  A.tiles = C.tiles[flag];
+  A.tiles_next = C.tiles[flag ^ 1];
+  A.slab = C.slab + kSlabWords * spar;
+  A.G = C.G;
+  A.omega = (T)C.omega;
+  A.L = C.tiles2;
+  A.ntiles = (uint32_t)C.G.tnx * C.G.tny * (((uint32_t)C.G.nz + kTile - 1) / kTile);
+  A.flags = 0;
+  A.dirty = 0;
+  A.bulk = 0;
+  return A;
+}
+
+template <typename T, int FACES>
+__global__ __launch_bounds__(step2_threads<T>()) void k_batch_step2(const ColumnDev* __restrict__ cols,
+                                                                    const uint32_t* __restrict__ blocks,
+                                                                    int cur, int flag, int spar) {
+  __shared__ Plane2<T, step2_threads<T>()> s[2];
+  const uint32_t col = blocks[2 * blockIdx.x], b = blocks[2 * blockIdx.x + 1];
+  if (col == kNoColumn) return;
+  const Step2Args<T> A = pair_args<T>(cols[col], cur, flag, spar);
+  step2_block<T, FACES, false>(s, A, b);
+}
+
+// The first step of every column's slab, by a share of the workgroups in proportion to its cells.
+template <typename T, bool FS>
+__global__ __launch_bounds__(256) void k_batch_slab(const ColumnDev* __restrict__ cols,
+                                                    const uint32_t* __restrict__ blocks, int cur, int flag,
+                                                    int spar) {
+  const ColumnDev& C = cols[blocks[2 * blockIdx.x]];
+  const Step2Args<T> P = pair_args<T>(C, cur, flag, spar);
+  const SlabArgs<T> A = {P.src, const_cast<T*>(P.mid), P.F, P.U, P.tiles, P.tiles_next, P.slab, P.G,
+                         P.omega, 0, P.ntiles, P.L.oy, SLAB_FIRST};
+  slab_block<T, FS>(A, blocks[2 * blockIdx.x + 1], C.slab_blocks);
 }
 
 // Per-column sums (eq. (10)) of the current state: kSumBlocks workgroups per column accumulate
@@ -146,15 +205,107 @@ bool column_ok(const lbm_column& c) {
   return cells * 19.0 < 2147483648.0;
 }
 
+// Batches from this size on take their method steps in pairs: 4 columns of 36 to 44 cells across, 0.8M
+// cells, 52 us per step one by one and 55 in pairs; 48 of 16 to 24, 1.1M, 70 and 69; 6 of 40 to 60, 2.2M,
+// 106 and 89; 48 of 24 to 96, 30M, 900 and 669; the nine tanks of Table 5, 7M, 246 and 175.
+constexpr size_t kBatchPairMinCells = 1u << 20;
+
+// As pairs_ok() of a single lattice, for every column.
+bool batch_pairs_ok(const lbm_column* cols, int ncols, size_t elem, int flags) {
+  if (flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL)) return false;
+  size_t total = 0;
+  for (int c = 0; c < ncols; ++c) {
+    for (int f = 0; f < 6; ++f)
+      if (cols[c].bc[f] == LBM_BC_PERIODIC) return false;
+    const size_t n = (size_t)cols[c].nx * cols[c].ny * cols[c].nz;
+    if (19 * n * elem > 0xffffffffull) return false;
+    total += n;
+  }
+  return total >= kBatchPairMinCells;
+}
+
+// The workgroups of the two-step launch: a column's tiles are the cheapest of a lattice of its size, its
+// planes are cut into chunks. A chunk's tiles stay together on one XCD (workgroup i runs on XCD i modulo
+// 8), where they read each other's halo rows through the L2; the costliest chunks come first, each dealt to
+// the least loaded XCD. The length of the chunks is that of the shortest of a range of schedules, played
+// through with one workgroup per compute unit: long chunks leave compute units idle at the end, short ones
+// march more halo planes. Costs are in planes of full workgroups.
+void plan_pairs(const lbm_column* cols, int ncols, size_t elem, std::vector<Tiles2>& tiles,
+                std::vector<uint32_t>& blocks) {
+  struct Chunk {
+    double cost;  // of each tile
+    uint32_t col, ch;
+  };
+  constexpr int kXcds = 8;
+  const double full = elem == 4 ? step2_threads<float>() : step2_threads<double>();
+  constexpr double kLeast = 0.6, kStart = 1.0;  // of a plane, however few threads it takes; of a workgroup
+  std::vector<double> plane(ncols);
+  double total = 0.0;
+  tiles.resize(ncols);
+  for (int c = 0; c < ncols; ++c) {
+    Geom G;
+    memset(&G, 0, sizeof(G));
+    G.nx = cols[c].nx;
+    G.ny = cols[c].ny;
+    G.nz = cols[c].nz;
+    choose_tiles2(G, elem, 1, &tiles[c]);
+    plane[c] = std::max(kLeast, tiles[c].ox * (tiles[c].oy + 2.0) / full);
+    total += plane[c] * tiles[c].ntx * tiles[c].nty * G.nz;
+  }
+  double best = 1e300;
+  std::vector<uint32_t> nchunk(ncols);
+  std::vector<Chunk> chunks;
+  std::vector<uint32_t> xcd[kXcds];
+  for (double per_cu = 0.8; per_cu < 10.0; per_cu *= 1.06) {
+    const double most = total / (kCus * per_cu);
+    chunks.clear();
+    for (int c = 0; c < ncols; ++c) {
+      const double nz = cols[c].nz;
+      nchunk[c] = (uint32_t)std::min(std::max(1.0, ceil(plane[c] * nz / most)), std::max(1.0, nz / 4));
+      for (uint32_t i = 0; i < nchunk[c]; ++i)
+        chunks.push_back({plane[c] * (nz / nchunk[c] + 2.0) + kStart, (uint32_t)c, i});
+    }
+    std::stable_sort(chunks.begin(), chunks.end(), [](const Chunk& a, const Chunk& b) { return a.cost > b.cost; });
+    double load[kXcds] = {}, end = 0.0;
+    std::vector<double> cu(kCus, 0.0);  // the time each compute unit is free, a heap per XCD
+    for (auto& l : xcd) l.clear();
+    for (const Chunk& k : chunks) {
+      const int x = (int)(std::min_element(load, load + kXcds) - load);
+      const uint32_t nt = tiles[k.col].ntx * tiles[k.col].nty;
+      load[x] += k.cost * nt;
+      for (uint32_t i = 0; i < nt; ++i) {
+        xcd[x].push_back(k.col);
+        xcd[x].push_back(k.ch * nt + i);
+        const auto lo = cu.begin() + x * (kCus / kXcds), hi = lo + kCus / kXcds;
+        std::pop_heap(lo, hi, std::greater<double>());
+        end = std::max(end, *(hi - 1) += k.cost);
+        std::push_heap(lo, hi, std::greater<double>());
+      }
+    }
+    if (end < best) {
+      best = end;
+      size_t longest = 0;
+      for (const auto& l : xcd) longest = std::max(longest, l.size() / 2);
+      blocks.assign(longest * 2 * kXcds, kNoColumn);
+      for (int x = 0; x < kXcds; ++x)
+        for (size_t j = 0; j < xcd[x].size(); ++j) blocks[(j / 2 * kXcds + x) * 2 + j % 2] = xcd[x][j];
+      for (int c = 0; c < ncols; ++c) tiles[c].nchunk = nchunk[c];
+    }
+  }
+}
+
 struct BatchLayout {
   std::vector<size_t> pops0, pops1, force, vel, tiles0, tiles1, tcount, tlist;
   std::vector<uint32_t> ntiles;
-  size_t pool, table, bcol, jobs, job_count, item_col, barrier, partials, result, status, scratch;
-  uint32_t total_tiles, max_items;
+  std::vector<size_t> mid;
+  std::vector<Tiles2> tiles2;
+  std::vector<uint32_t> blocks2, slab_blocks;
+  size_t pool, table, bcol, jobs, job_count, item_col, barrier, partials, result, status, slab, blocks, init, scratch;
+  uint32_t total_tiles, max_items, nblocks2;
   int32_t nb_total;
 };
 
-bool layout_batch(const lbm_column* cols, int ncols, size_t elem, BatchLayout& L) {
+bool layout_batch(const lbm_column* cols, int ncols, size_t elem, int flags, BatchLayout& L) {
   L.pool = 0;
   size_t tiles = 0;
   L.nb_total = 0;
@@ -202,7 +353,28 @@ bool layout_batch(const lbm_column* cols, int ncols, size_t elem, BatchLayout& L
   const size_t nparts = std::max<size_t>(kRedBlocks, (size_t)ncols * kSumBlocks);
   L.result = align_up(L.partials + nparts * 4 * sizeof(double));
   L.status = align_up(L.result + (size_t)ncols * 4 * sizeof(double));
-  L.scratch = align_up(L.status + sizeof(int32_t));
+  L.slab = align_up(L.status + sizeof(int32_t));
+  L.blocks = align_up(L.slab + (size_t)ncols * 2 * kSlabWords * sizeof(uint32_t));
+  const bool pairs = batch_pairs_ok(cols, ncols, elem, flags);
+  if (pairs) plan_pairs(cols, ncols, elem, L.tiles2, L.blocks2);
+  L.nblocks2 = (uint32_t)(L.blocks2.size() / 2);
+  size_t cells = 0;
+  for (int c = 0; c < ncols; ++c) cells += (size_t)cols[c].nx * cols[c].ny * cols[c].nz;
+  for (int c = 0; pairs && c < ncols; ++c) {
+    const size_t n = (size_t)cols[c].nx * cols[c].ny * cols[c].nz;
+    L.slab_blocks.push_back((uint32_t)std::min(std::max<size_t>(2048 * n / cells, 8), (n + 255) / 256));
+    for (uint32_t i = 0; i < L.slab_blocks[c]; ++i) {
+      L.blocks2.push_back((uint32_t)c);
+      L.blocks2.push_back(i);
+    }
+  }
+  L.init = align_up(L.blocks + L.blocks2.size() * sizeof(uint32_t));
+  // the middle buffers, of which a pair writes what it reads
+  L.scratch = L.init;
+  for (int c = 0; pairs && c < ncols; ++c) {
+    L.mid.push_back(L.scratch);
+    L.scratch = align_up(L.scratch + 19 * (size_t)cols[c].nx * cols[c].ny * cols[c].nz * elem);
+  }
   return true;
 }
 
@@ -241,7 +413,7 @@ template <typename T, int FACES>
 hipError_t batch_step_faces(lbm_batch* b) {
   hipLaunchKernelGGL((k_batch_step<T, FACES>), dim3(b->nitems), dim3(256),
                      occupancy_lds(b->lds_per_cu, b->step_wgs), b->stream, b->dev, b->item_col_dev,
-                     b->nitems, b->cur, b->flag_cur, b->flags);
+                     b->nitems, b->hs.cur, b->hs.flag_cur, b->flags);
   return hipGetLastError();
 }
 
@@ -254,10 +426,10 @@ hipError_t batch_step_typed(lbm_batch* b) {
   }
 }
 
-// One method step of every column: bubble half, then the liquid step.
-hipError_t batch_method_step(lbm_batch* b, const bubble_params* p, const bubble_soa* s, int32_t nb) {
-  const int m = b->flag_cur ^ 1;
-  if (!b->flag_clean[m]) {
+// The tile mask of the next bubble half, clear.
+hipError_t next_mask(lbm_batch* b) {
+  const int m = b->hs.flag_cur ^ 1;
+  if (!b->hs.flag_clean[m]) {
     for (int c = 0; c < b->ncols; ++c) {
       const hipError_t e = launch_fill(b->host[c].tiles[m],
                                        (size_t)b->host[c].G.tnx * b->host[c].G.tny *
@@ -266,8 +438,11 @@ hipError_t batch_method_step(lbm_batch* b, const bubble_params* p, const bubble_
       if (e != hipSuccess) return e;
     }
   }
-  b->flag_clean[m] = false;
-  b->flag_cur = m;
+  return hipSuccess;
+}
+
+// What the bubble kernels name, with mask m (and the tile jobs of its parity).
+ManyColumns bubble_columns(const lbm_batch* b, int m) {
   ManyColumns geo;
   geo.cols = b->dev;
   geo.bubble_col = b->bubble_col;
@@ -275,14 +450,83 @@ hipError_t batch_method_step(lbm_batch* b, const bubble_params* p, const bubble_
   geo.jobs = b->jobs;
   geo.job_count = b->job_count;
   geo.job_cap = b->job_cap;
-  geo.par = b->cur;  // alternates every step, like the tile jobs' lists
-  hipError_t e = launch_bubbles_batch(geo, b->elem, p, s, nb, b->status, b->stream);
+  geo.par = m;  // alternates every step
+  geo.slab_word = geo.slab_clear = -1;
+  return geo;
+}
+
+// The bubble half of a method step. half: 0 or 1 in a pair of steps, else -1.
+hipError_t batch_bubble_half(lbm_batch* b, const bubble_params* p, const bubble_soa* s, int32_t nb, int half) {
+  const hipError_t e = next_mask(b);
+  if (e != hipSuccess) return e;
+  const int m = b->hs.flag_cur ^ 1;
+  b->hs.flag_clean[m] = false;
+  b->hs.flag_cur = m;
+  ManyColumns geo = bubble_columns(b, m);
+  if (half >= 0) geo.slab_word = kSlabWords * b->hs.spar + 4 * half;
+  if (half == 0) geo.slab_clear = kSlabWords * (b->hs.spar ^ 1);
+  return launch_bubbles_batch(geo, b->elem, p, s, nb, b->status, b->stream);
+}
+
+// One method step of every column: bubble half, then the liquid step.
+hipError_t batch_method_step(lbm_batch* b, const bubble_params* p, const bubble_soa* s, int32_t nb) {
+  hipError_t e = batch_bubble_half(b, p, s, nb, -1);
   if (e != hipSuccess) return e;
   e = b->elem == 4 ? batch_step_typed<float>(b) : batch_step_typed<double>(b);
   if (e != hipSuccess) return e;
-  b->cur ^= 1;
-  b->flag_clean[b->flag_cur ^ 1] = true;
-  ++b->steps;
+  b->hs.cur ^= 1;
+  b->hs.flag_clean[b->hs.flag_cur ^ 1] = true;
+  ++b->hs.steps;
+  return hipSuccess;
+}
+
+template <typename T>
+hipError_t batch_slab(lbm_batch* b) {
+  const uint32_t* const blocks = b->blocks2 + 2 * b->nblocks2;
+  if (b->faces == FACES_WALLS)
+    hipLaunchKernelGGL((k_batch_slab<T, true>), dim3(b->nblocks_slab), dim3(256), 0, b->stream, b->dev, blocks,
+                       b->hs.cur, b->hs.flag_cur, b->hs.spar);
+  else
+    hipLaunchKernelGGL((k_batch_slab<T, false>), dim3(b->nblocks_slab), dim3(256), 0, b->stream, b->dev, blocks,
+                       b->hs.cur, b->hs.flag_cur, b->hs.spar);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t batch_step2(lbm_batch* b) {
+  const dim3 grid(b->nblocks2), block(step2_threads<T>());
+  if (b->faces == FACES_WALLS)
+    hipLaunchKernelGGL((k_batch_step2<T, FACES_WALLS>), grid, block, 0, b->stream, b->dev, b->blocks2, b->hs.cur,
+                       b->hs.flag_cur, b->hs.spar);
+  else
+    hipLaunchKernelGGL((k_batch_step2<T, FACES_BB>), grid, block, 0, b->stream, b->dev, b->blocks2, b->hs.cur,
+                       b->hs.flag_cur, b->hs.spar);
+  return hipGetLastError();
+}
+
+// Two method steps of every column (see step2.hip).
+hipError_t batch_pair(lbm_batch* b, const bubble_params* p, const bubble_soa* s, int32_t nb) {
+  for (int half = 0; half < 2; ++half) {
+    hipError_t e = batch_bubble_half(b, p, s, nb, half);
+    if (e == hipSuccess && half == 0 && nb > 0) e = b->elem == 4 ? batch_slab<float>(b) : batch_slab<double>(b);
+    if (e == hipSuccess && half == 1) e = b->elem == 4 ? batch_step2<float>(b) : batch_step2<double>(b);
+    if (e != hipSuccess) return e;
+    b->hs.flag_clean[b->hs.flag_cur ^ 1] = true;
+  }
+  b->hs.cur ^= 1;
+  if (nb > 0) b->hs.spar ^= 1;
+  b->hs.steps += 2;
+  return hipSuccess;
+}
+
+// n method steps of every column.
+hipError_t batch_steps(lbm_batch* b, const bubble_params* p, const bubble_soa* s, int32_t nb, int32_t n) {
+  for (int32_t i = 0; i < n;) {
+    const bool two = b->nblocks2 > 0 && n - i >= 2;
+    const hipError_t e = two ? batch_pair(b, p, s, nb) : batch_method_step(b, p, s, nb);
+    if (e != hipSuccess) return e;
+    i += two ? 2 : 1;
+  }
   return hipSuccess;
 }
 
@@ -293,31 +537,16 @@ constexpr uint32_t kBarrierSpinLimit = 1u << 20;
 hipError_t batch_persistent_steps(lbm_batch* b, const bubble_params* p, const bubble_soa* s,
                                   int32_t nb, int32_t n) {
   if (n <= 0) return hipSuccess;
-  const int m0 = b->flag_cur ^ 1;  // tile mask of the first step
-  if (!b->flag_clean[m0]) {
-    for (int c = 0; c < b->ncols; ++c) {
-      const hipError_t e = launch_fill(b->host[c].tiles[m0],
-                                       (size_t)b->host[c].G.tnx * b->host[c].G.tny *
-                                           div_up(b->host[c].G.nz, kTile),
-                                       b->stream);
-      if (e != hipSuccess) return e;
-    }
-  }
-  hipError_t e = launch_fill(b->barrier, 4 * sizeof(uint32_t), b->stream);
+  const int m0 = b->hs.flag_cur ^ 1;  // tile mask of the first step
+  hipError_t e = next_mask(b);
+  if (e == hipSuccess) e = launch_fill(b->barrier, 4 * sizeof(uint32_t), b->stream);
   if (e != hipSuccess) return e;
-  ManyColumns geo;
-  geo.cols = b->dev;
-  geo.bubble_col = b->bubble_col;
-  geo.flag = m0;
-  geo.jobs = b->jobs;
-  geo.job_count = b->job_count;
-  geo.job_cap = b->job_cap;
-  geo.par = b->cur;
+  const ManyColumns geo = bubble_columns(b, m0);
   PersistArgs P;
   P.cols = b->dev;
   P.item_col = b->item_col_dev;
   P.nitems = b->nitems;
-  P.cur0 = b->cur;
+  P.cur0 = b->hs.cur;
   P.flag0 = m0;
   P.flags = b->flags;
   P.nsteps = n;
@@ -328,12 +557,12 @@ hipError_t batch_persistent_steps(lbm_batch* b, const bubble_params* p, const bu
                               b->stream);
   if (e != hipSuccess) return e;
   for (int32_t i = 0; i < n; ++i) {  // the host step state the n steps leave
-    const int m = b->flag_cur ^ 1;
-    b->flag_clean[m] = false;
-    b->flag_cur = m;
-    b->cur ^= 1;
-    b->flag_clean[b->flag_cur ^ 1] = true;
-    ++b->steps;
+    const int m = b->hs.flag_cur ^ 1;
+    b->hs.flag_clean[m] = false;
+    b->hs.flag_cur = m;
+    b->hs.cur ^= 1;
+    b->hs.flag_clean[b->hs.flag_cur ^ 1] = true;
+    ++b->hs.steps;
   }
   return hipSuccess;
 }
@@ -352,7 +581,7 @@ lbm_status lbm_batch_bytes_required(const lbm_column* cols, int32_t ncols, int32
   if (!cols || ncols < 1) return LBM_EINVAL;
   if (precision != LBM_FP32_SHIFTED && precision != LBM_FP64_SHIFTED) return LBM_EINVAL;
   BatchLayout L;
-  if (!layout_batch(cols, ncols, precision == LBM_FP32_SHIFTED ? 4 : 8, L)) return LBM_EINVAL;
+  if (!layout_batch(cols, ncols, precision == LBM_FP32_SHIFTED ? 4 : 8, 0, L)) return LBM_EINVAL;
   if (pool_bytes) *pool_bytes = L.pool;
   if (scratch_bytes) *scratch_bytes = L.scratch;
   return LBM_OK;
@@ -367,7 +596,7 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
   if (flags & ~(LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL | LBM_FLAG_PLAIN_SOA)) return LBM_EINVAL;
   const size_t elem = precision == LBM_FP32_SHIFTED ? 4 : 8;
   BatchLayout L;
-  if (!layout_batch(cols, ncols, elem, L)) return LBM_EINVAL;
+  if (!layout_batch(cols, ncols, elem, flags, L)) return LBM_EINVAL;
   lbm_batch* b = new (std::nothrow) lbm_batch();
   if (!b) return LBM_EDEVICE;
   b->ncols = ncols;
@@ -390,10 +619,10 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
       lds = 0;
     b->lds_per_cu = lds > 0 ? (uint32_t)lds : 0u;
   }
-  b->cur = 0;
-  b->flag_cur = 0;
-  b->flag_clean[0] = b->flag_clean[1] = true;
-  b->steps = 0;
+  b->hs.cur = 0;
+  b->hs.flag_cur = 0;
+  b->hs.flag_clean[0] = b->hs.flag_clean[1] = true;
+  b->hs.steps = 0;
   uint8_t* P = static_cast<uint8_t*>(pool);
   uint8_t* S = static_cast<uint8_t*>(scratch);
   b->dev = reinterpret_cast<ColumnDev*>(S + L.table);
@@ -408,11 +637,15 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
   b->persistent = false;
   b->barrier = reinterpret_cast<uint32_t*>(S + L.barrier);
   b->last_grid = 0;
+  b->blocks2 = reinterpret_cast<uint32_t*>(S + L.blocks);
+  b->nblocks2 = L.nblocks2;
+  b->nblocks_slab = (uint32_t)(L.blocks2.size() / 2) - L.nblocks2;
+  b->hs.spar = 0;
   b->nred = kRedBlocks;
   b->host.resize(ncols);
   std::vector<int32_t> bcol(L.nb_total > 0 ? L.nb_total : 1, 0);
   hipError_t e = launch_fill(pool, L.pool, b->stream);
-  if (e == hipSuccess) e = launch_fill(scratch, L.scratch, b->stream);
+  if (e == hipSuccess) e = launch_fill(scratch, L.init, b->stream);
   size_t cells = 0;
   for (int c = 0; c < ncols; ++c) cells += (size_t)cols[c].nx * cols[c].ny * cols[c].nz;
   for (int c = 0; c < ncols && e == hipSuccess; ++c) {
@@ -451,6 +684,12 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
     D.tcount = reinterpret_cast<uint32_t*>(S + L.tcount[c]);
     D.tlist = reinterpret_cast<uint32_t*>(S + L.tlist[c]);
     D.item_cells = default_item_cells(k);
+    D.slab = reinterpret_cast<uint32_t*>(S + L.slab) + (size_t)c * 2 * kSlabWords;
+    if (b->nblocks2 > 0) {
+      D.tiles2 = L.tiles2[c];
+      D.slab_blocks = L.slab_blocks[c];
+      D.mid = S + L.mid[c];
+    }
     D.bubble_begin = k.bubble_begin;
     D.nb = k.nb;
     for (int i = 0; i < k.nb; ++i) bcol[k.bubble_begin + i] = c;
@@ -462,6 +701,9 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->bubble_col, bcol.data(), bcol.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess && b->nblocks2 > 0)
+    e = hipMemcpyAsync(b->blocks2, L.blocks2.data(), L.blocks2.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
+                       b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) {
     delete b;
@@ -512,11 +754,7 @@ lbm_status lbm_batch_step(lbm_batch* b, const bubble_params* p, const bubble_soa
                  !s->uly || !s->ulz || !s->state || !s->work))
     return LBM_EINVAL;
   if (b->persistent) return to_status(batch_persistent_steps(b, p, s, nb, nsteps));
-  for (int32_t i = 0; i < nsteps; ++i) {
-    const hipError_t e = batch_method_step(b, p, s, nb);
-    if (e != hipSuccess) return LBM_EDEVICE;
-  }
-  return LBM_OK;
+  return to_status(batch_steps(b, p, s, nb, nsteps));
 }
 
 lbm_status lbm_batch_set_persistent(lbm_batch* b, int32_t enable) {
@@ -544,41 +782,25 @@ lbm_status lbm_batch_run(lbm_batch* b, const bubble_params* p, const bubble_soa*
   if (st != LBM_OK) return st;
   auto enqueue = [&](int n) -> hipError_t {
     if (b->persistent) return batch_persistent_steps(b, p, s, nb, n);  // one launch
-    for (int i = 0; i < n; ++i) {
-      const hipError_t e = batch_method_step(b, p, s, nb);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return batch_steps(b, p, s, nb, n);
   };
   int32_t done = 0;
   while (nsteps - done >= graph_steps) {
-    const uint32_t mode = (b->flag_clean[0] ? 1u : 0u) | (b->flag_clean[1] ? 2u : 0u) |
-                          (b->persistent ? 4u : 0u);
-    const GraphKey key = GraphKey::of(p, s, nb, b->cur, b->flag_cur, graph_steps, mode);
-    const int cur0 = b->cur, flag0 = b->flag_cur;
-    const bool clean0[2] = {b->flag_clean[0], b->flag_clean[1]};
-    const int64_t steps0 = b->steps;
+    const uint32_t mode = (b->hs.flag_clean[0] ? 1u : 0u) | (b->hs.flag_clean[1] ? 2u : 0u) |
+                          (b->persistent ? 4u : 0u) | ((uint32_t)b->hs.spar << 3);
+    const GraphKey key = GraphKey::of(p, s, nb, b->hs.cur, b->hs.flag_cur, graph_steps, mode);
+    const BatchState pre = b->hs;
     bool captured = false;
     hipError_t e = b->graph.ensure(key, b->stream, [&]() { return enqueue(graph_steps); }, &captured);
-    // a capture only records the launches (and a failed one ran nothing): rewind the host-side
-    // step state, then replay
-    b->cur = cur0;
-    b->flag_cur = flag0;
-    b->flag_clean[0] = clean0[0];
-    b->flag_clean[1] = clean0[1];
-    b->steps = steps0;
+    // a capture only records the launches (and a failed one ran nothing): back to the state before it,
+    // then replay
+    if (captured) b->graph.post() = b->hs;
+    b->hs = pre;
     if (e != hipSuccess) return LBM_EDEVICE;
     e = b->graph.launch(b->stream);
     if (e != hipSuccess) return LBM_EDEVICE;
-    for (int i = 0; i < graph_steps; ++i) {  // advance the host state as the steps did
-      const int m = b->flag_cur ^ 1;
-      b->flag_clean[m] = false;
-      b->flag_cur = m;
-      b->cur ^= 1;
-      b->flag_clean[b->flag_cur ^ 1] = true;
-      ++b->steps;
-    }
-    (void)captured;
+    b->hs = b->graph.post();
+    b->hs.steps = pre.steps + graph_steps;
     done += graph_steps;
   }
   if (nsteps > done) return lbm_batch_step(b, p, s, nb, nsteps - done);
@@ -591,17 +813,17 @@ lbm_status lbm_batch_sums(lbm_batch* b, double* sums) {
   if (b->elem == 4) {
     if (b->general)
       hipLaunchKernelGGL((k_batch_sums<float, true>), dim3(blocks), dim3(256), 0, b->stream, b->dev,
-                         b->cur, b->partials);
+                         b->hs.cur, b->partials);
     else
       hipLaunchKernelGGL((k_batch_sums<float, false>), dim3(blocks), dim3(256), 0, b->stream, b->dev,
-                         b->cur, b->partials);
+                         b->hs.cur, b->partials);
   } else {
     if (b->general)
       hipLaunchKernelGGL((k_batch_sums<double, true>), dim3(blocks), dim3(256), 0, b->stream, b->dev,
-                         b->cur, b->partials);
+                         b->hs.cur, b->partials);
     else
       hipLaunchKernelGGL((k_batch_sums<double, false>), dim3(blocks), dim3(256), 0, b->stream, b->dev,
-                         b->cur, b->partials);
+                         b->hs.cur, b->partials);
   }
   if (hipGetLastError() != hipSuccess) return LBM_EDEVICE;
   hipLaunchKernelGGL(k_batch_sums_reduce, dim3(div_up((uint32_t)b->ncols, 64)), dim3(64), 0, b->stream,
@@ -623,24 +845,24 @@ lbm_status lbm_batch_populations(lbm_batch* b, int32_t col, void* out) {
   if (b->elem == 4) {
     if (b->general)
       hipLaunchKernelGGL((k_batch_populations<float, true>), dim3(div_up(N, 256)), dim3(256), 0,
-                         b->stream, dc, b->cur, static_cast<float*>(out));
+                         b->stream, dc, b->hs.cur, static_cast<float*>(out));
     else
       hipLaunchKernelGGL((k_batch_populations<float, false>), dim3(div_up(N, 256)), dim3(256), 0,
-                         b->stream, dc, b->cur, static_cast<float*>(out));
+                         b->stream, dc, b->hs.cur, static_cast<float*>(out));
   } else {
     if (b->general)
       hipLaunchKernelGGL((k_batch_populations<double, true>), dim3(div_up(N, 256)), dim3(256), 0,
-                         b->stream, dc, b->cur, static_cast<double*>(out));
+                         b->stream, dc, b->hs.cur, static_cast<double*>(out));
     else
       hipLaunchKernelGGL((k_batch_populations<double, false>), dim3(div_up(N, 256)), dim3(256), 0,
-                         b->stream, dc, b->cur, static_cast<double*>(out));
+                         b->stream, dc, b->hs.cur, static_cast<double*>(out));
   }
   return to_status(hipGetLastError());
 }
 
 lbm_status lbm_batch_column(lbm_batch* b, int32_t col, void** state, void** force, void** vel) {
   if (!b || col < 0 || col >= b->ncols) return LBM_EINVAL;
-  if (state) *state = b->host[col].pops[b->cur];
+  if (state) *state = b->host[col].pops[b->hs.cur];
   if (force) *force = b->host[col].F;
   if (vel) *vel = b->host[col].U;
   return LBM_OK;

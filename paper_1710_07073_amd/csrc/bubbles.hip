@@ -825,6 +825,7 @@ __device__ void interp_bubble(const Geo& geo, const BubbleArgs& A, const int b) 
 template <typename T, typename Geo, bool EXACT = false, int GATHER = 1, bool FUSE = false>
 __global__ __launch_bounds__(kBlock, FUSE ? 2 : 1) void k_interp(Geo geo, BubbleArgs A) {
   if (blockIdx.x == 0 && threadIdx.x == 0) clear_for_step(geo);
+  if (threadIdx.x == 0) geo.clear_slab(blockIdx.x);
   interp_bubble<T, Geo, EXACT, GATHER, FUSE>(geo, A, bubble_of_block(A.nb));
   if (FUSE && !geo.use_lists()) advance_traj_row(A);  // no spreading kernel follows
 }
@@ -1658,7 +1659,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_persistent(ManyColumns geo,
     const int odd = s & 1;
     ManyColumns g = geo;
     g.flag = P.flag0 ^ odd;
-    g.par = P.cur0 ^ odd;
+    g.par = P.flag0 ^ odd;
     if (A.nb > 0) {
       if (blockIdx.x == 0 && threadIdx.x == 0) clear_for_step(g);
       for (int b = blockIdx.x; b < A.nb; b += gridDim.x) {

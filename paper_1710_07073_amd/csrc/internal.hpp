@@ -150,7 +150,13 @@ struct OneColumn {
   __device__ uint32_t* tlist_of(int) const { return tlist; }
   __device__ void note_tile(int, uint32_t) const {}
   __device__ void clear_other_jobs() const {}
+  __device__ void clear_slab(int) const {}
 };
+
+// Slab: the box of rows and planes the bubbles reach in a pair of steps. Its words (uint32, zero: empty),
+// for either half of the pair: the maxima over the bubbles of kSlabBase - za, zb, kSlabBase - ya, yb.
+constexpr int kSlabWords = 8;
+constexpr uint32_t kSlabBase = 1u << 30;
 
 // One column of a batch, in device memory: geometry, relaxation rate, buffers, and its share of
 // the work items of the batched liquid step and of the bubble arrays.
@@ -170,6 +176,11 @@ struct ColumnDev {
   uint32_t* tcount;
   uint32_t* tlist;
   float rnx, rny;  // 1 / nx and 1 / ny rounded to float (cell coordinates of the batched step)
+  // two steps per launch: its tiles, middle buffer, and slab words of the two pair parities
+  Tiles2 tiles2;
+  uint32_t slab_blocks;  // workgroups of its slab's first step
+  void* mid;
+  uint32_t* slab;
   double g, sigma;  // the column's bubbles' gravity and surface tension (0: the shared value)
 };
 
@@ -185,11 +196,21 @@ struct ManyColumns {
   uint32_t* job_count;  // [2]
   uint32_t job_cap;
   int par;
+  // a half of a pair of steps: the first of its words among each column's slab words, and those of
+  // the next pair it clears (-1: none)
+  int slab_word, slab_clear;
   template <typename T>
   __device__ ColumnView<T> view(int b) const {
     const ColumnDev& c = cols[bubble_col[b]];
-    return {c.G, static_cast<const T*>(c.U), static_cast<T*>(c.F), c.tiles[flag], c.nu, nullptr, nullptr, nullptr,
-            nullptr};
+    return {c.G, static_cast<const T*>(c.U), static_cast<T*>(c.F), c.tiles[flag], c.nu, nullptr,
+            slab_word < 0 ? nullptr : c.slab + slab_word, nullptr, nullptr};
+  }
+  // by the first thread of bubble b's workgroup: the next pair's slab words, once per column
+  __device__ void clear_slab(int b) const {
+    if (slab_clear < 0) return;
+    const ColumnDev& c = cols[bubble_col[b]];
+    if (b != c.bubble_begin) return;
+    for (int i = 0; i < kSlabWords; ++i) c.slab[slab_clear + i] = 0u;
   }
   __device__ bool use_lists() const { return true; }
   // the bubble constants of bubble b: the shared ones with its column's g and sigma where set
@@ -236,8 +257,8 @@ constexpr uint32_t kRedBlocks = 1024;  // upper bound of moments reduction block
 enum : int32_t { STATUS_STENCIL_TOO_LARGE = 1, STATUS_REGION_MISS = 2, STATUS_BARRIER_TIMEOUT = 4 };
 
 // A persistent batched launch: nsteps method steps of every column in one kernel (see
-// launch_batch_persistent). Step s uses tile mask flag0 ^ (s & 1), reads population buffer
-// cur0 ^ (s & 1) and note list parity cur0 ^ (s & 1).
+// launch_batch_persistent). Step s uses tile mask (and note list parity) flag0 ^ (s & 1) and reads
+// population buffer cur0 ^ (s & 1).
 struct PersistArgs {
   const ColumnDev* cols;
   const uint32_t* item_col;
@@ -261,11 +282,6 @@ constexpr int kPairBesideMaxBubbles = 256;
 
 // Lattices from this size on overlap the bubble kernels with the liquid step by default.
 constexpr uint32_t kOverlapMinCells = 1u << 22;
-
-// Slab: the box of rows and planes the bubbles reach in a pair of steps. Its words (uint32, zero: empty),
-// for either half of the pair: the maxima over the bubbles of kSlabBase - za, zb, kSlabBase - ya, yb.
-constexpr int kSlabWords = 8;
-constexpr uint32_t kSlabBase = 1u << 30;
 
 // Lattices from these sizes on are advanced two steps per launch, alone and with bubbles. Alone, the
 // shorter chunks of a small lattice lose to their halo planes: 30 x 30 x 90 FP32 6.0 us per step

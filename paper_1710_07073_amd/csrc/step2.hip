@@ -18,124 +18,15 @@
 namespace lbm {
 namespace {
 
-
-// One step of one cell, inside a loop over cells. The strides are made opaque in every
-// iteration: hoisted out of the loop, the 38 offsets that follow from them fill the registers.
-template <typename T, bool FS>
-__device__ __forceinline__ void step_one(const gchar* src, gchar* dst, gchar* F, gchar* U,
-                                         const gchar* tiles, const Geom& G0, T omega, int flags,
-                                         uint32_t x, uint32_t y, uint32_t z, uint32_t fs) {
-  Geom G = G0;
-  asm volatile("" : "+s"(G.qs), "+s"(G.zs), "+s"(G.nx));
-  const uint32_t tile = ((z >> 3) * G.tny + (y >> 3)) * G.tnx + (x >> 3);
-  step_cell_bb<T, FS>(src, dst, F, U, tiles, tile, G, omega, flags, (int)x, (int)y, z, fs);
-}
-
-template <typename T>
-struct Step2Args {
-  const T* src;
-  const T* mid;  // step n + 1 of the slab (and a plane beside it), or null
-  T* dst;
-  T* F;
-  T* U;
-  const uint8_t* tiles;  // mask of the second step
-  uint8_t* tiles_next;   // cleared
-  const uint32_t* slab;  // slab words of the pair, or null
-  Geom G;
-  T omega;
-  Tiles2 L;
-  uint32_t ntiles;
-  int flags;
-  int dirty;  // no slab: some tile of the mask may be set
-  int bulk;   // an overlapped pair's planes outside the slab (whole tiles) and nothing else
-};
-
-// A workgroup per (tile, chunk of its planes); of a tile whose rows the slab holds, the planes outside the
-// slab in two steps and as many parts of those inside in one, so that the launch stays balanced
-// whatever the slab holds.
 template <typename T, int FACES, bool FORCE>
 __global__ __launch_bounds__(step2_threads<T>()) void k_step2(Step2Args<T> A) {
-  constexpr int NT = step2_threads<T>();
-  __shared__ Plane2<T, NT> s[2];
-  const Geom& G = A.G;
-  const uint32_t nblocks = gridDim.x;
-  const uint32_t b = xcd_remap(blockIdx.x, nblocks);
-  const uint32_t txi = b % A.L.ntx, r = b / A.L.ntx;
-  const uint32_t tyi = r % A.L.nty, ch = r / A.L.nty;
-  const Box box = slab_box(A.slab, G, A.bulk, A.L.oy);
-  const int y0 = (int)(tyi * A.L.oy), y1 = min(y0 + (int)A.L.oy, G.ny);
-  const bool in_slab = y0 < box.yb && y1 > box.ya;  // the box holds whole tiles of rows
-  const int sa = in_slab ? box.za : 0, sb = in_slab ? box.zb : 0;
-  Lattice2 D;
-  D.src = gbytes<T>(A.src);
-  D.dst = gbytes<T>(A.dst);
-  D.F = gbytes<T>(A.F);
-  D.U = gbytes<T>(A.U);
-  D.tiles = gbytes<uint8_t>(A.tiles);
-  D.u_all = A.flags & LBM_FLAG_WRITE_U_ALL;
-  if (A.bulk) {
-    D.fa = D.fb = 0;  // every flagged tile lies in the slab
-  } else if (A.slab) {
-    const Box f = slab_box(A.slab + 4, G, true, 1);  // planes of the second half's windows
-    D.fa = f.za;
-    D.fb = f.zb;
-  } else {
-    D.fa = 0;
-    D.fb = A.dirty ? G.nz : 0;
-  }
-  // chunk of the planes outside the slab, counted without it
-  const uint32_t nzb = (uint32_t)(G.nz - (sb - sa));
-  const int c0 = (int)(ch * nzb / A.L.nchunk), c1 = (int)((ch + 1) * nzb / A.L.nchunk);
-  if (c0 < min(c1, sa)) march2<T, FACES, FORCE, NT>(s, G, D, A.omega, A.L, txi, tyi, c0, min(c1, sa));
-  if (max(c0, sa) < c1)
-    march2<T, FACES, FORCE, NT>(s, G, D, A.omega, A.L, txi, tyi, max(c0, sa) + (sb - sa), c1 + (sb - sa));
-  if (A.bulk) return;
-  if constexpr (FACES != FACES_GENERAL && !FORCE) {
-    const uint32_t nzs = (uint32_t)(sb - sa);
-    const int p0 = sa + (int)(ch * nzs / A.L.nchunk), p1 = sa + (int)((ch + 1) * nzs / A.L.nchunk);
-    const int x0 = (int)(txi * A.L.ox), x1 = min(x0 + (int)A.L.ox, G.nx);
-    const uint32_t fs = FACES == FACES_WALLS ? free_slip_faces(G) : 0u;
-    const uint32_t w = (uint32_t)(x1 - x0), wh = w * (uint32_t)(y1 - y0), cells = wh * (uint32_t)(p1 - p0);
-#pragma unroll 1
-    for (uint32_t k = threadIdx.x; k < cells; k += NT) {
-      const uint32_t z = k / wh, rem = k - z * wh, y = rem / w, x = rem - y * w;
-      step_one<T, FACES == FACES_WALLS>(gbytes<T>(A.mid), D.dst, gbytes<T>(A.F), D.U, D.tiles, G, A.omega,
-                                        A.flags, (uint32_t)x0 + x, (uint32_t)y0 + y, (uint32_t)p0 + z, fs);
-    }
-  }
-  for (uint32_t k = blockIdx.x * NT + threadIdx.x; k < A.ntiles; k += nblocks * NT) A.tiles_next[k] = 0;
+  __shared__ Plane2<T, step2_threads<T>()> s[2];
+  step2_block<T, FACES, FORCE>(s, A, xcd_remap(blockIdx.x, gridDim.x));
 }
 
-// One step of a slab's cells from src into dst. SLAB_FIRST: step n of a pair, from the current state into
-// the middle buffer, with one row and plane beside the slab on every side; widened to whole force
-// tiles, so that the velocity is written in every tile the first bubble half flagged. SLAB_FIRST_WHOLE:
-// the same of an overlapped pair, whose slab is whole tiles. SLAB_SECOND: its step n + 1.
-enum : int { SLAB_FIRST = 0, SLAB_FIRST_WHOLE = 1, SLAB_SECOND = 2 };
-
 template <typename T, bool FS>
-__global__ __launch_bounds__(256) void k_slab(const T* __restrict__ src, T* __restrict__ dst,
-                                              T* __restrict__ F, T* __restrict__ U,
-                                              const uint8_t* __restrict__ tiles,
-                                              uint8_t* __restrict__ tiles_next,
-                                              const uint32_t* __restrict__ slab, Geom G, T omega,
-                                              int flags, uint32_t ntiles, uint32_t oy, int part) {
-  Box b = slab_box(slab, G, part != SLAB_FIRST, oy);
-  if (b.zb > b.za && part != SLAB_SECOND) {
-    constexpr int m = (int)kTile - 1;
-    b.za = max(0, min(b.za - 1, b.za & ~m));
-    b.ya = max(0, min(b.ya - 1, b.ya & ~m));
-    b.zb = min(G.nz, max(b.zb + 1, (b.zb + m) & ~m));
-    b.yb = min(G.ny, max(b.yb + 1, (b.yb + m) & ~m));
-  }
-  const uint32_t rows = (uint32_t)(b.yb - b.ya) * (uint32_t)G.nx, cells = rows * (uint32_t)(b.zb - b.za);
-  const uint32_t fs = FS ? free_slip_faces(G) : 0u;
-#pragma unroll 1
-  for (uint32_t k = blockIdx.x * 256 + threadIdx.x; k < cells; k += gridDim.x * 256) {
-    const uint32_t z = k / rows, rem = k - z * rows, y = rem / (uint32_t)G.nx, x = rem - y * (uint32_t)G.nx;
-    step_one<T, FS>(gbytes<T>(src), gbytes<T>(dst), gbytes<T>(F), gbytes<T>(U), gbytes<uint8_t>(tiles), G,
-                    omega, flags, x, (uint32_t)b.ya + y, (uint32_t)b.za + z, fs);
-  }
-  for (uint32_t k = blockIdx.x * 256 + threadIdx.x; k < ntiles; k += gridDim.x * 256) tiles_next[k] = 0;
+__global__ __launch_bounds__(256) void k_slab(SlabArgs<T> A) {
+  slab_block<T, FS>(A, blockIdx.x, gridDim.x);
 }
 
 // Threads a tile of ox by oy output cells takes at most.
@@ -224,11 +115,12 @@ hipError_t launch_slab_typed(lbm_ctx* c, const uint32_t* slab, int part, hipStre
   const bool second = part == SLAB_SECOND;
   const void* src = second ? c->mid : c->pops[c->hs.cur];
   void* dst = second ? c->pops[c->hs.cur ^ 1] : c->mid;
+  const SlabArgs<T> A = {static_cast<const T*>(src), static_cast<T*>(dst), static_cast<T*>(c->force),
+                         static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur], c->tiles[c->hs.flag_cur ^ 1], slab, G,
+                         (T)c->desc.omega, c->desc.flags, c->ntiles,
+                         part == SLAB_FIRST ? c->tiles2.oy : c->tiles2_beside.oy, part};
   hipLaunchKernelGGL((k_slab<T, FS>), dim3(std::min(div_up(G.N, 256), 2048u)), dim3(256),
-                     part == SLAB_FIRST_WHOLE ? 0 : step_lds(c), s, static_cast<const T*>(src),
-                     static_cast<T*>(dst), static_cast<T*>(c->force), static_cast<T*>(c->vel),
-                     c->tiles[c->hs.flag_cur], c->tiles[c->hs.flag_cur ^ 1], slab, G, (T)c->desc.omega,
-                     c->desc.flags, c->ntiles, part == SLAB_FIRST ? c->tiles2.oy : c->tiles2_beside.oy, part);
+                     part == SLAB_FIRST_WHOLE ? 0 : step_lds(c), s, A);
   return hipGetLastError();
 }
 

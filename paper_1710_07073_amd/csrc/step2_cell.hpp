@@ -407,4 +407,137 @@ __device__ void march2(Plane2<T, NT>* s, const Geom& G, const Lattice2& A, T ome
   }
 }
 
+// One step of one cell, inside a loop over cells. The strides are made opaque in every
+// iteration: hoisted out of the loop, the 38 offsets that follow from them fill the registers.
+template <typename T, bool FS>
+__device__ __forceinline__ void step_one(const gchar* src, gchar* dst, gchar* F, gchar* U,
+                                         const gchar* tiles, const Geom& G0, T omega, int flags,
+                                         uint32_t x, uint32_t y, uint32_t z, uint32_t fs) {
+  Geom G = G0;
+  asm volatile("" : "+s"(G.qs), "+s"(G.zs), "+s"(G.nx));
+  const uint32_t tile = ((z >> 3) * G.tny + (y >> 3)) * G.tnx + (x >> 3);
+  step_cell_bb<T, FS>(src, dst, F, U, tiles, tile, G, omega, flags, (int)x, (int)y, z, fs);
+}
+
+template <typename T>
+struct Step2Args {
+  const T* src;
+  const T* mid;  // step n + 1 of the slab (and a plane beside it), or null
+  T* dst;
+  T* F;
+  T* U;
+  const uint8_t* tiles;  // mask of the second step
+  uint8_t* tiles_next;   // cleared
+  const uint32_t* slab;  // slab words of the pair, or null
+  Geom G;
+  T omega;
+  Tiles2 L;
+  uint32_t ntiles;
+  int flags;
+  int dirty;  // no slab: some tile of the mask may be set
+  int bulk;   // an overlapped pair's planes outside the slab (whole tiles) and nothing else
+};
+
+// One workgroup's share of a two-step launch: block b of the lattice's tiles and chunks of planes. Of a
+// tile whose rows the slab holds, the planes outside the slab in two steps and as many parts of those
+// inside in one, so that the launch stays balanced whatever the slab holds.
+template <typename T, int FACES, bool FORCE>
+__device__ __forceinline__ void step2_block(Plane2<T, step2_threads<T>()>* s, const Step2Args<T>& A, uint32_t b) {
+  constexpr int NT = step2_threads<T>();
+  const Geom& G = A.G;
+  const uint32_t nblocks = A.L.ntx * A.L.nty * A.L.nchunk;
+  const uint32_t txi = b % A.L.ntx, r = b / A.L.ntx;
+  const uint32_t tyi = r % A.L.nty, ch = r / A.L.nty;
+  const Box box = slab_box(A.slab, G, A.bulk, A.L.oy);
+  const int y0 = (int)(tyi * A.L.oy), y1 = min(y0 + (int)A.L.oy, G.ny);
+  const bool in_slab = y0 < box.yb && y1 > box.ya;  // the box holds whole tiles of rows
+  const int sa = in_slab ? box.za : 0, sb = in_slab ? box.zb : 0;
+  Lattice2 D;
+  D.src = gbytes<T>(A.src);
+  D.dst = gbytes<T>(A.dst);
+  D.F = gbytes<T>(A.F);
+  D.U = gbytes<T>(A.U);
+  D.tiles = gbytes<uint8_t>(A.tiles);
+  D.u_all = A.flags & LBM_FLAG_WRITE_U_ALL;
+  if (A.bulk) {
+    D.fa = D.fb = 0;  // every flagged tile lies in the slab
+  } else if (A.slab) {
+    const Box f = slab_box(A.slab + 4, G, true, 1);  // planes of the second half's windows
+    D.fa = f.za;
+    D.fb = f.zb;
+  } else {
+    D.fa = 0;
+    D.fb = A.dirty ? G.nz : 0;
+  }
+  // chunk of the planes outside the slab, counted without it; the march is one call site for the parts
+  // below and above the slab (twice its code does not fit the instruction cache)
+  const uint32_t nzb = (uint32_t)(G.nz - (sb - sa));
+  const int c0 = (int)(ch * nzb / A.L.nchunk), c1 = (int)((ch + 1) * nzb / A.L.nchunk);
+#pragma unroll 1
+  for (int part = 0; part < 2; ++part) {
+    const int z0 = part == 0 ? c0 : max(c0, sa) + (sb - sa), z1 = part == 0 ? min(c1, sa) : c1 + (sb - sa);
+    if (z0 < z1) march2<T, FACES, FORCE, NT>(s, G, D, A.omega, A.L, txi, tyi, z0, z1);
+  }
+  if (A.bulk) return;
+  if constexpr (FACES != FACES_GENERAL && !FORCE) {
+    const uint32_t nzs = (uint32_t)(sb - sa);
+    const int p0 = sa + (int)(ch * nzs / A.L.nchunk), p1 = sa + (int)((ch + 1) * nzs / A.L.nchunk);
+    const int x0 = (int)(txi * A.L.ox), x1 = min(x0 + (int)A.L.ox, G.nx);
+    const uint32_t fs = FACES == FACES_WALLS ? free_slip_faces(G) : 0u;
+    const uint32_t w = (uint32_t)(x1 - x0), wh = w * (uint32_t)(y1 - y0), cells = wh * (uint32_t)(p1 - p0);
+#pragma unroll 1
+    for (uint32_t k = threadIdx.x; k < cells; k += NT) {
+      const uint32_t z = k / wh, rem = k - z * wh, y = rem / w, x = rem - y * w;
+      step_one<T, FACES == FACES_WALLS>(gbytes<T>(A.mid), D.dst, gbytes<T>(A.F), D.U, D.tiles, G, A.omega,
+                                        A.flags, (uint32_t)x0 + x, (uint32_t)y0 + y, (uint32_t)p0 + z, fs);
+    }
+  }
+  for (uint32_t k = b * NT + threadIdx.x; k < A.ntiles; k += nblocks * NT) A.tiles_next[k] = 0;
+}
+
+// One step of a slab's cells from src into dst. SLAB_FIRST: step n of a pair, from the current state into
+// the middle buffer, with one row and plane beside the slab on every side; widened to whole force
+// tiles, so that the velocity is written in every tile the first bubble half flagged. SLAB_FIRST_WHOLE:
+// the same of an overlapped pair, whose slab is whole tiles. SLAB_SECOND: its step n + 1.
+enum : int { SLAB_FIRST = 0, SLAB_FIRST_WHOLE = 1, SLAB_SECOND = 2 };
+
+template <typename T>
+struct SlabArgs {
+  const T* src;
+  T* dst;
+  T* F;
+  T* U;
+  const uint8_t* tiles;
+  uint8_t* tiles_next;
+  const uint32_t* slab;
+  Geom G;
+  T omega;
+  int flags;
+  uint32_t ntiles, oy;
+  int part;
+};
+
+// The cells in turn over the 256-thread workgroups [0, nblocks).
+template <typename T, bool FS>
+__device__ __forceinline__ void slab_block(const SlabArgs<T>& A, uint32_t block, uint32_t nblocks) {
+  const Geom& G = A.G;
+  Box b = slab_box(A.slab, G, A.part != SLAB_FIRST, A.oy);
+  if (b.zb > b.za && A.part != SLAB_SECOND) {
+    constexpr int m = (int)kTile - 1;
+    b.za = max(0, min(b.za - 1, b.za & ~m));
+    b.ya = max(0, min(b.ya - 1, b.ya & ~m));
+    b.zb = min(G.nz, max(b.zb + 1, (b.zb + m) & ~m));
+    b.yb = min(G.ny, max(b.yb + 1, (b.yb + m) & ~m));
+  }
+  const uint32_t rows = (uint32_t)(b.yb - b.ya) * (uint32_t)G.nx, cells = rows * (uint32_t)(b.zb - b.za);
+  const uint32_t fs = FS ? free_slip_faces(G) : 0u;
+#pragma unroll 1
+  for (uint32_t k = block * 256 + threadIdx.x; k < cells; k += nblocks * 256) {
+    const uint32_t z = k / rows, rem = k - z * rows, y = rem / (uint32_t)G.nx, x = rem - y * (uint32_t)G.nx;
+    step_one<T, FS>(gbytes<T>(A.src), gbytes<T>(A.dst), gbytes<T>(A.F), gbytes<T>(A.U), gbytes<uint8_t>(A.tiles),
+                    G, A.omega, A.flags, x, (uint32_t)b.ya + y, (uint32_t)b.za + z, fs);
+  }
+  for (uint32_t k = block * 256 + threadIdx.x; k < A.ntiles; k += nblocks * 256) A.tiles_next[k] = 0;
+}
+
 }  // namespace lbm
