@@ -68,7 +68,7 @@ Layout layout_of(const lbm_desc* d) {
   L.tcount = align_up(L.region_count + 2 * sizeof(uint32_t));
   L.tlist = align_up(L.tcount + (size_t)L.ntiles * 4);
   L.partials = align_up(L.tlist + (size_t)L.ntiles * lbm::kTileCap * 4);
-  L.result = align_up(L.partials + (size_t)L.nred * 4 * sizeof(double));
+  L.result = align_up(L.partials + (size_t)L.nred * 4 * sizeof(double));  // 4 sums and the status
   L.status = align_up(L.result + 4 * sizeof(double));
   L.traj_row = align_up(L.status + sizeof(int32_t));
   L.slab = align_up(L.traj_row + sizeof(uint32_t));
@@ -470,10 +470,15 @@ lbm_status moments(lbm_ctx* ctx, void* rho_out, void* u_out, double* sums_out) {
   if (!ctx) return LBM_EINVAL;
   if (lbm::launch_moments(ctx, rho_out, u_out, sums_out != nullptr) != hipSuccess) return LBM_EDEVICE;
   if (!sums_out) return LBM_OK;
-  double r[4];
-  if (hipMemcpyAsync(r, ctx->result, sizeof(r), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
+  struct {
+    double r[4];
+    int32_t status;
+  } h;
+  if (hipMemcpyAsync(&h, ctx->result, sizeof(h), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+      hipStreamSynchronize(ctx->stream) != hipSuccess)
     return LBM_EDEVICE;
-  const lbm_status st = lbm_check(ctx);  // synchronises; reports and clears a kernel error
+  const double* const r = h.r;
+  const lbm_status st = h.status != 0 ? lbm_check(ctx) : LBM_OK;  // reports and clears a kernel error
   if (st == LBM_EDEVICE) return st;
   for (int k = 0; k < 4; ++k) sums_out[k] = r[k];
   // a diverged liquid also gives its bubbles non-finite positions (a kernel error): the

@@ -4,6 +4,7 @@
 #include <utility>
 
 #include "collide.hpp"
+#include "step2_cell.hpp"
 
 namespace lbm {
 namespace {
@@ -16,19 +17,59 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Grid-stride over cells; per-block partial sums of (sum drho, sum rho u) in double precision.
-template <typename T, bool GENERAL>
+// The 19 populations arriving at a cell. With walls only (and 32-bit byte offsets) as the
+// liquid step pulls them: with the general pull k_moments was held by its address arithmetic.
+template <typename T, int FACES>
+__device__ __forceinline__ void pull_cell(T* g, const T* __restrict__ src, const Geom& G, uint32_t cell,
+                                          uint32_t x, uint32_t y, uint32_t z) {
+  const uint32_t lc = layout_cell(G, cell, z);
+  if constexpr (FACES == FACES_GENERAL) {
+    const CellNbr nb = cell_neighbours(G, (int)x, (int)y, (int)z);
+    pull_all<true>(g, src, G, lc, nb, std::make_integer_sequence<int, 19>{});
+  } else {
+    pull_bb_all<T, FACES == FACES_WALLS>(g, gbytes<T>(src), G, lc * (uint32_t)sizeof(T),
+                                         wall_bits(G, (int)x, (int)y, z),
+                                         FACES == FACES_WALLS ? free_slip_faces(G) : 0u,
+                                         std::make_integer_sequence<int, 19>{});
+  }
+}
+
+// What bounds it: the 92 bytes of a cell in FP32 (76 read, 16 written). 128 x 128 x 512 with a free-slip
+// top: 147 us (5.2 TB/s); with the general pull and each cell loaded when its turn came 229 us.
+// Grid-stride over cells; per-block partial sums of (sum drho, sum rho u) in double precision. The next
+// cell's populations are on their way while a cell's are summed; its coordinates follow by addition.
+template <typename T, int FACES>
 __global__ __launch_bounds__(kThreads) void k_moments(const T* __restrict__ src, T* __restrict__ rho,
                                                       T* __restrict__ u, double* __restrict__ partials,
                                                       Geom G) {
   __shared__ double s[4][kThreads / 64];
   double acc[4] = {0, 0, 0, 0};
   const uint32_t stride = gridDim.x * kThreads;
-  for (uint32_t cell = blockIdx.x * kThreads + threadIdx.x; cell < G.N; cell += stride) {
-    const uint32_t x = cell % G.nx, y = (cell / G.nx) % G.ny, z = cell / G.plane;
-    const CellNbr nb = cell_neighbours(G, (int)x, (int)y, (int)z);
+  const uint32_t sz = stride / G.plane, sr = stride - sz * G.plane, sy = sr / (uint32_t)G.nx,
+                 sx = sr - sy * (uint32_t)G.nx;
+  uint32_t next = blockIdx.x * kThreads + threadIdx.x;
+  uint32_t z = next / G.plane, y = (next - z * G.plane) / (uint32_t)G.nx,
+           x = next - z * G.plane - y * (uint32_t)G.nx;
+  T gn[19];
+  if (next < G.N) pull_cell<T, FACES>(gn, src, G, next, x, y, z);
+  while (next < G.N) {
+    const uint32_t cell = next;
     T g[19];
-    pull_all<GENERAL>(g, src, G, layout_cell(G, cell, z), nb, std::make_integer_sequence<int, 19>{});
+#pragma unroll
+    for (int q = 0; q < 19; ++q) g[q] = gn[q];
+    next += stride;
+    x += sx;
+    y += sy;
+    z += sz;
+    if (x >= (uint32_t)G.nx) {
+      x -= (uint32_t)G.nx;
+      ++y;
+    }
+    if (y >= (uint32_t)G.ny) {
+      y -= (uint32_t)G.ny;
+      ++z;
+    }
+    if (next < G.N) pull_cell<T, FACES>(gn, src, G, next, x, y, z);
     double drho = 0, m[3] = {0, 0, 0};
 #pragma unroll
     for (int q = 0; q < 19; ++q) {
@@ -62,9 +103,11 @@ __global__ __launch_bounds__(kThreads) void k_moments(const T* __restrict__ src,
   }
 }
 
-// One block: fixed-order sum of the partials (deterministic), result[0] = N + sum drho.
+// One block: fixed-order sum of the partials (deterministic), result[0] = N + sum drho. The kernel status
+// goes behind the sums, so that the host reads both in one copy.
 __global__ __launch_bounds__(kThreads) void k_reduce(const double* __restrict__ partials, int nblocks,
-                                                     double ncells, double* __restrict__ result) {
+                                                     double ncells, const int32_t* __restrict__ status,
+                                                     double* __restrict__ result) {
   __shared__ double s[4][kThreads / 64];
   double acc[4] = {0, 0, 0, 0};
   for (int b = threadIdx.x; b < nblocks; b += kThreads)
@@ -79,21 +122,28 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const double* __restrict__ 
     double v = 0;
     for (int w = 0; w < kThreads / 64; ++w) v += s[threadIdx.x][w];
     result[threadIdx.x] = threadIdx.x == 0 ? ncells + v : v;
+    if (threadIdx.x == 0) *reinterpret_cast<int32_t*>(result + 4) = *status;
   }
 }
 
-template <typename T, bool GENERAL>
+template <typename T, int FACES>
 __global__ __launch_bounds__(kThreads) void k_populations(const T* __restrict__ src, T* __restrict__ out,
                                                           Geom G) {
   const uint32_t cell = blockIdx.x * kThreads + threadIdx.x;
   if (cell >= G.N) return;
   const uint32_t x = cell % G.nx, y = (cell / G.nx) % G.ny, z = cell / G.plane;
-  const CellNbr nb = cell_neighbours(G, (int)x, (int)y, (int)z);
   T g[19];
-  pull_all<GENERAL>(g, src, G, layout_cell(G, cell, z), nb, std::make_integer_sequence<int, 19>{});
-  // exported in the plain (19, nz, ny, nx) order whatever the buffer layout
+  pull_cell<T, FACES>(g, src, G, cell, x, y, z);
+  // exported in the plain (19, nz, ny, nx) order whatever the buffer layout, stored as a step stores
+  if (G.stream1) {
+    keep_branch();
 #pragma unroll
-  for (int q = 0; q < 19; ++q) out[(size_t)q * G.N + cell] = g[q];
+    for (int q = 0; q < 19; ++q) __builtin_nontemporal_store(g[q], &out[(size_t)q * G.N + cell]);
+    keep_branch();
+  } else {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) out[(size_t)q * G.N + cell] = g[q];
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void k_fill(uint32_t* __restrict__ p, size_t words) {
@@ -106,41 +156,62 @@ __global__ void k_fill_bytes(uint8_t* __restrict__ p, size_t n) {
   if (i < n) p[i] = 0;
 }
 
-template <typename T, bool GENERAL>
+template <typename T, int FACES>
 hipError_t moments_typed(lbm_ctx* c, void* rho, void* u) {
   const uint32_t blocks = c->nred;
   c->bins_clean = false;
-  hipLaunchKernelGGL((k_moments<T, GENERAL>), dim3(blocks), dim3(kThreads), 0, c->stream,
+  hipLaunchKernelGGL((k_moments<T, FACES>), dim3(blocks), dim3(kThreads), 0, c->stream,
                      static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(rho),
                      static_cast<T*>(u), c->partials, c->geom);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kThreads), 0, c->stream, c->partials, (int)blocks,
-                     (double)c->geom.N, c->result);
+                     (double)c->geom.N, c->status, c->result);
   return hipGetLastError();
 }
 
-template <typename T, bool GENERAL>
+template <typename T, int FACES>
 hipError_t populations_typed(lbm_ctx* c, void* out) {
-  hipLaunchKernelGGL((k_populations<T, GENERAL>), dim3(div_up(c->geom.N, kThreads)), dim3(kThreads),
-                     0, c->stream, static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(out),
-                     c->geom);
+  // a copy of the state (128 x 128 x 512 FP32 208 us, 6.1 TB/s, in the 5 workgroups per compute unit the
+  // liquid step runs with; 223 us uncapped, 220 in 3)
+  hipLaunchKernelGGL((k_populations<T, FACES>), dim3(div_up(c->geom.N, kThreads)), dim3(kThreads),
+                     occupancy_lds(c->lds_per_cu, kDefaultStepWgsF32), c->stream,
+                     static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(out), c->geom);
   return hipGetLastError();
+}
+
+// Periodic axes and states of 4 GiB and more take the general pull.
+int pull_faces(const lbm_ctx* c) {
+  if (c->periodic || !bb_fast_ok(c->geom, c->elem)) return FACES_GENERAL;
+  return c->general ? FACES_WALLS : FACES_BB;
 }
 
 }  // namespace
 
 hipError_t launch_moments(lbm_ctx* c, void* rho, void* u, bool) {
-  if (c->elem == 4)
-    return c->general ? moments_typed<float, true>(c, rho, u) : moments_typed<float, false>(c, rho, u);
-  return c->general ? moments_typed<double, true>(c, rho, u) : moments_typed<double, false>(c, rho, u);
+  switch (pull_faces(c)) {
+    case FACES_BB:
+      return c->elem == 4 ? moments_typed<float, FACES_BB>(c, rho, u) : moments_typed<double, FACES_BB>(c, rho, u);
+    case FACES_WALLS:
+      return c->elem == 4 ? moments_typed<float, FACES_WALLS>(c, rho, u)
+                          : moments_typed<double, FACES_WALLS>(c, rho, u);
+    default:
+      return c->elem == 4 ? moments_typed<float, FACES_GENERAL>(c, rho, u)
+                          : moments_typed<double, FACES_GENERAL>(c, rho, u);
+  }
 }
 
 hipError_t launch_populations(lbm_ctx* c, void* out) {
-  if (c->elem == 4)
-    return c->general ? populations_typed<float, true>(c, out) : populations_typed<float, false>(c, out);
-  return c->general ? populations_typed<double, true>(c, out)
-                    : populations_typed<double, false>(c, out);
+  switch (pull_faces(c)) {
+    case FACES_BB:
+      return c->elem == 4 ? populations_typed<float, FACES_BB>(c, out) : populations_typed<double, FACES_BB>(c, out);
+    case FACES_WALLS:
+      return c->elem == 4 ? populations_typed<float, FACES_WALLS>(c, out)
+                          : populations_typed<double, FACES_WALLS>(c, out);
+    default:
+      return c->elem == 4 ? populations_typed<float, FACES_GENERAL>(c, out)
+                          : populations_typed<double, FACES_GENERAL>(c, out);
+  }
 }
 
 hipError_t launch_fill(void* ptr, size_t bytes, hipStream_t s) {
