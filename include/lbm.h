@@ -145,8 +145,8 @@ typedef struct lbm_ctx lbm_ctx;
 
 /* Sizes, in bytes, of one population buffer (19 x cells), of one vector field (3 x cells:
  * force or velocity) and of the scratch buffer (tile masks, reduction partials and, for lattices of
- * 2^19 cells or more with walls on every face, one more population buffer that pairs of method steps
- * pass through, see lbm_run). */
+ * 3 2^18 cells (FP32; FP64 3 2^17) or more with walls on every face, one more population buffer that
+ * pairs of method steps pass through, see lbm_run). */
 lbm_status lbm_bytes_required(const lbm_desc* desc, size_t* pop_buffer_bytes,
                               size_t* field_bytes, size_t* scratch_bytes);
 
@@ -208,8 +208,8 @@ lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells);
  * forcing (13), BGK collision (14), Guo forcing (12), (15), streaming (16). Each step reads the
  * force field where bubbles have spread force (or everywhere with LBM_FLAG_STATIC_FORCE),
  * writes the collision velocity U of eq. (13) there (or everywhere with LBM_FLAG_WRITE_U_ALL)
- * and clears the force it used. Lattices of 2^17 cells or more advance two steps per launch where
- * nsteps allows (same results bit for bit; with one cell per thread, lbm_set_launch). */
+ * and clears the force it used. Lattices of 9 2^16 cells (FP32; FP64 2^17) or more advance two steps per
+ * launch where nsteps allows (same results bit for bit; with one cell per thread, lbm_set_launch). */
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps);
 
 /* Bubble half of one step of Algorithm 1 for nb bubbles (forward coupling eq. (20) of the
@@ -270,8 +270,8 @@ lbm_status lbm_check(lbm_ctx* ctx);
  * graph_steps consecutive steps captured once into a HIP graph and replayed; the graph is kept
  * while params, soa and nb stay the same. graph_steps must be even (the step alternates two
  * population buffers), 0 runs every step eagerly. Graph capture needs a non-NULL stream. Lattices of
- * 2^19 cells or more with walls on every face (no flag but LBM_FLAG_PLAIN_SOA, one cell per thread,
- * not the exact-time coupling) take their steps in pairs: the rows and planes the bubbles reach one
+ * 3 2^18 cells (FP32; FP64 3 2^17) or more with walls on every face (no flag but LBM_FLAG_PLAIN_SOA,
+ * one cell per thread, not the exact-time coupling) take their steps in pairs: the rows and planes the bubbles reach one
  * step at a time, the others both steps in one launch; same results bit for bit. */
 lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* params, const bubble_soa* soa, int32_t nb,
                    int32_t nsteps, int32_t graph_steps);

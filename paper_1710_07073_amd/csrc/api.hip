@@ -43,8 +43,8 @@ bool desc_ok(const lbm_desc* d) {
 bool pairs_ok(const lbm_desc* d) {
   for (int f = 0; f < 6; ++f)
     if (d->bc[f] == LBM_BC_PERIODIC) return false;
-  const size_t cells = (size_t)d->nx * d->ny * d->nz;
-  return cells >= lbm::kPairMinCells && 19 * cells * (d->precision == LBM_FP32_SHIFTED ? 4 : 8) <= 0xffffffffull &&
+  const size_t cells = (size_t)d->nx * d->ny * d->nz, elem = d->precision == LBM_FP32_SHIFTED ? 4 : 8;
+  return cells >= lbm::pair_min_cells(elem) && 19 * cells * elem <= 0xffffffffull &&
          !(d->flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL));
 }
 
@@ -178,7 +178,7 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   c->traj_row = reinterpret_cast<uint32_t*>(s + L.traj_row);
   c->slab = reinterpret_cast<uint32_t*>(s + L.slab);
   c->mid = pairs_ok(desc) ? s + L.mid : nullptr;
-  if (G.N < lbm::kStep2MinCells || !lbm::bb_fast_ok(G, c->elem) ||
+  if (G.N < lbm::step2_min_cells(c->elem) || !lbm::bb_fast_ok(G, c->elem) ||
       !lbm::choose_tiles2(G, c->elem, lbm::kCus, &c->tiles2) ||
       !lbm::choose_tiles2(G, c->elem, lbm::kCusBeside, &c->tiles2_beside))
     c->tiles2 = c->tiles2_beside = lbm::Tiles2{};

@@ -284,11 +284,12 @@ constexpr int kPairBesideMaxBubbles = 256;
 constexpr uint32_t kOverlapMinCells = 1u << 22;
 
 // Lattices from these sizes on are advanced two steps per launch, alone and with bubbles. Alone, the
-// shorter chunks of a small lattice lose to their halo planes: 30 x 30 x 90 FP32 6.0 us per step
-// against 4.9 us one by one, 32 x 32 x 64 FP64 6.0 against 5.4, 48 x 48 x 144 FP32 9.1 against 12.9.
+// shorter chunks of a small lattice lose to their halo planes. Per step, one by one and in pairs:
+// 48 x 48 x 144 FP32 10.3 us and 12.0, 64 x 64 x 128 13.8 and 14.7, 60 x 60 x 180 17.9 and 16.1,
+// 64 x 64 x 192 19.7 and 15.0; 32 x 64 x 64 FP64 with periodic axes 15.1 and 12.4, 48 x 48 x 144 18.2 and 14.8.
 // With bubbles the slab launch comes on top (about 5 us per pair).
-constexpr uint32_t kStep2MinCells = 1u << 17;
-constexpr uint32_t kPairMinCells = 1u << 19;
+constexpr uint32_t step2_min_cells(size_t elem) { return elem == 4 ? 9u << 16 : 1u << 17; }
+constexpr uint32_t pair_min_cells(size_t elem) { return elem == 4 ? 3u << 18 : 3u << 17; }
 
 // A valid bubble_params.coupling: known bits and a known reaction.
 inline bool coupling_ok(int32_t c) {

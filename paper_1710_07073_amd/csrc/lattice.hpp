@@ -63,15 +63,13 @@ inline void set_layout(Geom& G, bool plain_soa) {
 //     caches and through them: 96 x 80 x 200 (117 MB) 28.8 us and 24.3, one step 45.9 and 39.1;
 //     64 x 64 x 192 16.6 and 15.1, 22.2 and 19.3; FP64 28.1 and 23.7, 40.8 and 36.2; but
 //     128 x 128 x 128 (159 MB) 34.5 and 36.0;
-//   - and a wavefront's stores cover whole 64-byte pieces, which needs rows of such: a piece two wavefronts
-//     share goes out in two parts, unless the L2 joins them. 120 x 120 x 360 110 us past the caches and 94
-//     through, 101 x 67 x 251 38.5 and 25.6 (one step 71 and 57). Not so one step in FP64 (101 x 67 x 251
-//     113 and 136).
+//   - and, with two steps per launch, whose wavefronts store rows of a tile, rows are whole 64-byte pieces:
+//     a piece two wavefronts share goes out in two parts unless the L2 joins them. 120 x 120 x 360 110 us
+//     past the caches and 94 through, 101 x 67 x 251 38.5 and 25.6; 64 x 64 x 442 30.0 and 33.4.
 // state_bytes: the populations of every lattice the launch covers.
 inline void set_stores(Geom& G, size_t elem, size_t state_bytes) {
-  const bool large = state_bytes > (size_t)128 << 20, rows = (size_t)G.nx * elem % 64 == 0;
-  G.stream1 = large && (rows || elem == 8);
-  G.stream2 = large && rows;
+  G.stream1 = state_bytes > (size_t)128 << 20;
+  G.stream2 = G.stream1 && (size_t)G.nx * elem % 64 == 0;
 }
 
 // Keeps the two branches of such a choice apart (merged, the stores lose the hint).

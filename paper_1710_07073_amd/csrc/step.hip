@@ -101,23 +101,40 @@ __device__ __forceinline__ void pull_runs(T (*g)[19], const T* __restrict__ src,
   (pull_run<Qs, GENERAL, VEC>(g, src, G, lc, nb), ...);
 }
 
-template <typename T, int VEC, bool GENERAL>
+// The cell (the first of VEC) of a thread of a step launch: workgroups of rows of one z-plane, or FLAT
+// one cell per thread in flat order. False: none. Workgroups in launch order: the dispatcher deals
+// consecutive ones to the eight XCDs in turn, so the chip streams one compact window of planes at a time
+// (measured faster on the fused step than giving each XCD a contiguous eighth of the lattice).
+template <int VEC, bool FLAT>
+__device__ __forceinline__ bool step_place(const Geom& G, uint32_t bx_blocks, uint32_t by_blocks, int& x, int& y,
+                                           uint32_t& z) {
+  const uint32_t L = blockIdx.x;
+  if constexpr (FLAT) {
+    const uint32_t cell = L * 256 + threadIdx.x;
+    z = cell / G.plane;
+    const uint32_t rem = cell - z * G.plane;
+    y = (int)(rem / (uint32_t)G.nx);
+    x = (int)(rem - (uint32_t)y * (uint32_t)G.nx);
+    return cell < G.N;
+  }
+  const uint32_t bxi = L % bx_blocks;
+  const uint32_t rest = L / bx_blocks;
+  const uint32_t byi = rest % by_blocks;
+  z = rest / by_blocks;
+  x = (int)(bxi * blockDim.x + threadIdx.x) * VEC;
+  y = (int)(byi * blockDim.y + threadIdx.y);
+  return x < G.nx && y < G.ny;
+}
+
+template <typename T, int VEC, bool GENERAL, bool FLAT>
 __global__ __launch_bounds__(256) void k_step(const T* __restrict__ src, T* __restrict__ dst,
                                               T* __restrict__ F, T* __restrict__ U,
                                               const uint8_t* __restrict__ tiles,
                                               uint8_t* __restrict__ tiles_next, Geom G, T omega,
                                               int flags, uint32_t bx_blocks, uint32_t by_blocks) {
-  // workgroups in launch order: the dispatcher deals consecutive ones to the eight XCDs in turn,
-  // so the chip streams one compact window of planes at a time (measured faster on the fused
-  // step than giving each XCD a contiguous eighth of the lattice)
-  const uint32_t L = blockIdx.x;
-  const uint32_t bxi = L % bx_blocks;
-  const uint32_t rest = L / bx_blocks;
-  const uint32_t byi = rest % by_blocks;
-  const uint32_t z = rest / by_blocks;
-  const int x0 = (int)(bxi * blockDim.x + threadIdx.x) * VEC;
-  const int y = (int)(byi * blockDim.y + threadIdx.y);
-  if (x0 >= G.nx || y >= G.ny) return;
+  int x0, y;
+  uint32_t z;
+  if (!step_place<VEC, FLAT>(G, bx_blocks, by_blocks, x0, y, z)) return;
   const uint32_t cell = ((uint32_t)z * G.ny + y) * G.nx + x0;
   const uint32_t lc = layout_cell(G, cell, z);
   T g[VEC][19];
@@ -179,7 +196,7 @@ __global__ __launch_bounds__(256) void k_step(const T* __restrict__ src, T* __re
 
 // The whole lattice (region == nullptr), or the bulk of an overlapped step: every cell whose tile
 // row is not in the region. No face periodic; FS: some face free slip.
-template <typename T, bool FS>
+template <typename T, bool FS, bool FLAT>
 __global__ __launch_bounds__(256) void k_step_bb(const T* __restrict__ src, T* __restrict__ dst,
                                                  T* __restrict__ F, T* __restrict__ U,
                                                  const uint8_t* __restrict__ tiles,
@@ -187,17 +204,9 @@ __global__ __launch_bounds__(256) void k_step_bb(const T* __restrict__ src, T* _
                                                  const uint32_t* __restrict__ region, Geom G,
                                                  T omega, int flags, uint32_t bx_blocks,
                                                  uint32_t by_blocks) {
-  // workgroups in launch order: the dispatcher deals consecutive ones to the eight XCDs in turn,
-  // so the chip streams one compact window of planes at a time (measured faster on the fused
-  // step than giving each XCD a contiguous eighth of the lattice)
-  const uint32_t L = blockIdx.x;
-  const uint32_t bxi = L % bx_blocks;
-  const uint32_t rest = L / bx_blocks;
-  const uint32_t byi = rest % by_blocks;
-  const uint32_t z = rest / by_blocks;
-  const int x = (int)(bxi * blockDim.x + threadIdx.x);
-  const int y = (int)(byi * blockDim.y + threadIdx.y);
-  if (x >= G.nx || y >= G.ny) return;
+  int x, y;
+  uint32_t z;
+  if (!step_place<1, FLAT>(G, bx_blocks, by_blocks, x, y, z)) return;
   const uint32_t tile = ((z >> 3) * G.tny + ((uint32_t)y >> 3)) * G.tnx + ((uint32_t)x >> 3);
   if (region && region[(z >> 3) * G.tny + ((uint32_t)y >> 3)]) return;  // the region launch's
   step_cell_bb<T, FS>(gbytes<T>(src), gbytes<T>(dst), gbytes<T>(F), gbytes<T>(U),
@@ -243,26 +252,53 @@ __global__ __launch_bounds__(256) void k_region_bb(const T* __restrict__ src, T*
   }
 }
 
+// A thread per cell in flat order, instead of workgroups of rows, where the rows' last workgroups would leave
+// lanes idle (FP64 runs fewer wavefronts and bears a tenth idle). Per step: 101 x 67 x 251 FP32 57.0 us in
+// rows of 64 threads, 44.4 flat; 120 x 120 x 360 192 and 134; 200 x 50 x 600 254 and 152; 70 x 30 x 200 19.1
+// and 12.5; FP64 101 x 67 x 251 110 and 92, 120 x 120 x 360 282 and 303. Not for small lattices, which need
+// every workgroup: 30 x 30 x 90 FP32 5.4 us and 5.9.
+constexpr uint32_t kFlatMinCells = 1u << 17;
+
+bool flat_step(const lbm_ctx* c) {
+  const uint32_t nx = (uint32_t)c->geom.nx, bx = c->step_bx;
+  return c->step_vec == 1 && c->geom.N >= kFlatMinCells && nx % bx != 0 &&
+         (c->elem == 4 || 10 * nx < 9 * div_up(nx, bx) * bx);
+}
+
+// The step of every cell (region null) or of those outside the region, with the wall fast path.
+template <typename T, bool FS>
+hipError_t launch_bb(lbm_ctx* c, const uint32_t* region) {
+  const Geom& G = c->geom;
+  const uint32_t bx = c->step_bx, by = 256 / bx;
+  const uint32_t nbx = div_up(G.nx, bx), nby = div_up(G.ny, by);
+  auto go = [&](auto kernel, uint32_t nblocks, dim3 threads) {
+    hipLaunchKernelGGL(kernel, dim3(nblocks), threads, step_lds(c), c->stream,
+                       static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.cur ^ 1]),
+                       static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
+                       c->tiles[c->hs.flag_cur ^ 1], region, G, (T)c->desc.omega, c->desc.flags, nbx, nby);
+    return hipGetLastError();
+  };
+  if (flat_step(c)) return go(k_step_bb<T, FS, true>, div_up(G.N, 256), dim3(256));
+  return go(k_step_bb<T, FS, false>, nbx * nby * (uint32_t)G.nz, dim3(bx, by));
+}
+
 template <typename T, int VEC, bool GENERAL>
 hipError_t launch_typed(lbm_ctx* c, uint32_t bx) {
   const Geom& G = c->geom;
+  // walls only: GENERAL then means some face is free slip
+  if (VEC == 1 && !c->periodic && bb_fast_ok(G, sizeof(T))) return launch_bb<T, GENERAL>(c, nullptr);
   const uint32_t by = 256 / bx;
   const uint32_t nbx = div_up(G.nx / VEC, bx), nby = div_up(G.ny, by);
-  const uint32_t nblocks = nbx * nby * (uint32_t)G.nz;
-  const T* src = static_cast<const T*>(c->pops[c->hs.cur]);
-  T* dst = static_cast<T*>(c->pops[c->hs.cur ^ 1]);
-  if (VEC == 1 && !c->periodic && bb_fast_ok(G, sizeof(T))) {
-    // walls only: GENERAL then means some face is free slip
-    hipLaunchKernelGGL((k_step_bb<T, GENERAL>), dim3(nblocks), dim3(bx, by), step_lds(c), c->stream, src, dst,
+  auto go = [&](auto kernel, uint32_t nblocks, dim3 threads) {
+    hipLaunchKernelGGL(kernel, dim3(nblocks), threads, step_lds(c), c->stream,
+                       static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.cur ^ 1]),
                        static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
-                       c->tiles[c->hs.flag_cur ^ 1], nullptr, G, (T)c->desc.omega, c->desc.flags,
-                       nbx, nby);
+                       c->tiles[c->hs.flag_cur ^ 1], G, (T)c->desc.omega, c->desc.flags, nbx, nby);
     return hipGetLastError();
-  }
-  hipLaunchKernelGGL((k_step<T, VEC, GENERAL>), dim3(nblocks), dim3(bx, by), step_lds(c), c->stream, src, dst,
-                     static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
-                     c->tiles[c->hs.flag_cur ^ 1], G, (T)c->desc.omega, c->desc.flags, nbx, nby);
-  return hipGetLastError();
+  };
+  if constexpr (VEC == 1)
+    if (flat_step(c)) return go(k_step<T, 1, GENERAL, true>, div_up(G.N, 256), dim3(256));
+  return go(k_step<T, VEC, GENERAL, false>, nbx * nby * (uint32_t)G.nz, dim3(bx, by));
 }
 
 template <typename T, bool GENERAL>
@@ -272,20 +308,6 @@ hipError_t launch_vec(lbm_ctx* c) {
     case 2: return launch_typed<T, 2, GENERAL>(c, c->step_bx);
     default: return launch_typed<T, 1, GENERAL>(c, c->step_bx);
   }
-}
-
-template <typename T, bool FS>
-hipError_t launch_bulk_typed(lbm_ctx* c) {
-  const Geom& G = c->geom;
-  const uint32_t bx = c->step_bx, by = 256 / bx;
-  const uint32_t nbx = div_up(G.nx, bx), nby = div_up(G.ny, by);
-  const uint32_t nblocks = nbx * nby * (uint32_t)G.nz;
-  hipLaunchKernelGGL((k_step_bb<T, FS>), dim3(nblocks), dim3(bx, by), step_lds(c), c->stream,
-                     static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.cur ^ 1]),
-                     static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
-                     c->tiles[c->hs.flag_cur ^ 1], c->region[c->hs.rpar], G, (T)c->desc.omega,
-                     c->desc.flags, nbx, nby);
-  return hipGetLastError();
 }
 
 template <typename T, bool FS>
@@ -316,8 +338,8 @@ bool can_overlap(const lbm_ctx* c) {
 hipError_t launch_bulk(lbm_ctx* c) {
   return timed(c, c->stream, [&] {
     if (c->elem == 4)
-      return c->general ? launch_bulk_typed<float, true>(c) : launch_bulk_typed<float, false>(c);
-    return c->general ? launch_bulk_typed<double, true>(c) : launch_bulk_typed<double, false>(c);
+      return c->general ? launch_bb<float, true>(c, c->region[c->hs.rpar]) : launch_bb<float, false>(c, c->region[c->hs.rpar]);
+    return c->general ? launch_bb<double, true>(c, c->region[c->hs.rpar]) : launch_bb<double, false>(c, c->region[c->hs.rpar]);
   });
 }
 

@@ -61,8 +61,10 @@ def _same(a, b):
 def test_liquid_pairs_equal_single_steps(bc, precision):
     """Liquid alone: even and odd step counts, every face kind, rows that fill a workgroup, that
     leave threads idle, that are cut in pieces with and without a remainder; thin lattices."""
-    for shape in [(128, 64, 17), (37, 61, 60), (300, 45, 10), (1100, 40, 3), (31, 2200, 2),
-                  (129, 33, 40)]:
+    # FP64 takes pairs from 2^17 cells on, FP32 from 9 2^16 on
+    for shape in ([(128, 64, 17), (37, 61, 60), (300, 45, 10), (1100, 40, 3), (31, 2200, 2), (129, 33, 40)]
+                  if precision == "f64" else
+                  [(128, 64, 73), (37, 61, 263), (300, 45, 44), (1100, 40, 14), (31, 2200, 9), (129, 33, 139)]):
         a, b = _sim(shape, precision, bc), _sim(shape, precision, bc)
         for _ in range(5):
             a.liquid_steps(1)
@@ -77,7 +79,7 @@ def test_liquid_pairs_equal_single_steps(bc, precision):
                                    L.LBM_FLAG_WRITE_U_ALL | L.LBM_FLAG_PLAIN_SOA])
 def test_liquid_pairs_with_flags(flags, bc, precision):
     """A static force field, the velocity written everywhere, the plain layout."""
-    a, b = (_sim((96, 71, 33), precision, bc, flags) for _ in range(2))
+    a, b = (_sim((96, 71, 33 if precision == "f64" else 88), precision, bc, flags) for _ in range(2))
     for _ in range(4):
         a.liquid_steps(1)
     b.liquid_steps(4)
@@ -98,7 +100,7 @@ def _bubbles(shape, nb, d, seed, z):
 def test_method_step_pairs_equal_single_steps(nb, d, z, bc, precision):
     """With bubbles, through lbm_run eagerly and in graphs (4 and 10 steps), then liquid alone over the
     flagged tiles the last bubble half left."""
-    shape = (96, 80, 70)
+    shape = (96, 80, 70 if precision == "f64" else 104)  # 3 2^17 cells and 3 2^18
     pos, dd, _ = _bubbles(shape, nb, d, 3, z)
     for steps, graph in ((7, 0), (12, 4), (21, 10)):
         stream = torch.cuda.Stream()
@@ -127,7 +129,7 @@ def test_method_step_pairs_equal_single_steps(nb, d, z, bc, precision):
 def test_overlapped_pairs_equal_single_steps(nb, d, z, bc, precision):
     """The same with the bubble kernels and the slab's first step beside the rest of the lattice, single
     overlapped steps in between (odd counts, calls of one step) and bubbles moved from the host."""
-    shape = (96, 80, 70)
+    shape = (96, 80, 70 if precision == "f64" else 104)  # 3 2^17 cells and 3 2^18
     pos, dd, _ = _bubbles(shape, nb, d, 3, z)
     for steps, graph in ((8, 0), (12, 4), (31, 10)):
         stream = torch.cuda.Stream()
@@ -153,7 +155,7 @@ def test_overlapped_pairs_equal_single_steps(nb, d, z, bc, precision):
 
 def test_overlapped_pair_reports_a_bubble_beyond_its_slab():
     """A bubble thrown further than the slab's margin is reported, as by an overlapped step."""
-    sim = _sim((96, 80, 70), "f32", WALLS)
+    sim = _sim((96, 80, 104), "f32", WALLS)
     sim.add_bubbles([[40.0], [40.0], [20.0]], [2.0], S.bubble_params(g=1e-4, sigma=1e-3),
                     vel=np.array([[0.0], [0.0], [24.0]]))
     L.lbm_set_overlap(sim.ctx, True)
@@ -168,7 +170,7 @@ def test_overlapped_pair_reports_a_bubble_beyond_its_slab():
 @pytest.mark.parametrize("nb", [1, 5, 300])
 def test_pairs_follow_fast_bubbles(nb, speed):
     """Bubbles thrown along z, several cells in one step: the planes of a pair follow them."""
-    shape = (96, 80, 70)
+    shape = (96, 80, 104)
     pos, dd, v = _bubbles(shape, nb, 2.0, 5, (0.2, 0.8))
     sims = []
     for paired in (False, True):
