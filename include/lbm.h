@@ -362,6 +362,12 @@ lbm_status lbm_adjoint_liquid(lbm_ctx* ctx, const void* state, const void* force
  * which reads the mask and clears it for a later step. */
 lbm_status lbm_step_tiles(lbm_ctx* ctx, uint8_t* tiles, int64_t* ntiles);
 
+/* The mask (as lbm_step_tiles) and, into force (3 x N, lattice type), the force field: what
+ * lbm_adjoint_liquid_tiles() reads of a step beside its state, in one launch. Where every face is
+ * bounce-back that is the force of the flagged tiles, and force keeps its values elsewhere. Not with
+ * LBM_FLAG_STATIC_FORCE. */
+lbm_status lbm_step_inputs(lbm_ctx* ctx, uint8_t* tiles, void* force);
+
 /* lbm_adjoint_liquid() with the step's tile mask from lbm_step_tiles() (NULL: every tile). Outside
  * the flagged tiles the step's force and the velocity adjoint lam_u are zero (the step neither
  * forced nor wrote the velocity there, and lbm_adjoint_bubbles() scatters only into the velocity

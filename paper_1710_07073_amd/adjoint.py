@@ -146,9 +146,10 @@ class TrajectoryProblem:
                 # the bubble update fills the step record itself, sub-step velocities included
                 L.lbm_record_next_bubble_half(sim.ctx, _p(rec[i]))
                 L.bubbles_step(sim.ctx, sim.params, bub.soa, nb)
-                Fk[i].copy_(sim.force)
                 if Tk is not None:
-                    L.lbm_step_tiles(sim.ctx, _p(Tk[i]))
+                    L.lbm_step_inputs(sim.ctx, _p(Tk[i]), _p(Fk[i]))
+                else:
+                    Fk[i].copy_(sim.force)
                 L.lbm_bind_buffers(sim.ctx, None, None, _p(Up[i + 1]))
                 L.lbm_step(sim.ctx, 1)
             for i in reversed(range(n)):

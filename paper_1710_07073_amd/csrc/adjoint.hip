@@ -15,6 +15,7 @@
 #include "adjoint_math.hpp"
 #include "collide.hpp"
 #include "step_cell.hpp"
+#include "wave.hpp"
 
 namespace lbm {
 namespace {
@@ -24,22 +25,6 @@ constexpr int kBW = kB / 64;
 static_assert(kRecordMaxSub == kMaxSub, "the record holds every sub-step the adjoint allows");
 // adjoint bubble state (doubles)
 constexpr int A_X = 0, A_UB = 3, A_ULP = 6, A_SIZE = LBM_BUBBLE_ADJ;
-
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-__device__ __forceinline__ double bsum(double v, double* s_red) {
-  v = wsum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int w = 0; w < kBW; ++w) t += s_red[w];
-  return t;
-}
 
 __device__ __forceinline__ int wrapi(int i, int n) {
   i %= n;
@@ -83,7 +68,7 @@ __global__ __launch_bounds__(256) void k_adj_liquid(const T* __restrict__ h, con
     lam_u[G.N + cell] = T(0);
     lam_u[2 * (size_t)G.N + cell] = T(0);
   }
-  dom = wsum(dom);
+  dom = wave_sum(dom);
   if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = dom;
   __syncthreads();
   if (threadIdx.x == 0) atomicAdd(&grad[0], s_red[0] + s_red[1] + s_red[2] + s_red[3]);
@@ -158,7 +143,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 1) void k_adj_liquid_bb(c
       *at_bytes(lam_u, c4 + 2 * n4) = T(0);
     }
   }
-  dom = wsum(dom);
+  dom = wave_sum(dom);
   if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = dom;
   __syncthreads();
   if (threadIdx.x == 0)
@@ -173,7 +158,7 @@ __global__ __launch_bounds__(64) void k_bins(double* __restrict__ bins, uint32_t
     v = bins[threadIdx.x];
     bins[threadIdx.x] = 0.0;
   }
-  v = wsum(v);
+  v = wave_sum(v);
   if (threadIdx.x == 0) grad[0] += v;
 }
 
@@ -209,7 +194,7 @@ __device__ bool wave_weights_dx(const Geom& G, const double* xb, double n, int l
   entry(i0, w0, d0);
   entry(i1, w1, d1);
   if (!per) {  // clipped at a wall: renormalise, d(w/S) = (dw - (w/S) dS) / S
-    const double sum = wsum(w0 + w1), dsum = wsum(d0 + d1);
+    const double sum = wave_sum(w0 + w1), dsum = wave_sum(d0 + d1);
     if (sum > 0.0) {
       w0 /= sum;
       w1 /= sum;
@@ -251,10 +236,10 @@ __device__ bool wave_weights_dx(const Geom& G, const double* xb, double n, int l
   return true;
 }
 
-// The six sums of the gather over the workgroup behind one barrier (the order of bsum).
+// The six sums of the gather over the workgroup behind one barrier (in the order of the wavefronts).
 __device__ __forceinline__ void bsum6(double v[6], double (*s_red6)[kBW]) {
 #pragma unroll
-  for (int m = 0; m < 6; ++m) v[m] = wsum(v[m]);
+  for (int m = 0; m < 6; ++m) v[m] = wave_sum(v[m]);
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
     for (int m = 0; m < 6; ++m) s_red6[m][threadIdx.x >> 6] = v[m];
@@ -295,14 +280,16 @@ struct WindowWalk {
 // The bubble half of the adjoint for one bubble per workgroup:
 //   wavefronts 0-2   the weights of axis 0, 1, 2 (with their derivatives), side by side with
 //   wavefront 3      the sub-step velocities and clamp flags: from the record when the forward
-//                    update wrote them, else the forward sub-steps again (one lane);
+//                    update wrote them, else the forward sub-steps again (one lane); then the
+//                    n_sub + 1 force Jacobians at those velocities, a lane each;
 //   all              the gather dL/dpsi = sum_j W_j dL/dF(j) and the position term of the spreading
-//                    weights, while lanes of wavefront 3 first evaluate the n_sub + 1 force
-//                    Jacobians at the recorded velocities;
+//                    weights;
 //   lane 0           the reverse sweep of the sub-steps (ode_adjoint_sweep), while every thread
 //                    loads the velocities of its first scatter cells;
 //   all              the scatter, transpose of the interpolation: dL/dU(j) += W_j dL/du_l + curl
 //                    weights . dL/dw_l (atomic adds), and the position term of the interpolation.
+// What bounds it is the latency of that chain: 64 x 64 x 192 with 4 bubbles of d = 3, 19.1 us (21.8 us with
+// the Jacobians after the weights and sums through LDS permutes).
 template <typename T>
 __global__ __launch_bounds__(kB) void k_adj_bubble(const T* __restrict__ lam_f,
                                                    const T* __restrict__ U, T* __restrict__ lam_u,
@@ -348,25 +335,33 @@ __global__ __launch_bounds__(kB) void k_adj_bubble(const T* __restrict__ lam_f,
     else
       ok = wave_weights_dx<2>(G, xb, n, lane, w, dw, wx, dwx, win);
     if (lane == 0) s_bad[wave] = ok ? 0 : 1;
-  } else if (r[R_SUB] != 0.0) {
-    // sub-step velocities and clamp flags recorded by the forward update
-    if (lane <= P.n_sub)
-      for (int a = 0; a < 3; ++a) s_ubs[lane][a] = r[R_UBS + 3 * lane + a];
-    if (lane < P.n_sub)
+  } else {
+    if (r[R_SUB] != 0.0) {
+      // sub-step velocities and clamp flags recorded by the forward update
+      if (lane <= P.n_sub)
+        for (int a = 0; a < 3; ++a) s_ubs[lane][a] = r[R_UBS + 3 * lane + a];
+      if (lane < P.n_sub)
+        for (int a = 0; a < 3; ++a) {
+          const int bit = 3 * lane + a;
+          s_clamped[lane][a] = (unsigned char)(((uint32_t)r[R_CLAMP + bit / 32] >> (bit % 32)) & 1u);
+        }
+    } else if (lane == 0) {
+      OdeBounds Bd;
+      const int ext[3] = {G.nx, G.ny, G.nz};
       for (int a = 0; a < 3; ++a) {
-        const int bit = 3 * lane + a;
-        s_clamped[lane][a] = (unsigned char)(((uint32_t)r[R_CLAMP + bit / 32] >> (bit % 32)) & 1u);
+        Bd.hi[a] = ext[a] - 1.0;
+        Bd.len[a] = G.bc[2 * a] == BC_PER ? (double)ext[a] : 0.0;
       }
-  } else if (lane == 0) {
-    OdeBounds Bd;
-    const int ext[3] = {G.nx, G.ny, G.nz};
-    for (int a = 0; a < 3; ++a) {
-      Bd.hi[a] = ext[a] - 1.0;
-      Bd.len[a] = G.bc[2 * a] == BC_PER ? (double)ext[a] : 0.0;
+      Bd.top = G.bc[4] != BC_PER;
+      OdeOut o;
+      ode_forward(P, nu, r[R_D], r + R_X, r + R_UB, ul, r + R_WL, dul, Bd, o, s_ubs, s_clamped);
     }
-    Bd.top = G.bc[4] != BC_PER;
-    OdeOut o;
-    ode_forward(P, nu, r[R_D], r + R_X, r + R_UB, ul, r + R_WL, dul, Bd, o, s_ubs, s_clamped);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // force Jacobians at the sub-step velocities, a lane each
+    if (lane <= P.n_sub) {
+      const ForceConst fc = force_const(P, nu, r[R_D]);
+      force_jac(P, fc, nu, r[R_D], s_ubs[lane], ul, r + R_WL, s_jac[lane]);
+    }
   }
   __syncthreads();
   if (s_bad[0] | s_bad[1] | s_bad[2]) return;  // the forward step flagged this bubble's window
@@ -378,11 +373,6 @@ __global__ __launch_bounds__(kB) void k_adj_bubble(const T* __restrict__ lam_f,
   };
   constexpr int kBatch = 8;  // cells per thread whose loads are in flight together
 
-  // force Jacobians at the sub-step velocities (lanes of wavefront 3), then the gather
-  if (wave == 3 && lane <= P.n_sub) {
-    const ForceConst fc = force_const(P, nu, r[R_D]);
-    force_jac(P, fc, nu, r[R_D], s_ubs[lane], ul, r + R_WL, s_jac[lane]);
-  }
   double acc[6] = {0, 0, 0, 0, 0, 0};
   {
     const double psi[3] = {r[R_PSI], r[R_PSI + 1], r[R_PSI + 2]};
@@ -552,6 +542,27 @@ __global__ __launch_bounds__(64) void k_record(bubble_soa S, int nb, int stage, 
   }
 }
 
+// What a step's adjoint reads of its inputs beside the state: the tile mask and the force in its flagged
+// tiles (whole: in all of them), a workgroup per tile. (64 x 64 x 192, 4 bubbles: one launch of 3 us in place of two copies of
+// 4 us each, the force field's whole.)
+template <typename T>
+__global__ __launch_bounds__(256) void k_step_inputs(const uint8_t* __restrict__ tiles,
+                                                     uint8_t* __restrict__ tiles_out, const T* __restrict__ F,
+                                                     T* __restrict__ out, Geom G, bool whole) {
+  const uint32_t t = blockIdx.x;
+  const uint8_t flag = tiles[t];
+  if (threadIdx.x == 0) tiles_out[t] = flag;
+  if (!flag && !whole) return;
+  const uint32_t tx = t % (uint32_t)G.tnx, r = t / (uint32_t)G.tnx;
+  const uint32_t ty = r % (uint32_t)G.tny, tz = r / (uint32_t)G.tny;
+  const uint32_t x = tx * kTile + (threadIdx.x & 7u), y = ty * kTile + ((threadIdx.x >> 3) & 7u);
+  if (x >= (uint32_t)G.nx || y >= (uint32_t)G.ny) return;
+  for (uint32_t z = tz * kTile + (threadIdx.x >> 6); z < min((tz + 1) * kTile, (uint32_t)G.nz); z += 4) {
+    const size_t c = (size_t)z * G.plane + y * (uint32_t)G.nx + x;
+    for (int m = 0; m < 3; ++m) out[m * (size_t)G.N + c] = F[m * (size_t)G.N + c];
+  }
+}
+
 // Records the armed timing events (lbm_time_next_adjoint_liquid) around one launch, then disarms.
 template <typename F>
 hipError_t timed_adjoint(lbm_ctx* c, F&& launch) {
@@ -635,6 +646,19 @@ lbm_status lbm_adjoint_liquid_tiles(lbm_ctx* ctx, const void* state, const void*
             ? liquid_typed<double, true>(ctx, state, force, lam_next, lam_prev, lam_u, lam_f, tiles, grad)
             : liquid_typed<double, false>(ctx, state, force, lam_next, lam_prev, lam_u, lam_f, tiles, grad);
   return e == hipSuccess ? LBM_OK : LBM_EDEVICE;
+}
+
+lbm_status lbm_step_inputs(lbm_ctx* ctx, uint8_t* tiles, void* force) {
+  if (!ctx || !tiles || !force || (ctx->desc.flags & LBM_FLAG_STATIC_FORCE)) return LBM_EINVAL;
+  const uint8_t* const mask = ctx->tiles[ctx->hs.flag_cur];
+  const bool whole = ctx->general || !bb_fast_ok(ctx->geom, ctx->elem);  // k_adj_liquid reads every cell's
+  if (ctx->elem == 4)
+    hipLaunchKernelGGL((k_step_inputs<float>), dim3(ctx->ntiles), dim3(256), 0, ctx->stream, mask, tiles,
+                       static_cast<const float*>(ctx->force), static_cast<float*>(force), ctx->geom, whole);
+  else
+    hipLaunchKernelGGL((k_step_inputs<double>), dim3(ctx->ntiles), dim3(256), 0, ctx->stream, mask, tiles,
+                       static_cast<const double*>(ctx->force), static_cast<double*>(force), ctx->geom, whole);
+  return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
 lbm_status lbm_adjoint_liquid(lbm_ctx* ctx, const void* state, const void* force,

@@ -462,9 +462,10 @@ LBM_HD void ode_adjoint_sweep(const bubble_params& P, double d, const unsigned c
   const double inv_meff = 1.0 / (P.rho_b * V + P.c_a * P.rho_l * V);
   const double va = (1.0 + P.c_a) * P.rho_l * V;
   const double s = inv_meff / P.n_sub;
-  double lx[3], lub[3];
+  double lx[3], lxn[3], lub[3];
   for (int a = 0; a < 3; ++a) {
     lx[a] = lx_new[a];
+    lxn[a] = lx_new[a] / P.n_sub;  // lx changes to 0 and to nothing else
     lub[a] = lub_new[a];
     g.ul[a] = g.wl[a] = g.dul[a] = 0.0;
   }
@@ -493,9 +494,9 @@ LBM_HD void ode_adjoint_sweep(const bubble_params& P, double d, const unsigned c
     for (int a = 0; a < 3; ++a) {
       if (clamped[k][a]) {
         lup[a] = 0.0;
-        lx[a] = 0.0;
+        lx[a] = lxn[a] = 0.0;
       } else {
-        lup[a] = lub[a] + lx[a] / P.n_sub;
+        lup[a] = lub[a] + lxn[a];
       }
     }
     // ub' = ub_k + dt/m_eff (F(ub_k) + va dul + fb e_z)

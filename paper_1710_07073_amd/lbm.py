@@ -41,7 +41,7 @@ EXPORTS = ("lbm_bytes_required", "lbm_init", "lbm_set_stream", "lbm_set_launch",
            "lbm_batch_column",
            "lbm_batch_check", "lbm_batch_destroy",
            "lbm_checkpoint", "lbm_restore",
-           "lbm_adjoint_liquid", "lbm_adjoint_liquid_tiles", "lbm_step_tiles",
+           "lbm_adjoint_liquid", "lbm_adjoint_liquid_tiles", "lbm_step_tiles", "lbm_step_inputs",
            "lbm_adjoint_bubbles", "lbm_bubble_record",
            "lbm_record_next_bubble_half", "lbm_record_positions", "lbm_bind_buffers",
            "lbm_host_collide",
@@ -140,6 +140,7 @@ def lib():
         L.lbm_adjoint_liquid.argtypes = [P, P, P, P, P, P, P, P]
         L.lbm_adjoint_liquid_tiles.argtypes = [P, P, P, P, P, P, P, P, P]
         L.lbm_step_tiles.argtypes = [P, P, ct.POINTER(ct.c_int64)]
+        L.lbm_step_inputs.argtypes = [P, P, P]
         L.lbm_checkpoint.argtypes = [P, P, P]
         L.lbm_restore.argtypes = [P, P, P]
         L.lbm_adjoint_bubbles.argtypes = [P, ct.POINTER(BubbleParams), P, P, P, P, P, P, ct.c_int32, P]
@@ -410,6 +411,10 @@ def lbm_checkpoint(ctx, state_out, vel_out):
 
 def lbm_restore(ctx, state, vel):
     _ok(lib().lbm_restore(ctx, state, vel), "lbm_restore")
+
+
+def lbm_step_inputs(ctx, tiles, force):
+    _ok(lib().lbm_step_inputs(ctx, tiles, force), "lbm_step_inputs")
 
 
 def lbm_step_tiles(ctx, tiles=None):
