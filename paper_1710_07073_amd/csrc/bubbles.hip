@@ -1226,20 +1226,37 @@ struct GatherLane {
   double wx, wy, wz, psi;
 };
 
-__device__ __forceinline__ GatherLane gather_lane(const Geom& G, const BubbleArgs& A, uint32_t b,
-                                                  bool valid, int i, const int org[3],
-                                                  const bool per[3]) {
-  GatherLane s = {0.0, 0.0, 0.0, 0.0};
+// What it reads first of the bubble, and its weights from there.
+struct GatherBubble {
+  double x0[3], d, psi;
+};
+__device__ __forceinline__ GatherBubble gather_bubble(const BubbleArgs& A, uint32_t b, bool valid, int i) {
+  GatherBubble p = {{0.0, 0.0, 0.0}, 0.0, 0.0};
+  if (!valid) return p;
+  const double* work = A.S.work + (size_t)b * kWork;
+  for (int a = 0; a < 3; ++a) p.x0[a] = work[W_X0 + a];
+  p.psi = work[W_PSI + i % 3];
+  p.d = A.S.d[b];
+  return p;
+}
+__device__ __forceinline__ GatherLane gather_weights(const Geom& G, const BubbleArgs& A, const GatherBubble& p,
+                                                     uint32_t b, bool valid, int i, const int org[3],
+                                                     const bool per[3]) {
+  GatherLane s = {0.0, 0.0, 0.0, p.psi};
   if (!valid) return s;
   const double* work = A.S.work + (size_t)b * kWork;
-  const double x0[3] = {work[W_X0], work[W_X0 + 1], work[W_X0 + 2]};
-  s.psi = work[W_PSI + i % 3];
   Axis win[3];
-  windows(G, x0, A.P.kernel_factor * A.S.d[b], win);  // valid: the bubble was listed
+  windows(G, p.x0, A.P.kernel_factor * p.d, win);  // valid: the bubble was listed
   s.wx = axis_weight_at(win[0], work + W_WGT, org[0] + i, G.nx, per[0]);
   s.wy = axis_weight_at(win[1], work + W_WGT + kSpan, org[1] + i, G.ny, per[1]);
   s.wz = axis_weight_at(win[2], work + W_WGT + 2 * kSpan, org[2] + i, G.nz, per[2]);
   return s;
+}
+
+__device__ __forceinline__ GatherLane gather_lane(const Geom& G, const BubbleArgs& A, uint32_t b,
+                                                  bool valid, int i, const int org[3],
+                                                  const bool per[3]) {
+  return gather_weights(G, A, gather_bubble(A, b, valid, i), b, valid, i, org, per);
 }
 
 // The jobs first, first + stride, ... of the step's gather, one per wavefront (first and stride
@@ -1352,24 +1369,32 @@ __global__ __launch_bounds__(kBlock) void k_spread_gather(Geo geo, BubbleArgs A)
   gather_tiles<T, Geo>(geo, A, blockIdx.x * kBlockWaves + threadIdx.x / 64, gridDim.x * kBlockWaves);
 }
 
-// The same sums with a workgroup per tile, for lattices of few tiles (kGatherWideTiles): a wavefront per
-// tile leaves most of the chip idle there, and with crowded tiles its chain of staged chunks, two
-// round trips to memory for 8 bubbles, is the kernel (30 x 30 x 90 with 384
-// bubbles, 192 tiles: 67 us, 26 us this way).
-// Here 32 bubbles are staged at a time through LDS, and each of the four wavefronts sums two of the
-// tile's eight layers along z. The terms of a cell and their order are the same.
+// The same sums with four workgroups per tile, for lattices of few tiles (kGatherWideTiles): a wavefront
+// per tile leaves most of the chip idle there, and a crowded tile's chain of staged chunks is the kernel
+// (30 x 30 x 90 with 384 bubbles, 192 tiles, up to 300 bubbles in one: 67 us; one workgroup per tile, whose
+// wavefronts all read every bubble's terms from its LDS, 26 us; 17.6 us this way). Each workgroup sums two
+// of the tile's eight layers along z, a wavefront each; all four of its wavefronts stage 32 bubbles at a time
+// in LDS. The terms of a cell and their order are the same.
 constexpr int kWideChunk = kBlock / (int)kTile;  // bubbles staged at a time
+constexpr int kWideLayers = 2;                   // of a workgroup
+constexpr uint32_t kWideParts = kTile / kWideLayers;
+// The tile's count takes the workgroups that have read it in its high bits; the last one clears it.
+constexpr uint32_t kWideRead = 1u << 24;
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_spread_gather_wide(OneColumn geo, BubbleArgs A) {
-  static_assert(kTile == 8 && kBlockWaves == 4, "two layers of the tile per wavefront");
-  __shared__ double s_wt[3][kWideChunk][kTile], s_psi[kWideChunk][3];
+  static_assert(kTile == 8 && kBlockWaves >= kWideLayers, "a wavefront per layer");
+  __shared__ double s_wt[2][2][kWideChunk][kTile];
+  // per bubble and layer: the layer's weight and the reaction
+  __shared__ __align__(16) double s_z[2][kWideChunk][kWideLayers][4];
   __shared__ uint32_t s_ids[kBlock];
   __shared__ uint32_t s_n[kBlockWaves];
   advance_traj_row(A);
-  const GatherJob<T> J = gather_job<T>(geo, A, blockIdx.x);
+  const GatherJob<T> J = gather_job<T>(geo, A, blockIdx.x / kWideParts);
+  const int part = (int)(blockIdx.x % kWideParts);
   const Geom& G = J.G;
-  const uint32_t t = J.t, cnt = J.tcount[t];
+  const uint32_t t = J.t;
+  const uint32_t cnt = __hip_atomic_load(&J.tcount[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kWideRead - 1u);
   if (cnt == 0u) return;  // uniform over the workgroup
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1378,29 +1403,42 @@ __global__ __launch_bounds__(kBlock) void k_spread_gather_wide(OneColumn geo, Bu
   const int org[3] = {(int)(tx * kTile), (int)(ty * kTile), (int)(tz * kTile)};
   const bool per[3] = {G.bc[0] == BC_PER, G.bc[2] == BC_PER, G.bc[4] == BC_PER};
   const int lx = lane % (int)kTile, ly = lane / (int)kTile;
-  double acc[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-  // adds the terms of the n bubbles in s_ids, in that order
+  double acc[3] = {0.0, 0.0, 0.0};
+  // Adds the terms of the n bubbles in s_ids, in that order. The weights of the next chunk, and the
+  // positions of the one after it that theirs follow from, are on their way while a chunk is summed.
   auto add = [&](uint32_t n) {
-    for (uint32_t k0 = 0; k0 < n; k0 += kWideChunk) {
-      const int m = (int)min(n - k0, (uint32_t)kWideChunk);
-      const int k = tid / (int)kTile, i = tid % (int)kTile;
-      const GatherLane st = gather_lane(G, A, s_ids[min(k0 + k, n - 1u)], k < m, i, org, per);
-      s_wt[0][k][i] = st.wx;
-      s_wt[1][k][i] = st.wy;
-      s_wt[2][k][i] = st.wz;
-      if (i < 3) s_psi[k][i] = st.psi;
+    const int k = tid / (int)kTile, i = tid % (int)kTile;
+    auto id = [&](uint32_t k0) { return s_ids[min(k0 + (uint32_t)k, n - 1u)]; };
+    auto bubble = [&](uint32_t k0) { return gather_bubble(A, id(k0), k0 + (uint32_t)k < n, i); };
+    auto weights = [&](uint32_t k0, const GatherBubble& p) {
+      return gather_weights(G, A, p, id(k0), k0 + (uint32_t)k < n, i, org, per);
+    };
+    if (n == 0u) return;
+    GatherBubble next = bubble(0);
+    GatherLane st = weights(0, next);
+    next = bubble(kWideChunk);
+    int p = 0;
+    for (uint32_t k0 = 0; k0 < n; k0 += kWideChunk, p ^= 1) {
+      s_wt[p][0][k][i] = st.wx;
+      s_wt[p][1][k][i] = st.wy;
+      if (i / kWideLayers == part) s_z[p][k][i % kWideLayers][0] = st.wz;
+      if (i < 3)
+        for (int c = 0; c < kWideLayers; ++c) s_z[p][k][c][1 + i] = st.psi;
       __syncthreads();
-      for (int j = 0; j < m; ++j) {
-        const double wx = s_wt[0][j][lx], wy = s_wt[1][j][ly];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const double wz = s_wt[2][j][2 * wave + c];
-          const double W = wx * wy * wz;
-          for (int q = 0; q < 3; ++q) acc[c][q] += s_psi[j][q] * W;
+      st = weights(k0 + kWideChunk, next);
+      next = bubble(k0 + 2 * kWideChunk);
+      if (wave < kWideLayers) {
+        const int m = (int)min(n - k0, (uint32_t)kWideChunk);
+#pragma unroll 4
+        for (int j = 0; j < m; ++j) {
+          const double wx = s_wt[p][0][j][lx], wy = s_wt[p][1][j][ly];
+          const double* z = s_z[p][j][wave];
+          const double W = wx * wy * z[0];
+          for (int q = 0; q < 3; ++q) acc[q] += z[1 + q] * W;
         }
       }
-      __syncthreads();
     }
+    __syncthreads();  // s_ids and the first buffer are free
   };
   if (cnt <= kTileCap) {
     if (wave == 0) {  // the list sorted by bubble index
@@ -1441,26 +1479,18 @@ __global__ __launch_bounds__(kBlock) void k_spread_gather_wide(OneColumn geo, Bu
         n += s_n[w];
       }
       if (cov) s_ids[at] = (uint32_t)b;
-      __syncthreads();
+      __syncthreads();  // also: every thread has read s_n
       add(n);
-      __syncthreads();  // s_n and s_ids are free for the next pass (also when n is zero)
     }
   }
-  const int x = org[0] + lx, y = org[1] + ly;
-  if (x < G.nx && y < G.ny) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int z = org[2] + 2 * wave + c;
-      if (z < G.nz) {
-        const uint32_t at = ((uint32_t)z * G.ny + y) * G.nx + x;
-        J.F[at] = (T)acc[c][0];
-        J.F[G.N + at] = (T)acc[c][1];
-        J.F[2 * (size_t)G.N + at] = (T)acc[c][2];
-      }
-    }
+  const int x = org[0] + lx, y = org[1] + ly, z = org[2] + kWideLayers * part + wave;
+  if (wave < kWideLayers && x < G.nx && y < G.ny && z < G.nz) {
+    const uint32_t at = ((uint32_t)z * G.ny + y) * G.nx + x;
+    J.F[at] = (T)acc[0];
+    J.F[G.N + at] = (T)acc[1];
+    J.F[2 * (size_t)G.N + at] = (T)acc[2];
   }
-  // every thread has read the count (before the barriers above)
-  if (tid == 0) J.tcount[t] = 0u;
+  if (tid == 0 && atomicAdd(&J.tcount[t], kWideRead) / kWideRead == kWideParts - 1u) J.tcount[t] = 0u;
 }
 
 // Region of an overlapped step (one wavefront per bubble): the tile rows (y, z) of the bubble's
@@ -1516,7 +1546,7 @@ __global__ __launch_bounds__(256) void k_mark_slab(OneColumn geo, BubbleArgs A, 
   slab_note(slab, 2, wz.lo - 1 - 2 * kRegionMargin, wz.hi + 1 + 2 * kRegionMargin);
 }
 
-// Tiles up to which a lattice's gather takes a workgroup per tile: four of them per compute unit. (On
+// Tiles up to which a lattice's gather takes four workgroups per tile. (On
 // 256 x 256 x 768 with 20 000 bubbles, 98 304 tiles, a workgroup per tile took 212 us against 79 us.)
 constexpr uint32_t kGatherWideTiles = 1024;
 
@@ -1571,8 +1601,8 @@ hipError_t launch_bubble_kernels(const Geo& geo, const BubbleArgs& A, hipStream_
     }
     if (geo.lists) {  // several bubbles: the lists k_interp filled, summed per tile
       const uint32_t ntiles = (uint32_t)geo.G.tnx * geo.G.tny * div_up(geo.G.nz, kTile);
-      if (ntiles <= kGatherWideTiles) {
-        hipLaunchKernelGGL((k_spread_gather_wide<T>), dim3(ntiles), dim3(kBlock), 0, stream, geo, A);
+      if (ntiles <= kGatherWideTiles && (uint32_t)nb < kWideRead) {
+        hipLaunchKernelGGL((k_spread_gather_wide<T>), dim3(ntiles * kWideParts), dim3(kBlock), 0, stream, geo, A);
         return hipGetLastError();
       }
       hipLaunchKernelGGL((k_spread_gather<T, OneColumn>), dim3(div_up(ntiles, kBlockWaves)),
