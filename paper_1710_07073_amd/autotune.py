@@ -63,9 +63,10 @@ def _save(db):
     os.replace(tmp, CACHE)
 
 
-def time_launch(sim, vec, bx, steps=20, warmup=3, occ=None):
-    """Average duration (s) of one liquid-step launch with the given shape (and occupancy cap, if
-    given)."""
+def time_launch(sim, vec, bx, steps=20, warmup=3, occ=None, pairs=False):
+    """Average duration (s) of one liquid step with the given launch shape (and occupancy cap, if
+    given), one step per launch on lattices that take two with one cell per thread, unless pairs
+    (the shape and the cap do not apply to those launches)."""
     L.lbm_set_launch(sim.ctx, vec, bx)
     if occ is not None:
         L.lbm_set_step_occupancy(sim.ctx, occ)
@@ -73,8 +74,13 @@ def time_launch(sim, vec, bx, steps=20, warmup=3, occ=None):
     L.lbm_step(sim.ctx, warmup)
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
+    single = not pairs and int(np.prod(sim.shape)) >= 1 << 17
     e0.record(stream)
-    L.lbm_step(sim.ctx, steps)
+    if single:
+        for _ in range(steps):
+            L.lbm_step(sim.ctx, 1)
+    else:
+        L.lbm_step(sim.ctx, steps)
     e1.record(stream)
     e1.synchronize()
     return e0.elapsed_time(e1) * 1e-3 / steps
@@ -99,6 +105,10 @@ def tune(sim, steps=20, use_cache=True, verbose=False):
             print(f"  vec={vec} bx={bx}: {t * 1e6:.1f} us/step", flush=True)
     results.sort()
     t, vec, bx = results[0]
+    if vec > 1:  # several cells per thread give up two steps per launch
+        one = min(r for r in results if r[1] == 1)
+        if time_launch(sim, 1, one[2], steps, pairs=True) < t:
+            t, vec, bx = one
     occ_results = []
     for occ in OCCUPANCY:
         to = time_launch(sim, vec, bx, steps, occ=occ)

@@ -1,8 +1,9 @@
 // Batched columns: many independent lattices of uneven size and relaxation rate (the paper's
 // grid-independence and stability sweeps, Sec. 4.2-4.3) advanced together. One liquid-step launch
-// covers every column through a table of work items (contiguous cell ranges of one column); the
+// covers every column through a table of work items (contiguous cell ranges of one column), or, from
+// kBatchPairMinCells cells on, two steps of every column through a table of tiles and chunks of planes; the
 // bubbles of all columns go through the same three bubble kernels as a single lattice. Repeated
-// steps are captured once into a HIP graph and replayed (graph.hpp).
+// steps are captured into HIP graphs and replayed (graph.hpp).
 #include <math.h>
 
 #include <algorithm>

@@ -8,8 +8,9 @@
 //             liquid step must force, or must write the velocity in;
 //   k_spread  (one bubble, exact-time variant: one workgroup) the backward coupling (eq. (21)) of the
 //             reaction into the force field with the same weights (atomic adds) and the tile flags, or
-//   k_spread_gather (several bubbles: one wavefront per tile, or k_spread_gather_wide: one
-//             workgroup per tile of a small lattice) the same sums per cell in bubble order from the lists, so that the force field is bit-reproducible.
+//   k_spread_gather (several bubbles: one wavefront per tile, or k_spread_gather_wide: four
+//             workgroups per tile of a small lattice) the same sums per cell in bubble order from the
+//             lists, so that the force field is bit-reproducible.
 // Up to 256 bubbles on one lattice and 512 over many columns (not in the exact-time variant)
 // k_interp's workgroup also runs k_ode's update of its bubble and flags the bubble's tiles, and k_ode is
 // not launched; a lattice's only bubble is spread there as well, so its bubble half is one launch.
