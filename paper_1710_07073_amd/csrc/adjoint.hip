@@ -26,6 +26,14 @@ static_assert(kRecordMaxSub == kMaxSub, "the record holds every sub-step the adj
 // adjoint bubble state (doubles)
 constexpr int A_X = 0, A_UB = 3, A_ULP = 6, A_SIZE = LBM_BUBBLE_ADJ;
 
+// The sum of the liquid kernels: with wave_sum the compiler contracts the FP32 arithmetic before it in another
+// way (dL/domega 1e-11 apart), and they gain nothing from it.
+__device__ __forceinline__ double wsum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
 __device__ __forceinline__ int wrapi(int i, int n) {
   i %= n;
   return i < 0 ? i + n : i;
@@ -68,7 +76,7 @@ __global__ __launch_bounds__(256) void k_adj_liquid(const T* __restrict__ h, con
     lam_u[G.N + cell] = T(0);
     lam_u[2 * (size_t)G.N + cell] = T(0);
   }
-  dom = wave_sum(dom);
+  dom = wsum(dom);
   if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = dom;
   __syncthreads();
   if (threadIdx.x == 0) atomicAdd(&grad[0], s_red[0] + s_red[1] + s_red[2] + s_red[3]);
@@ -143,7 +151,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 1) void k_adj_liquid_bb(c
       *at_bytes(lam_u, c4 + 2 * n4) = T(0);
     }
   }
-  dom = wave_sum(dom);
+  dom = wsum(dom);
   if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = dom;
   __syncthreads();
   if (threadIdx.x == 0)
