@@ -423,18 +423,20 @@ bool can_pair(const lbm_ctx* ctx, const bubble_params* p) {
 
 // Two method steps (see step2.hip).
 lbm_status step_pair(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb) {
-  uint32_t* const words = ctx->slab + lbm::kSlabWords * ctx->hs.spar;
+  // no bubbles: no box, whatever an overlapped pair of an earlier call marked ahead in the words
+  uint32_t* const words = nb > 0 ? ctx->slab + lbm::kSlabWords * ctx->hs.spar : nullptr;
   if (ctx->overlap && nb > 0 && nb <= lbm::kPairBesideMaxBubbles && lbm::can_overlap(ctx)) {
     const lbm_status ok = check_half(ctx, p, s, nb);
     return ok != LBM_OK ? ok : from_hip(lbm::launch_pair_overlapped(ctx, p, s, nb));
   }
-  lbm_status st = bubble_half(ctx, p, s, nb, true, words, ctx->slab + lbm::kSlabWords * (ctx->hs.spar ^ 1));
+  uint32_t* const next = ctx->slab + lbm::kSlabWords * (ctx->hs.spar ^ 1);
+  lbm_status st = bubble_half(ctx, p, s, nb, true, words, next);
   if (st != LBM_OK) return st;
-  if (nb > 0 && lbm::launch_slab(ctx, words) != hipSuccess) return LBM_EDEVICE;
-  st = bubble_half(ctx, p, s, nb, true, words + 4, nullptr);
+  if (words && lbm::launch_slab(ctx, words) != hipSuccess) return LBM_EDEVICE;
+  st = bubble_half(ctx, p, s, nb, true, words ? words + 4 : nullptr, nullptr);
   if (st != LBM_OK) return st;
   if (lbm::launch_step2(ctx, words) != hipSuccess) return LBM_EDEVICE;
-  if (nb > 0) ctx->hs.spar ^= 1;
+  if (words) ctx->hs.spar ^= 1;
   return LBM_OK;
 }
 }  // namespace

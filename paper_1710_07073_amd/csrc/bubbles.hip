@@ -1818,6 +1818,7 @@ hipError_t launch_bubbles(lbm_ctx* c, const bubble_params* p, const bubble_soa* 
   OneColumn geo;
   BubbleArgs A;
   const hipError_t begun = begin_half(c, p, s, nb, geo, A);
+  if (begun == hipSuccess && nb == 0) c->hs.flag_clean[c->hs.flag_cur] = true;  // it stays all zero
   if (begun != hipSuccess || nb == 0) return begun;
   c->hs.forced = true;
   c->hs.slab_marked = false;
