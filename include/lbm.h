@@ -209,7 +209,10 @@ lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells);
  * force field where bubbles have spread force (or everywhere with LBM_FLAG_STATIC_FORCE),
  * writes the collision velocity U of eq. (13) there (or everywhere with LBM_FLAG_WRITE_U_ALL)
  * and clears the force it used. Lattices of 9 2^16 cells (FP32; FP64 2^17) or more advance two steps per
- * launch where nsteps allows (same results bit for bit; with one cell per thread, lbm_set_launch). */
+ * launch where nsteps allows (with one cell per thread, lbm_set_launch), the same results bit for bit. A launch
+ * swaps the two population buffers, whether it takes one step or two (lbm_state_buffer names the current one);
+ * once the caller has bound buffers (lbm_bind_buffers) or captured steps into a graph of its own, nsteps steps
+ * leave the state in the buffer that nsteps swaps leave it in. */
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps);
 
 /* Bubble half of one step of Algorithm 1 for nb bubbles (forward coupling eq. (20) of the
@@ -255,7 +258,8 @@ lbm_status lbm_restore(lbm_ctx* ctx, const void* state, const void* vel);
 /* Rebind the context to other caller-owned buffers (each nullable: keep the current one). state:
  * a population buffer (layout of the context) that already holds the current state; next_state:
  * the buffer the next liquid step writes into (then the current state); vel: the velocity field
- * the bubble half reads and the liquid step writes. Used by checkpointed recomputation to write
+ * the bubble half reads and the liquid step writes. From then on the two population buffers are written in
+ * turn, step by step (see lbm_step). Used by checkpointed recomputation to write
  * each step's state straight into its own buffer. Not allowed while a bubble half awaits its
  * lbm_step(); state and next_state must differ. Drops the captured lbm_run() graph. */
 lbm_status lbm_bind_buffers(lbm_ctx* ctx, void* state, void* next_state, void* vel);
@@ -272,7 +276,8 @@ lbm_status lbm_check(lbm_ctx* ctx);
  * population buffers), 0 runs every step eagerly. Graph capture needs a non-NULL stream. Lattices of
  * 3 2^18 cells (FP32; FP64 3 2^17) or more with walls on every face (no flag but LBM_FLAG_PLAIN_SOA,
  * one cell per thread, not the exact-time coupling) take their steps in pairs: the rows and planes the bubbles reach one
- * step at a time, the others both steps in one launch; same results bit for bit. */
+ * step at a time, the others both steps in one launch; the same results bit for bit; as for
+ * lbm_step(), a pair swaps the population buffers once, unless the caller has bound buffers or captured steps. */
 lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* params, const bubble_soa* soa, int32_t nb,
                    int32_t nsteps, int32_t graph_steps);
 
@@ -474,8 +479,9 @@ lbm_status lbm_batch_set_persistent(lbm_batch* batch, int32_t enable);
 lbm_status lbm_batch_get_persistent(lbm_batch* batch, int32_t* enabled, int32_t* grid);
 /* nsteps method steps of every column (eager launches). nb must equal the total bubble count. Where
  * every face is a wall and the batch holds 2^20 cells or more, steps are taken in pairs (two liquid
- * steps per launch, the same results), an odd last one by itself; a pair swaps the state buffers
- * once (lbm_batch_column names the current one). */
+ * steps per launch, the same results), an odd last one by itself; a pair swaps the state buffers once
+ * (lbm_batch_column names the current one), unless the caller has captured steps into a graph of its own: then
+ * nsteps steps leave the state in the buffer that nsteps swaps leave it in. */
 lbm_status lbm_batch_step(lbm_batch* batch, const bubble_params* params, const bubble_soa* soa,
                           int32_t nb, int32_t nsteps);
 /* As lbm_batch_step, with graph_steps steps captured into a HIP graph and replayed (see lbm_run). */

@@ -155,6 +155,8 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   c->pops[0] = pops_a;
   c->pops[1] = pops_b;
   c->hs = lbm::HostState{};
+  c->hs.nxt = 1;
+  c->in_order = false;
   c->hs.flag_clean[0] = c->hs.flag_clean[1] = true;
   c->force = force;
   c->vel = vel;
@@ -177,7 +179,7 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   c->traj_rows = 0;
   c->traj_row = reinterpret_cast<uint32_t*>(s + L.traj_row);
   c->slab = reinterpret_cast<uint32_t*>(s + L.slab);
-  c->mid = pairs_ok(desc) ? s + L.mid : nullptr;
+  c->pops[2] = pairs_ok(desc) ? s + L.mid : nullptr;
   if (G.N < lbm::step2_min_cells(c->elem) || !lbm::bb_fast_ok(G, c->elem) ||
       !lbm::choose_tiles2(G, c->elem, lbm::kCus, &c->tiles2) ||
       !lbm::choose_tiles2(G, c->elem, lbm::kCusBeside, &c->tiles2_beside))
@@ -367,20 +369,19 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x) {
 
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
   if (!ctx || nsteps < 0) return LBM_EINVAL;
-  int32_t i = 0;
+  if (lbm::can_step2(ctx) && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
+  auto one = [&] { return lbm::launch_step(ctx); };
+  hipError_t e = hipSuccess;
   // a force spread by a bubble half belongs to the first step
-  if (nsteps > 0 && (ctx->hs.pending || ctx->hs.forced || nsteps % 2)) {
-    if (lbm::launch_step(ctx) != hipSuccess) return LBM_EDEVICE;
-    ++i;
+  if (nsteps > 0 && (ctx->hs.pending || ctx->hs.forced)) {
+    e = one();
+    --nsteps;
   }
-  const bool pairs = lbm::can_step2(ctx);
-  while (i < nsteps) {
-    const int n = pairs && nsteps - i >= 2 ? 2 : 1;
-    if ((n == 2 ? lbm::launch_step2(ctx, nullptr) : lbm::launch_step(ctx)) != hipSuccess)
-      return LBM_EDEVICE;
-    i += n;
-  }
-  return LBM_OK;
+  if (e == hipSuccess && lbm::can_step2(ctx))
+    return from_hip(lbm::steps_in_pairs(ctx->hs, ctx->in_order, ctx->pops[2] != nullptr, nsteps,
+                                        [&] { return lbm::launch_step2(ctx, nullptr); }, one));
+  for (int32_t i = 0; i < nsteps && e == hipSuccess; ++i) e = one();
+  return from_hip(e);
 }
 
 namespace {
@@ -418,14 +419,19 @@ lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s
 // lbm_run() takes the method steps of this lattice in pairs (the exact-time coupling reads the whole
 // state between the two).
 bool can_pair(const lbm_ctx* ctx, const bubble_params* p) {
-  return ctx->mid && lbm::can_step2(ctx) && !(p->coupling & LBM_COUPLING_EXACT_TIME);
+  return ctx->pops[2] && lbm::can_step2(ctx) && !(p->coupling & LBM_COUPLING_EXACT_TIME);
+}
+
+// Pairs run the bubble kernels beside the liquid's two steps.
+bool pair_beside(const lbm_ctx* ctx, int32_t nb) {
+  return ctx->overlap && nb > 0 && nb <= lbm::kPairBesideMaxBubbles && lbm::can_overlap(ctx);
 }
 
 // Two method steps (see step2.hip).
 lbm_status step_pair(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb) {
   // no bubbles: no box, whatever an overlapped pair of an earlier call marked ahead in the words
   uint32_t* const words = nb > 0 ? ctx->slab + lbm::kSlabWords * ctx->hs.spar : nullptr;
-  if (ctx->overlap && nb > 0 && nb <= lbm::kPairBesideMaxBubbles && lbm::can_overlap(ctx)) {
+  if (pair_beside(ctx, nb)) {
     const lbm_status ok = check_half(ctx, p, s, nb);
     return ok != LBM_OK ? ok : from_hip(lbm::launch_pair_overlapped(ctx, p, s, nb));
   }
@@ -498,11 +504,12 @@ lbm_status lbm_populations(lbm_ctx* ctx, void* out) {
 lbm_status lbm_bind_buffers(lbm_ctx* ctx, void* state, void* next_state, void* vel) {
   if (!ctx || ctx->hs.pending) return LBM_EINVAL;
   void* cur = state ? state : ctx->pops[ctx->hs.cur];
-  void* nxt = next_state ? next_state : ctx->pops[ctx->hs.cur ^ 1];
+  void* nxt = next_state ? next_state : ctx->pops[ctx->hs.nxt];
   if (cur == nxt) return LBM_EINVAL;
   ctx->pops[ctx->hs.cur] = cur;
-  ctx->pops[ctx->hs.cur ^ 1] = nxt;
+  ctx->pops[ctx->hs.nxt] = nxt;
   if (vel) ctx->vel = vel;
+  if (state || next_state) ctx->in_order = true;
   ctx->graph.reset();  // captured launches name the old buffers
   return LBM_OK;
 }
@@ -542,22 +549,23 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
   // an armed step record belongs to one call of bubbles_step (a graph would replay it)
   if (ctx->arm_record) return LBM_EINVAL;
   ctx->hs.marked = ctx->hs.slab_marked = false;  // the bubble state may have changed since the last call
+  const lbm_status ok = check_half(ctx, p, s, nb);
+  if (ok != LBM_OK && nsteps > 0) return ok;
+  if (lbm::can_step2(ctx) && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
+  auto one = [&]() -> lbm_status {
+    const lbm_status st = bubble_half(ctx, p, s, nb, true);
+    return st == LBM_OK ? from_hip(lbm::launch_step(ctx)) : st;
+  };
   // the last `single` of the n steps are not paired
   auto steps = [&](int32_t n, int32_t single = 0) -> lbm_status {
-    const bool pairs = can_pair(ctx, p);
-    for (int32_t i = 0; i < n;) {
-      const bool two = pairs && n - single - i >= 2;
-      lbm_status st;
-      if (two) {
-        st = step_pair(ctx, p, s, nb);
-      } else {
-        st = bubble_half(ctx, p, s, nb, true);
-        if (st == LBM_OK) st = lbm_step(ctx, 1);
-      }
-      if (st != LBM_OK) return st;
-      i += two ? 2 : 1;
+    lbm_status st = LBM_OK;
+    if (can_pair(ctx, p)) {
+      auto two = [&] { return step_pair(ctx, p, s, nb); };
+      st = lbm::steps_in_pairs(ctx->hs, ctx->in_order, true, n - single, two, one);
+      n = single;
     }
-    return LBM_OK;
+    for (int32_t i = 0; i < n && st == LBM_OK; ++i) st = one();
+    return st;
   };
   if (graph_steps == 0 || nsteps < graph_steps || !ctx->stream) return steps(nsteps);
   // A pair flips the population buffers once, so an odd number of pairs would need two graphs, one
@@ -571,7 +579,7 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     // steps is recorded with the graph
     const lbm::HostState pre = ctx->hs;
     const uint32_t mode = (pre.flag_clean[0] ? 1u : 0u) | (pre.flag_clean[1] ? 2u : 0u) |
-                          ((uint32_t)pre.rpar << 4) | (ctx->overlap ? 32u : 0u) |
+                          ((uint32_t)pre.rpar << 4) | (ctx->overlap ? 32u : 0u) | (ctx->in_order ? 8u : 0u) |
                           (pre.marked ? 64u : 0u) | ((uint32_t)pre.spar << 7) |
                           (pre.slab_marked ? 4u : 0u) |
                           ((uint32_t)ctx->step_vec << 8) | (ctx->step_bx << 12) |

@@ -19,7 +19,7 @@
 namespace lbm {
 // Host-side step state of a batch, the same for all columns.
 struct BatchState {
-  int cur;         // population buffer holding the current state
+  int cur, nxt;    // population buffers: of the current state, and written next
   int flag_cur;    // current tile mask
   bool flag_clean[2];
   int spar;        // parity of the next pair of steps (its slab words)
@@ -29,6 +29,7 @@ struct BatchState {
 
 struct lbm_batch {
   lbm::BatchState hs;
+  bool in_order;    // the caller captured steps (see lbm_ctx)
   int ncols;
   int32_t precision;
   size_t elem;
@@ -75,20 +76,20 @@ constexpr uint32_t kSumBlocks = 16;  // workgroups per column of the per-column 
 template <typename T, int FACES>
 __global__ __launch_bounds__(256) void k_batch_step(const ColumnDev* __restrict__ cols,
                                                     const uint32_t* __restrict__ item_col,
-                                                    uint32_t nitems, int cur, int flag, int flags) {
+                                                    uint32_t nitems, int cur, int nxt, int flag, int flags) {
   // each XCD takes a contiguous range of items (measured faster here than launch order, unlike
   // the single-lattice step)
-  batch_item<T, FACES>(cols, item_col, xcd_remap(blockIdx.x, nitems), cur, flag, flags);
+  batch_item<T, FACES>(cols, item_col, xcd_remap(blockIdx.x, nitems), cur, nxt, flag, flags);
 }
 
 // Two liquid steps of every column in one launch (step2_cell.hpp), with the slab of each: see step2.hip.
 // What a column's launches of a pair name.
 template <typename T>
-__device__ __forceinline__ Step2Args<T> pair_args(const ColumnDev& C, int cur, int flag, int spar) {
+__device__ __forceinline__ Step2Args<T> pair_args(const ColumnDev& C, int cur, int nxt, int flag, int spar) {
   Step2Args<T> A;
   A.src = static_cast<const T*>(C.pops[cur]);
-  A.mid = static_cast<const T*>(C.mid);
-  A.dst = static_cast<T*>(C.pops[cur ^ 1]);
+  A.mid = static_cast<const T*>(C.pops[3 - cur - nxt]);
+  A.dst = static_cast<T*>(C.pops[nxt]);
   A.F = static_cast<T*>(C.F);
   A.U = static_cast<T*>(C.U);
   A.tiles = C.tiles[flag];
@@ -107,21 +108,21 @@ __device__ __forceinline__ Step2Args<T> pair_args(const ColumnDev& C, int cur, i
 template <typename T, int FACES>
 __global__ __launch_bounds__(step2_threads<T>()) void k_batch_step2(const ColumnDev* __restrict__ cols,
                                                                     const uint32_t* __restrict__ blocks,
-                                                                    int cur, int flag, int spar) {
+                                                                    int cur, int nxt, int flag, int spar) {
   __shared__ Plane2<T, step2_threads<T>()> s[2];
   const uint32_t col = blocks[2 * blockIdx.x], b = blocks[2 * blockIdx.x + 1];
   if (col == kNoColumn) return;
-  const Step2Args<T> A = pair_args<T>(cols[col], cur, flag, spar);
+  const Step2Args<T> A = pair_args<T>(cols[col], cur, nxt, flag, spar);
   step2_block<T, FACES, false>(s, A, b);
 }
 
 // The first step of every column's slab, by a share of the workgroups in proportion to its cells.
 template <typename T, bool FS>
 __global__ __launch_bounds__(256) void k_batch_slab(const ColumnDev* __restrict__ cols,
-                                                    const uint32_t* __restrict__ blocks, int cur, int flag,
-                                                    int spar) {
+                                                    const uint32_t* __restrict__ blocks, int cur, int nxt,
+                                                    int flag, int spar) {
   const ColumnDev& C = cols[blocks[2 * blockIdx.x]];
-  const Step2Args<T> P = pair_args<T>(C, cur, flag, spar);
+  const Step2Args<T> P = pair_args<T>(C, cur, nxt, flag, spar);
   const SlabArgs<T> A = {P.src, const_cast<T*>(P.mid), P.F, P.U, P.tiles, P.tiles_next, P.slab, P.G,
                          P.omega, 0, P.ntiles, P.L.oy, SLAB_FIRST};
   slab_block<T, FS>(A, blocks[2 * blockIdx.x + 1], C.slab_blocks);
@@ -414,7 +415,7 @@ template <typename T, int FACES>
 hipError_t batch_step_faces(lbm_batch* b) {
   hipLaunchKernelGGL((k_batch_step<T, FACES>), dim3(b->nitems), dim3(256),
                      occupancy_lds(b->lds_per_cu, b->step_wgs), b->stream, b->dev, b->item_col_dev,
-                     b->nitems, b->hs.cur, b->hs.flag_cur, b->flags);
+                     b->nitems, b->hs.cur, b->hs.nxt, b->hs.flag_cur, b->flags);
   return hipGetLastError();
 }
 
@@ -475,7 +476,7 @@ hipError_t batch_method_step(lbm_batch* b, const bubble_params* p, const bubble_
   if (e != hipSuccess) return e;
   e = b->elem == 4 ? batch_step_typed<float>(b) : batch_step_typed<double>(b);
   if (e != hipSuccess) return e;
-  b->hs.cur ^= 1;
+  swap_buffers(b->hs);
   b->hs.flag_clean[b->hs.flag_cur ^ 1] = true;
   ++b->hs.steps;
   return hipSuccess;
@@ -486,10 +487,10 @@ hipError_t batch_slab(lbm_batch* b) {
   const uint32_t* const blocks = b->blocks2 + 2 * b->nblocks2;
   if (b->faces == FACES_WALLS)
     hipLaunchKernelGGL((k_batch_slab<T, true>), dim3(b->nblocks_slab), dim3(256), 0, b->stream, b->dev, blocks,
-                       b->hs.cur, b->hs.flag_cur, b->hs.spar);
+                       b->hs.cur, b->hs.nxt, b->hs.flag_cur, b->hs.spar);
   else
     hipLaunchKernelGGL((k_batch_slab<T, false>), dim3(b->nblocks_slab), dim3(256), 0, b->stream, b->dev, blocks,
-                       b->hs.cur, b->hs.flag_cur, b->hs.spar);
+                       b->hs.cur, b->hs.nxt, b->hs.flag_cur, b->hs.spar);
   return hipGetLastError();
 }
 
@@ -498,10 +499,10 @@ hipError_t batch_step2(lbm_batch* b) {
   const dim3 grid(b->nblocks2), block(step2_threads<T>());
   if (b->faces == FACES_WALLS)
     hipLaunchKernelGGL((k_batch_step2<T, FACES_WALLS>), grid, block, 0, b->stream, b->dev, b->blocks2, b->hs.cur,
-                       b->hs.flag_cur, b->hs.spar);
+                       b->hs.nxt, b->hs.flag_cur, b->hs.spar);
   else
     hipLaunchKernelGGL((k_batch_step2<T, FACES_BB>), grid, block, 0, b->stream, b->dev, b->blocks2, b->hs.cur,
-                       b->hs.flag_cur, b->hs.spar);
+                       b->hs.nxt, b->hs.flag_cur, b->hs.spar);
   return hipGetLastError();
 }
 
@@ -514,7 +515,7 @@ hipError_t batch_pair(lbm_batch* b, const bubble_params* p, const bubble_soa* s,
     if (e != hipSuccess) return e;
     b->hs.flag_clean[b->hs.flag_cur ^ 1] = true;
   }
-  b->hs.cur ^= 1;
+  swap_buffers(b->hs);
   if (nb > 0) b->hs.spar ^= 1;
   b->hs.steps += 2;
   return hipSuccess;
@@ -522,13 +523,11 @@ hipError_t batch_pair(lbm_batch* b, const bubble_params* p, const bubble_soa* s,
 
 // n method steps of every column.
 hipError_t batch_steps(lbm_batch* b, const bubble_params* p, const bubble_soa* s, int32_t nb, int32_t n) {
-  for (int32_t i = 0; i < n;) {
-    const bool two = b->nblocks2 > 0 && n - i >= 2;
-    const hipError_t e = two ? batch_pair(b, p, s, nb) : batch_method_step(b, p, s, nb);
-    if (e != hipSuccess) return e;
-    i += two ? 2 : 1;
-  }
-  return hipSuccess;
+  auto one = [&] { return batch_method_step(b, p, s, nb); };
+  if (b->nblocks2 > 0) return steps_in_pairs(b->hs, b->in_order, true, n, [&] { return batch_pair(b, p, s, nb); }, one);
+  hipError_t e = hipSuccess;
+  for (int32_t i = 0; i < n && e == hipSuccess; ++i) e = one();
+  return e;
 }
 
 // Polls of a persistent launch's barrier before it aborts (about a second of waiting).
@@ -561,7 +560,7 @@ hipError_t batch_persistent_steps(lbm_batch* b, const bubble_params* p, const bu
     const int m = b->hs.flag_cur ^ 1;
     b->hs.flag_clean[m] = false;
     b->hs.flag_cur = m;
-    b->hs.cur ^= 1;
+    swap_buffers(b->hs);
     b->hs.flag_clean[b->hs.flag_cur ^ 1] = true;
     ++b->hs.steps;
   }
@@ -621,6 +620,8 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
     b->lds_per_cu = lds > 0 ? (uint32_t)lds : 0u;
   }
   b->hs.cur = 0;
+  b->hs.nxt = 1;
+  b->in_order = false;
   b->hs.flag_cur = 0;
   b->hs.flag_clean[0] = b->hs.flag_clean[1] = true;
   b->hs.steps = 0;
@@ -689,7 +690,7 @@ lbm_status lbm_batch_init(const lbm_column* cols, int32_t ncols, int32_t precisi
     if (b->nblocks2 > 0) {
       D.tiles2 = L.tiles2[c];
       D.slab_blocks = L.slab_blocks[c];
-      D.mid = S + L.mid[c];
+      D.pops[2] = S + L.mid[c];
     }
     D.bubble_begin = k.bubble_begin;
     D.nb = k.nb;
@@ -754,6 +755,7 @@ lbm_status lbm_batch_step(lbm_batch* b, const bubble_params* p, const bubble_soa
   if (nb > 0 && (!s->x || !s->y || !s->z || !s->ux || !s->uy || !s->uz || !s->d || !s->ulx ||
                  !s->uly || !s->ulz || !s->state || !s->work))
     return LBM_EINVAL;
+  if (caller_captures(b->stream)) b->in_order = true;
   if (b->persistent) return to_status(batch_persistent_steps(b, p, s, nb, nsteps));
   return to_status(batch_steps(b, p, s, nb, nsteps));
 }
@@ -788,7 +790,7 @@ lbm_status lbm_batch_run(lbm_batch* b, const bubble_params* p, const bubble_soa*
   int32_t done = 0;
   while (nsteps - done >= graph_steps) {
     const uint32_t mode = (b->hs.flag_clean[0] ? 1u : 0u) | (b->hs.flag_clean[1] ? 2u : 0u) |
-                          (b->persistent ? 4u : 0u) | ((uint32_t)b->hs.spar << 3);
+                          (b->persistent ? 4u : 0u) | ((uint32_t)b->hs.spar << 3) | (b->in_order ? 16u : 0u);
     const GraphKey key = GraphKey::of(p, s, nb, b->hs.cur, b->hs.flag_cur, graph_steps, mode);
     const BatchState pre = b->hs;
     bool captured = false;

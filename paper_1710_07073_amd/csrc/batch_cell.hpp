@@ -32,13 +32,13 @@ __device__ __forceinline__ void pull_all_g(T* g, const gmem<T>* src, const Geom&
 template <typename T, int FACES>
 __device__ __forceinline__ void batch_item(const ColumnDev* __restrict__ cols,
                                            const uint32_t* __restrict__ item_col, uint32_t item,
-                                           int cur, int flag, int flags) {
+                                           int cur, int nxt, int flag, int flags) {
   const ColumnDev& C = cols[item_col[item]];
   const Geom G = C.G;
   // the column's buffers, as pointers into global memory (the table is not a kernel argument,
   // so the compiler would otherwise address them as flat memory)
   const gmem<T>* src = reinterpret_cast<const gmem<T>*>(gbytes<T>(C.pops[cur]));
-  gmem<T>* dst = reinterpret_cast<gmem<T>*>(gbytes<T>(C.pops[cur ^ 1]));
+  gmem<T>* dst = reinterpret_cast<gmem<T>*>(gbytes<T>(C.pops[nxt]));
   gmem<T>* F = reinterpret_cast<gmem<T>*>(gbytes<T>(C.F));
   gmem<T>* U = reinterpret_cast<gmem<T>*>(gbytes<T>(C.U));
   const gmem<uint8_t>* tiles = reinterpret_cast<const gmem<uint8_t>*>(gbytes<uint8_t>(C.tiles[flag]));

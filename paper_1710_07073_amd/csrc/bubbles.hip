@@ -1694,8 +1694,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_persistent(ManyColumns geo,
       if (!grid_barrier(P.barrier, gridDim.x, P.spin_limit, A.status)) return;
     }
     for (uint32_t k = blockIdx.x; k < P.nitems; k += gridDim.x)
-      batch_item<T, FACES>(P.cols, P.item_col, xcd_remap(k, P.nitems), P.cur0 ^ odd, g.flag,
-                           P.flags);
+      batch_item<T, FACES>(P.cols, P.item_col, xcd_remap(k, P.nitems), P.cur0 ^ odd, P.cur0 ^ odd ^ 1,
+                           g.flag, P.flags);
     if (!grid_barrier(P.barrier, gridDim.x, P.spin_limit, A.status)) return;
   }
 }

@@ -20,6 +20,7 @@ struct Tiles2 {
 // Host-side step state of a context: which buffers and masks the next launches use.
 struct HostState {
   int cur;                // pops[cur] holds the current post-collision state
+  int nxt;                // pops[nxt] is what the next liquid launch writes (then the current state)
   int flag_cur;           // current force / velocity tile mask
   bool flag_clean[2];     // tile mask known to be all zero
   int rpar;               // parity of the next overlapped step (its region flags, list, counter)
@@ -40,10 +41,10 @@ struct lbm_ctx {
   bool general;     // any free-slip or periodic face
   bool periodic;    // any periodic face
   size_t elem;      // 4 or 8
-  void* pops[2];    // population buffers; pops[hs.cur] holds the current post-collision state
+  // the caller's population buffers, and the middle buffer of a pair of method steps (step2.hip) or null
+  void* pops[3];
   void* force;
   void* vel;
-  void* mid;  // middle buffer of a pair of method steps (step2.hip), or null
   uint32_t* slab;  // slab words, kSlabWords per pair parity
   lbm::Tiles2 tiles2, tiles2_beside;  // with the chip to itself, and beside the bubble kernels
   // Two tile masks, one byte per 8^3 tile (force present / velocity needed). bubbles_step()
@@ -64,6 +65,9 @@ struct lbm_ctx {
   uint32_t* tcount;
   uint32_t* tlist;
   lbm::HostState hs;
+  // the caller bound buffers of its own or captured steps: graphs and pointers of its own name the buffers, so
+  // that from then on n steps leave the state where n single steps do
+  bool in_order;
   bool overlap;               // overlap enabled (lbm_set_overlap)
   hipStream_t side;           // null if it could not be created (overlap then unavailable)
   hipEvent_t ev_fork, ev_join;
@@ -163,7 +167,7 @@ constexpr uint32_t kSlabBase = 1u << 30;
 struct ColumnDev {
   Geom G;
   double omega, nu;
-  void* pops[2];
+  void* pops[3];  // as lbm_ctx
   void* F;
   void* U;
   uint8_t* tiles[2];
@@ -176,10 +180,9 @@ struct ColumnDev {
   uint32_t* tcount;
   uint32_t* tlist;
   float rnx, rny;  // 1 / nx and 1 / ny rounded to float (cell coordinates of the batched step)
-  // two steps per launch: its tiles, middle buffer, and slab words of the two pair parities
+  // two steps per launch: its tiles, and slab words of the two pair parities
   Tiles2 tiles2;
   uint32_t slab_blocks;  // workgroups of its slab's first step
-  void* mid;
   uint32_t* slab;
   double g, sigma;  // the column's bubbles' gravity and surface tension (0: the shared value)
 };
@@ -347,6 +350,47 @@ hipError_t launch_populations(lbm_ctx* c, void* out);
 hipError_t launch_fill(void* ptr, size_t bytes, hipStream_t s);
 
 inline uint32_t div_up(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
+
+// The one of the three population buffers that neither holds the state nor is written next.
+template <class State>
+int third_buffer(const State& hs) {
+  return 3 - hs.cur - hs.nxt;
+}
+template <class State>
+void swap_buffers(State& hs) {
+  const int c = hs.cur;
+  hs.cur = hs.nxt;
+  hs.nxt = c;
+}
+
+// n steps by two() and one(), which advance two and one of them and swap hs.cur and hs.nxt. in_order: the state
+// ends in the buffer n single steps leave it in. A pair swaps once for two steps, so an odd number of pairs
+// then goes round through the middle buffer: its last pair writes there if a single step follows, else its
+// last two go there and back. Without a middle buffer (third false), and for one pair alone, two steps
+// are single instead. (101 x 67 x 251 FP32, ten steps: 240 us in pairs that swap, 335 us round through a third
+// buffer, which the caches do not hold beside the two.)
+template <class State, class Two, class One>
+auto steps_in_pairs(State& hs, bool in_order, bool third, int32_t n, Two&& two, One&& one) {
+  const bool odd = n % 2 != 0;
+  int32_t pairs = n / 2;
+  if (in_order && pairs % 2 != 0 && (!third || (pairs == 1 && !odd))) --pairs;
+  const int32_t round = !in_order || pairs % 2 == 0 ? 0 : odd ? 1 : 2;
+  decltype(one()) e{};
+  for (int32_t i = 0; i < pairs && !e; ++i) {
+    if (pairs - i <= round) hs.nxt = third_buffer(hs);
+    e = two();
+  }
+  if (hs.cur == 2) hs.nxt = third_buffer(hs);
+  for (int32_t i = 2 * pairs; i < n && !e; ++i) e = one();
+  if (hs.nxt == 2) hs.nxt = 1 - hs.cur;
+  return e;
+}
+
+// The stream is being captured by the caller (called outside the library's own captures).
+inline bool caller_captures(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
 
 // Records the caller's timing events (if any) around one launch on stream s.
 template <class F>

@@ -273,7 +273,7 @@ hipError_t launch_bb(lbm_ctx* c, const uint32_t* region) {
   const uint32_t nbx = div_up(G.nx, bx), nby = div_up(G.ny, by);
   auto go = [&](auto kernel, uint32_t nblocks, dim3 threads) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), threads, step_lds(c), c->stream,
-                       static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.cur ^ 1]),
+                       static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.nxt]),
                        static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
                        c->tiles[c->hs.flag_cur ^ 1], region, G, (T)c->desc.omega, c->desc.flags, nbx, nby);
     return hipGetLastError();
@@ -291,7 +291,7 @@ hipError_t launch_typed(lbm_ctx* c, uint32_t bx) {
   const uint32_t nbx = div_up(G.nx / VEC, bx), nby = div_up(G.ny, by);
   auto go = [&](auto kernel, uint32_t nblocks, dim3 threads) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), threads, step_lds(c), c->stream,
-                       static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.cur ^ 1]),
+                       static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.nxt]),
                        static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
                        c->tiles[c->hs.flag_cur ^ 1], G, (T)c->desc.omega, c->desc.flags, nbx, nby);
     return hipGetLastError();
@@ -321,7 +321,7 @@ hipError_t launch_region_typed(lbm_ctx* c, int32_t nb, hipStream_t stream) {
   const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(rows * per, 16384));
   const int r = c->hs.rpar;
   hipLaunchKernelGGL((k_region_bb<T, FS>), dim3(blocks), dim3(bx, by), step_lds(c), stream,
-                     static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.cur ^ 1]),
+                     static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(c->pops[c->hs.nxt]),
                      static_cast<T*>(c->force), static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur],
                      c->tiles[c->hs.flag_cur ^ 1], c->region[r], c->region_list[r], c->region_count + r,
                      G, (T)c->desc.omega, c->desc.flags, c->nrows,
@@ -369,7 +369,7 @@ hipError_t launch_step(lbm_ctx* c) {
     });
   }
   if (e == hipSuccess) {
-    c->hs.cur ^= 1;
+    swap_buffers(c->hs);
     c->hs.flag_clean[c->hs.flag_cur ^ 1] = true;
     c->hs.last_overlapped = overlapped;
     c->hs.last_pair = false;

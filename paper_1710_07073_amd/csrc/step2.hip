@@ -78,8 +78,8 @@ hipError_t launch_typed(lbm_ctx* c, const uint32_t* slab, bool bulk) {
   const Geom& G = c->geom;
   Step2Args<T> A;
   A.src = static_cast<const T*>(c->pops[c->hs.cur]);
-  A.mid = static_cast<const T*>(c->mid);
-  A.dst = static_cast<T*>(c->pops[c->hs.cur ^ 1]);
+  A.mid = static_cast<const T*>(c->pops[third_buffer(c->hs)]);
+  A.dst = static_cast<T*>(c->pops[c->hs.nxt]);
   A.F = static_cast<T*>(c->force);
   A.U = static_cast<T*>(c->vel);
   A.tiles = c->tiles[c->hs.flag_cur];
@@ -113,8 +113,9 @@ template <typename T, bool FS>
 hipError_t launch_slab_typed(lbm_ctx* c, const uint32_t* slab, int part, hipStream_t s) {
   const Geom& G = c->geom;
   const bool second = part == SLAB_SECOND;
-  const void* src = second ? c->mid : c->pops[c->hs.cur];
-  void* dst = second ? c->pops[c->hs.cur ^ 1] : c->mid;
+  void* const mid = c->pops[third_buffer(c->hs)];
+  const void* src = second ? mid : c->pops[c->hs.cur];
+  void* dst = second ? c->pops[c->hs.nxt] : mid;
   const SlabArgs<T> A = {static_cast<const T*>(src), static_cast<T*>(dst), static_cast<T*>(c->force),
                          static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur], c->tiles[c->hs.flag_cur ^ 1], slab, G,
                          (T)c->desc.omega, c->desc.flags, c->ntiles,
@@ -146,7 +147,7 @@ hipError_t launch_step2(lbm_ctx* c, const uint32_t* slab) {
     return c->elem == 4 ? launch_faces<float>(c, slab, false) : launch_faces<double>(c, slab, false);
   });
   if (e == hipSuccess) {
-    c->hs.cur ^= 1;
+    swap_buffers(c->hs);
     c->hs.flag_clean[c->hs.flag_cur ^ 1] = true;
     c->hs.last_overlapped = false;
     c->hs.forced = false;
@@ -172,7 +173,7 @@ hipError_t launch_pair_first(lbm_ctx* c, const uint32_t* slab, hipStream_t s) {
 hipError_t launch_pair_second(lbm_ctx* c, const uint32_t* slab) {
   const hipError_t e = launch_slab_part(c, slab, SLAB_SECOND, c->stream);
   if (e == hipSuccess) {
-    c->hs.cur ^= 1;
+    swap_buffers(c->hs);
     c->hs.last_overlapped = c->hs.last_pair = true;
     c->hs.forced = false;
     c->hs.steps += 2;
