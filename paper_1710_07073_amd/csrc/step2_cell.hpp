@@ -223,15 +223,17 @@ __device__ void march2(Plane2<T, NT>* s, const Geom& G, const Lattice2& A, T ome
     } else {
       // the rules of pull_index with 32-bit byte offsets: wrapped neighbours on periodic axes
       const uint32_t walls = ln.lat | (kz == 0 && !perz ? 16u : 0u) | (kz == G.nz - 1 && !perz ? 32u : 0u);
-      const int dzm = kz == 0 && perz ? (G.nz - 1) * (int)zs4 : -(int)zs4;
-      const int dzp = kz == G.nz - 1 && perz ? -(G.nz - 1) * (int)zs4 : (int)zs4;
+      // modulo 2^32: a state of 2 to 4 GiB spans more than an int
+      const uint32_t round_z = (uint32_t)(G.nz - 1) * zs4;
+      const uint32_t dzm = kz == 0 && perz ? round_z : 0u - zs4;
+      const uint32_t dzp = kz == G.nz - 1 && perz ? 0u - round_z : zs4;
       const uint32_t qs4 = G.qs * esz;
       auto one = [&](auto qc) {
         constexpr int q = decltype(qc)::value;
         constexpr uint32_t m = lat_mask(q) | (CZ[q] > 0 ? 16u : 0u) | (CZ[q] < 0 ? 32u : 0u);
         const uint32_t dx = (uint32_t)(CX[q] > 0 ? ln.dxm : CX[q] < 0 ? ln.dxp : 0);
         const uint32_t dy = (uint32_t)(CY[q] > 0 ? ln.dym : CY[q] < 0 ? ln.dyp : 0);
-        const uint32_t dz = (uint32_t)(CZ[q] > 0 ? dzm : CZ[q] < 0 ? dzp : 0);
+        const uint32_t dz = CZ[q] > 0 ? dzm : CZ[q] < 0 ? dzp : 0u;
         const uint32_t hit = walls & m;
         uint32_t at = (uint32_t)q * qs4 + dx + dy + dz;
         if (hit) {
