@@ -131,32 +131,40 @@ def tune_method_occupancy(sim, steps=8, caps=OCCUPANCY, modes=None):
     """The occupancy cap timed on whole method steps (bubble half and liquid step) rather than on
     the liquid step alone: beside the bubble kernels the best cap can differ. Where the lattice
     can overlap, the overlapped and the serial step are both timed (the same results bit for bit;
-    which is faster depends on how long the bubble half is against the liquid step). Applies the
-    fastest (cap, overlap) and returns (cap, [[cap, us per step, overlap]], method steps run).
-    The simulation advances by len(modes) * len(caps) * (steps + 2) steps (callers count them as
-    warm-up)."""
+    which is faster depends on how long the bubble half is against the liquid step). Runs of steps
+    decide between the two. They may take their steps in pairs, whose main launch the cap does not
+    apply to, so the cap is the fastest of the mode's single steps. Applies both and returns (cap,
+    [[cap, us per step of a run, overlap]], method steps run). The simulation advances by
+    len(modes) * len(caps) * (2 * steps + 2) steps (callers count them as warm-up)."""
     stream = sim.stream
     bub = sim.bubbles
     on, avail = L.lbm_get_overlap(sim.ctx)
     if modes is None:
         modes = (True, False) if avail else (bool(on),)
-    sweep = []
+
+    def timed(calls, n):
+        e0 = torch.cuda.Event(enable_timing=True)
+        e1 = torch.cuda.Event(enable_timing=True)
+        e0.record(stream)
+        for _ in range(calls):
+            L.lbm_run(sim.ctx, sim.params, bub.soa, bub.nb, n, 0)
+        e1.record(stream)
+        e1.synchronize()
+        return e0.elapsed_time(e1) * 1e3 / (calls * n)
+
+    sweep, singles = [], []
     for ov in modes:
         L.lbm_set_overlap(sim.ctx, ov)
         for occ in caps:
             L.lbm_set_step_occupancy(sim.ctx, occ)
-            L.lbm_run(sim.ctx, sim.params, bub.soa, bub.nb, 2, 0)
-            e0 = torch.cuda.Event(enable_timing=True)
-            e1 = torch.cuda.Event(enable_timing=True)
-            e0.record(stream)
-            L.lbm_run(sim.ctx, sim.params, bub.soa, bub.nb, steps, 0)
-            e1.record(stream)
-            e1.synchronize()
-            sweep.append([occ, e0.elapsed_time(e1) * 1e3 / steps, bool(ov)])
-    best = min(sweep, key=lambda r: r[1])
-    L.lbm_set_overlap(sim.ctx, best[2])
-    L.lbm_set_step_occupancy(sim.ctx, best[0])
-    return best[0], sweep, len(modes) * len(caps) * (steps + 2)
+            timed(2, 1)
+            sweep.append([occ, timed(1, steps), bool(ov)])
+            singles.append((timed(steps, 1), occ, bool(ov)))
+    overlap = min(sweep, key=lambda r: r[1])[2]
+    cap = min(r for r in singles if r[2] == overlap)[1]
+    L.lbm_set_overlap(sim.ctx, overlap)
+    L.lbm_set_step_occupancy(sim.ctx, cap)
+    return cap, sweep, len(sweep) * (2 * steps + 2)
 
 
 # ---------------------------------------------------------------------------------------------
