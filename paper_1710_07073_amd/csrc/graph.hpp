@@ -38,87 +38,126 @@ struct GraphKey {
   }
 };
 
-class StepGraph {
- public:
-  StepGraph() { memset(&key_, 0, sizeof(key_)); }
-  ~StepGraph() { reset(); }
-  StepGraph(const StepGraph&) = delete;
-  StepGraph& operator=(const StepGraph&) = delete;
+// A captured graph and the end of its last replay. The runtime still walks a graph it replays, one of several
+// streams most of all: it may be destroyed only once that replay has ended.
+struct GraphExec {
+  hipGraphExec_t exec = nullptr;
+  hipEvent_t done = nullptr;
 
+  void destroy() {
+    if (done) {
+      (void)hipEventSynchronize(done);  // ended long ago as a rule
+      (void)hipEventDestroy(done);
+    }
+    if (exec) (void)hipGraphExecDestroy(exec);
+    exec = nullptr;
+    done = nullptr;
+  }
+};
+
+// A few captured graphs, each with the host step state its replay leaves behind (Post); a new
+// key replaces the least recently used one. Replaced graphs wait for the end of their last replay among the old
+// ones, of which a few are kept.
+template <class Post, int N = 2>
+class GraphCache {
+ public:
+  GraphCache() = default;
+  ~GraphCache() {
+    reset();
+    for (int i = 0; i < nold_; ++i) old_[i].destroy();
+  }
+  GraphCache(const GraphCache&) = delete;
+  GraphCache& operator=(const GraphCache&) = delete;
+
+  // No graph is replayed any more; no call to the runtime, so also for a caller that captures.
   void reset() {
-    if (exec_) (void)hipGraphExecDestroy(exec_);
-    exec_ = nullptr;
-    key_.valid = false;
+    for (Slot& s : slot_) retire(s);
   }
 
   // Capture `enqueue` on stream s unless a graph for the same key exists.
   template <class F>
   hipError_t ensure(const GraphKey& key, hipStream_t s, F&& enqueue, bool* captured) {
     *captured = false;
-    if (exec_ && key_.same(key)) return hipSuccess;
-    reset();
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return e;
-    const hipError_t ee = enqueue();
-    e = hipStreamEndCapture(s, &g);
-    if (ee != hipSuccess) {
-      if (e == hipSuccess && g) (void)hipGraphDestroy(g);
-      return ee;
+    int k = -1;
+    for (int i = 0; i < N; ++i)
+      if (slot_[i].g.exec && slot_[i].key.same(key)) k = i;
+    if (k >= 0) {
+      cur_ = k;
+      slot_[k].used = ++clock_;
+      return hipSuccess;
     }
+    k = 0;
+    for (int i = 1; i < N; ++i)
+      if (slot_[i].used < slot_[k].used) k = i;
+    Slot& slot = slot_[k];
+    cur_ = k;
+    slot.used = ++clock_;
+    retire(slot);
+    clear_old();
+    hipError_t e = hipEventCreateWithFlags(&slot.g.done, hipEventDisableTiming);
     if (e != hipSuccess) return e;
-    e = hipGraphInstantiate(&exec_, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
+    hipGraph_t g = nullptr;
+    e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+      const hipError_t ee = enqueue();
+      e = hipStreamEndCapture(s, &g);
+      if (ee != hipSuccess) {
+        if (e == hipSuccess && g) (void)hipGraphDestroy(g);
+        e = ee;
+      } else if (e == hipSuccess) {
+        e = hipGraphInstantiate(&slot.g.exec, g, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(g);
+        if (e != hipSuccess) slot.g.exec = nullptr;
+      }
+    }
     if (e != hipSuccess) {
-      exec_ = nullptr;
+      slot.g.destroy();
       return e;
     }
-    key_ = key;
+    slot.key = key;
     *captured = true;
     return hipSuccess;
   }
 
-  hipError_t launch(hipStream_t s) { return hipGraphLaunch(exec_, s); }
-  bool holds(const GraphKey& key) const { return exec_ && key_.same(key); }
-
- private:
-  hipGraphExec_t exec_ = nullptr;
-  GraphKey key_;
-};
-
-// A few captured graphs, each with the host step state its replay leaves behind (Post); a new
-// key replaces the least recently used one.
-template <class Post, int N = 2>
-class GraphCache {
- public:
-  void reset() {
-    for (Slot& s : slot_) s.g.reset();
+  // Replays the graph of the last ensure().
+  hipError_t launch(hipStream_t s) {
+    GraphExec& g = slot_[cur_].g;
+    const hipError_t e = hipGraphLaunch(g.exec, s);
+    return e == hipSuccess ? hipEventRecord(g.done, s) : e;
   }
-  template <class F>
-  hipError_t ensure(const GraphKey& key, hipStream_t s, F&& enqueue, bool* captured) {
-    int k = -1;
-    for (int i = 0; i < N; ++i)
-      if (slot_[i].g.holds(key)) k = i;
-    if (k < 0) {
-      k = 0;
-      for (int i = 1; i < N; ++i)
-        if (slot_[i].used < slot_[k].used) k = i;
-    }
-    cur_ = k;
-    slot_[k].used = ++clock_;
-    return slot_[k].g.ensure(key, s, static_cast<F&&>(enqueue), captured);
-  }
-  // the graph of the last ensure()
-  hipError_t launch(hipStream_t s) { return slot_[cur_].g.launch(s); }
   Post& post() { return slot_[cur_].post; }
 
  private:
   struct Slot {
-    StepGraph g;
+    GraphExec g;
+    GraphKey key{};
     Post post{};
     unsigned long long used = 0;
   };
+  static constexpr int kOldMax = 8;  // kept by clear_old(), before the next of which at most N more come
+
+  void retire(Slot& s) {
+    if (s.g.exec) old_[nold_++] = s.g;
+    s.g = GraphExec{};
+  }
+  // Destroys the old graphs whose last replay has ended; waits for the oldest ones if there are many.
+  void clear_old() {
+    int kept = 0;
+    for (int i = 0; i < nold_; ++i) {
+      const hipError_t before = hipPeekAtLastError();
+      const bool ended = hipEventQuery(old_[i].done) == hipSuccess;
+      if (!ended && before == hipSuccess) (void)hipGetLastError();  // "not ready" is no error
+      if (ended || nold_ - i > kOldMax)
+        old_[i].destroy();
+      else
+        old_[kept++] = old_[i];
+    }
+    nold_ = kept;
+  }
+
   Slot slot_[N];
+  GraphExec old_[kOldMax + N];
+  int nold_ = 0;
   int cur_ = 0;
   unsigned long long clock_ = 0;
 };
