@@ -556,22 +556,14 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     const lbm_status st = bubble_half(ctx, p, s, nb, true);
     return st == LBM_OK ? from_hip(lbm::launch_step(ctx)) : st;
   };
-  // the last `single` of the n steps are not paired
-  auto steps = [&](int32_t n, int32_t single = 0) -> lbm_status {
+  auto steps = [&](int32_t n) -> lbm_status {
+    if (can_pair(ctx, p))
+      return lbm::steps_in_pairs(ctx->hs, ctx->in_order, true, n, [&] { return step_pair(ctx, p, s, nb); }, one);
     lbm_status st = LBM_OK;
-    if (can_pair(ctx, p)) {
-      auto two = [&] { return step_pair(ctx, p, s, nb); };
-      st = lbm::steps_in_pairs(ctx->hs, ctx->in_order, true, n - single, two, one);
-      n = single;
-    }
     for (int32_t i = 0; i < n && st == LBM_OK; ++i) st = one();
     return st;
   };
   if (graph_steps == 0 || nsteps < graph_steps || !ctx->stream) return steps(nsteps);
-  // A pair flips the population buffers once, so an odd number of pairs would need two graphs, one
-  // for each buffer: a graph of ten steps or more ends in two single ones instead (a shorter one
-  // is captured twice).
-  const int32_t single = graph_steps % 4 == 2 && graph_steps >= 10 ? 2 : 0;
   int32_t done = 0;
   while (nsteps - done >= graph_steps) {
     // the captured launches depend on the host step state (buffer and mask parities, which
@@ -589,7 +581,7 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     bool captured = false;
     hipError_t e = ctx->graph.ensure(key, ctx->stream,
                                      [&]() -> hipError_t {
-                                       st_cap = steps(graph_steps, single);
+                                       st_cap = steps(graph_steps);
                                        return st_cap == LBM_OK ? hipSuccess : hipErrorInvalidValue;
                                      },
                                      &captured);
