@@ -811,7 +811,8 @@ __global__ __launch_bounds__(kBlock, FUSE ? 2 : 1) void k_interp(Geo geo, Bubble
 // branches. With the library's log, exp, tanh, division and square root, in one lane, a sub-step took
 // 1.2 us, most of it these; it takes 0.5 us.
 
-// a / b and sqrt(a): the hardware approximation, two Newton steps and a residual correction.
+// a / b and sqrt(a): the hardware approximation, two Newton steps and a residual correction. An a that
+// overflowed stays infinite (or a NaN), so that a bubble that runs away still ends in a position that is reported.
 __device__ __forceinline__ double quick_div(double a, double b) {
   double r = __builtin_amdgcn_rcp(b);
   r = fma(r, fma(-b, r, 1.0), r);
@@ -826,7 +827,8 @@ __device__ __forceinline__ double quick_sqrt(double a) {
   g = fma(g, r, g);
   h = fma(h, r, h);
   g = fma(fma(-g, g, a), h, g);
-  return fma(fma(-g, g, a), h, g);
+  g = fma(fma(-g, g, a), h, g);
+  return a < INFINITY ? g : a;
 }
 
 // exp(f) - 1 for |f| <= ln(2)/2 by its Taylor series to f^14 (the next term is below 1e-18 of f).
@@ -886,7 +888,7 @@ __device__ __forceinline__ void drag_lift(const BubbleConst& k, int q, double ub
   const double Re = mag * k.re_scale;
   constexpr double ln2_hi = 0x1.62e42fefa3800p-1, ln2_lo = 0x1.ef35793c76730p-45;
   // exponents: 0.687 log Re, and 0.242 Re up to where tanh rounds to 1
-  const double y = q == 1 ? 2.0 * fmin(0.121 * Re, 25.0) : 0.687 * quick_log(fmax(Re, 1e-290));
+  const double y = q == 1 ? 2.0 * fmin(0.121 * Re, 25.0) : 0.687 * quick_log(fmin(fmax(Re, 1e-290), 1e290));
   const double n = rint(y * 1.4426950408889634074);
   const double f = fma(-n, ln2_lo, fma(-n, ln2_hi, y));
   const double p = __builtin_amdgcn_ldexp(1.0, (int)n), e = expm1_small(f);
