@@ -1072,8 +1072,8 @@ __global__ __launch_bounds__(64) void k_ode(Geo geo, BubbleArgs A) {
   // A lattice's slab words are met in LDS first: noted by every bubble, 20 000 bubbles' atomics on the same
   // few words took 47 of 70 us.
   constexpr bool kOne = std::is_same_v<Geo, OneColumn>;
-  __shared__ uint32_t s_note[2][kSlabWords / 2];
-  if (lane < kSlabWords) (&s_note[0][0])[lane] = 0u;
+  __shared__ uint32_t s_note[kSlabWords / 2];
+  if (lane < kSlabWords / 2) s_note[lane] = 0u;
   __syncthreads();
   if (b < A.nb) {  // whole quads
     OdeOut3 o;
@@ -1083,8 +1083,9 @@ __global__ __launch_bounds__(64) void k_ode(Geo geo, BubbleArgs A) {
       const double xn[3] = {quad<kQuad0>(o.xn), quad<kQuad1>(o.xn), quad<kQuad2>(o.xn)};
       ColumnView<float> col = geo.template view<float>(b);
       if constexpr (kOne) {
-        if (col.slab) col.slab = s_note[0];
-        if (col.slab_out) col.slab_out = s_note[1];
+        if (col.slab) col.slab = s_note;
+        col.slab_in = nullptr;  // overlapped pairs are updated in k_interp (kPairBesideMaxBubbles)
+        col.slab_out = nullptr;
       }
       Axis win[3];
       if (windows(col.G, x0, o.n, win)) mark_tiles<float>(col, A, win, xn, o.n, q, 4);
@@ -1092,11 +1093,7 @@ __global__ __launch_bounds__(64) void k_ode(Geo geo, BubbleArgs A) {
   }
   __syncthreads();
   if constexpr (kOne) {
-    if (lane < kSlabWords) {
-      const uint32_t v = (&s_note[0][0])[lane];
-      uint32_t* const w = lane < kSlabWords / 2 ? geo.slab : geo.slab_out;
-      if (v != 0u) slab_raise(w + lane % (kSlabWords / 2), v);
-    }
+    if (lane < kSlabWords / 2 && s_note[lane] != 0u) slab_raise(geo.slab + lane, s_note[lane]);
   }
 }
 
@@ -1565,6 +1562,7 @@ constexpr int kInterpLatencyMaxBubbles = 1024;
 // resident at once (two per compute unit).
 constexpr int kFuseMaxBubbles = 256;
 constexpr int kFuseMaxBubblesBatch = 512;
+static_assert(kPairBesideMaxBubbles <= kFuseMaxBubbles, "k_ode notes no box of an overlapped pair");
 
 template <typename Geo>
 constexpr int fuse_max_bubbles() {
