@@ -7,7 +7,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <functional>
 #include <new>
 #include <string.h>
 #include <vector>
@@ -234,14 +233,10 @@ bool batch_pairs_ok(const lbm_column* cols, int ncols, size_t elem, int flags) {
 // march more halo planes. Costs are in planes of full workgroups.
 void plan_pairs(const lbm_column* cols, int ncols, size_t elem, std::vector<Tiles2>& tiles,
                 std::vector<uint32_t>& blocks) {
-  struct Chunk {
-    double cost;  // of each tile
-    uint32_t col, ch;
-  };
-  constexpr int kXcds = 8;
+  constexpr int kXcds = 8, kCusXcd = kCus / kXcds;
   const double full = elem == 4 ? step2_threads<float>() : step2_threads<double>();
   constexpr double kLeast = 0.6, kStart = 1.0;  // of a plane, however few threads it takes; of a workgroup
-  std::vector<double> plane(ncols);
+  std::vector<double> plane(ncols), cost(ncols);  // of a plane and a chunk of each tile
   double total = 0.0;
   tiles.resize(ncols);
   for (int c = 0; c < ncols; ++c) {
@@ -254,46 +249,74 @@ void plan_pairs(const lbm_column* cols, int ncols, size_t elem, std::vector<Tile
     plane[c] = std::max(kLeast, tiles[c].ox * (tiles[c].oy + 2.0) / full);
     total += plane[c] * tiles[c].ntx * tiles[c].nty * G.nz;
   }
-  double best = 1e300;
-  std::vector<uint32_t> nchunk(ncols);
-  std::vector<Chunk> chunks;
+  std::vector<int> order(ncols);
   std::vector<uint32_t> xcd[kXcds];
-  for (double per_cu = 0.8; per_cu < 10.0; per_cu *= 1.06) {
+  // The columns in chunks of at most total / (kCus per_cu): the cost of the chunks, and a bound of the schedule's
+  // length (all of them spread evenly, or the longest).
+  auto cut = [&](double per_cu) {
     const double most = total / (kCus * per_cu);
-    chunks.clear();
+    double sum = 0.0, longest = 0.0;
     for (int c = 0; c < ncols; ++c) {
       const double nz = cols[c].nz;
-      nchunk[c] = (uint32_t)std::min(std::max(1.0, ceil(plane[c] * nz / most)), std::max(1.0, nz / 4));
-      for (uint32_t i = 0; i < nchunk[c]; ++i)
-        chunks.push_back({plane[c] * (nz / nchunk[c] + 2.0) + kStart, (uint32_t)c, i});
+      tiles[c].nchunk = (uint32_t)std::min(std::max(1.0, ceil(plane[c] * nz / most)), std::max(1.0, nz / 4));
+      cost[c] = plane[c] * (nz / tiles[c].nchunk + 2.0) + kStart;
+      sum += cost[c] * tiles[c].nchunk * tiles[c].ntx * tiles[c].nty;
+      longest = std::max(longest, cost[c]);
     }
-    std::stable_sort(chunks.begin(), chunks.end(), [](const Chunk& a, const Chunk& b) { return a.cost > b.cost; });
+    return std::max(sum / kCus, longest);
+  };
+  // The length of that schedule, or of its beginning once it is no shorter than `best`; keep: its workgroups by XCD.
+  auto play = [&](double best, bool keep) {
+    for (int c = 0; c < ncols; ++c) order[c] = c;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
     double load[kXcds] = {}, end = 0.0;
-    std::vector<double> cu(kCus, 0.0);  // the time each compute unit is free, a heap per XCD
-    for (auto& l : xcd) l.clear();
-    for (const Chunk& k : chunks) {
-      const int x = (int)(std::min_element(load, load + kXcds) - load);
-      const uint32_t nt = tiles[k.col].ntx * tiles[k.col].nty;
-      load[x] += k.cost * nt;
-      for (uint32_t i = 0; i < nt; ++i) {
-        xcd[x].push_back(k.col);
-        xcd[x].push_back(k.ch * nt + i);
-        const auto lo = cu.begin() + x * (kCus / kXcds), hi = lo + kCus / kXcds;
-        std::pop_heap(lo, hi, std::greater<double>());
-        end = std::max(end, *(hi - 1) += k.cost);
-        std::push_heap(lo, hi, std::greater<double>());
+    double cu[kXcds][kCusXcd] = {};  // the time each compute unit is free, a heap per XCD
+    for (const int c : order) {
+      const uint32_t nt = tiles[c].ntx * tiles[c].nty;
+      for (uint32_t ch = 0; ch < tiles[c].nchunk; ++ch) {
+        const int x = (int)(std::min_element(load, load + kXcds) - load);
+        load[x] += cost[c] * nt;
+        for (uint32_t i = 0; i < nt; ++i) {
+          if (keep) {
+            xcd[x].push_back((uint32_t)c);
+            xcd[x].push_back(ch * nt + i);
+          }
+          // the compute unit free first, at the top of the heap, takes the workgroup
+          double* const h = cu[x];
+          const double t = h[0] + cost[c];
+          int k = 0;
+          for (int m = 1; m < kCusXcd; m = 2 * k + 1) {
+            if (m + 1 < kCusXcd && h[m + 1] < h[m]) ++m;
+            if (h[m] >= t) break;
+            h[k] = h[m];
+            k = m;
+          }
+          h[k] = t;
+          end = std::max(end, t);
+        }
+        if (end >= best) return end;
       }
     }
+    return end;
+  };
+  double best = 1e300, best_per_cu = 0.0, last = 0.0;
+  for (double per_cu = 0.8; per_cu < 10.0; per_cu *= 1.06) {
+    const double least = cut(per_cu);
+    if (least >= best || least == last) continue;  // no shorter, or the same chunks as before
+    last = least;
+    const double end = play(best, false);
     if (end < best) {
       best = end;
-      size_t longest = 0;
-      for (const auto& l : xcd) longest = std::max(longest, l.size() / 2);
-      blocks.assign(longest * 2 * kXcds, kNoColumn);
-      for (int x = 0; x < kXcds; ++x)
-        for (size_t j = 0; j < xcd[x].size(); ++j) blocks[(j / 2 * kXcds + x) * 2 + j % 2] = xcd[x][j];
-      for (int c = 0; c < ncols; ++c) tiles[c].nchunk = nchunk[c];
+      best_per_cu = per_cu;
     }
   }
+  cut(best_per_cu);
+  play(1e300, true);
+  size_t longest = 0;
+  for (const auto& l : xcd) longest = std::max(longest, l.size() / 2);
+  blocks.assign(longest * 2 * kXcds, kNoColumn);
+  for (int x = 0; x < kXcds; ++x)
+    for (size_t j = 0; j < xcd[x].size(); ++j) blocks[(j / 2 * kXcds + x) * 2 + j % 2] = xcd[x][j];
 }
 
 struct BatchLayout {
