@@ -449,8 +449,9 @@ typedef struct {
 
 typedef struct lbm_batch lbm_batch;
 
-/* Batches of 2^20 cells or more with walls on every face also take a middle buffer as large as one
- * state in scratch (two steps per launch, see lbm_batch_step). */
+/* Batches of 2^20 cells or more with walls on every face, whose columns are not narrow (planes of 1536 bytes per
+ * population in the mean over the cells, 1024 without bubbles), also take a middle buffer as large as one state
+ * in scratch (two steps per launch, see lbm_batch_step). */
 lbm_status lbm_batch_bytes_required(const lbm_column* cols, int32_t ncols, int32_t precision,
                                     size_t* pool_bytes, size_t* scratch_bytes);
 /* Lay the columns out in pool, initialise every population to g = 0 and the fields to 0. The call
@@ -478,7 +479,7 @@ lbm_status lbm_batch_get_step_occupancy(lbm_batch* batch, int32_t* workgroups_pe
 lbm_status lbm_batch_set_persistent(lbm_batch* batch, int32_t enable);
 lbm_status lbm_batch_get_persistent(lbm_batch* batch, int32_t* enabled, int32_t* grid);
 /* nsteps method steps of every column (eager launches). nb must equal the total bubble count. Where
- * every face is a wall and the batch holds 2^20 cells or more, steps are taken in pairs (two liquid
+ * lbm_batch_bytes_required() has a middle buffer, steps are taken in pairs (two liquid
  * steps per launch, the same results), an odd last one by itself; a pair swaps the state buffers once
  * (lbm_batch_column names the current one), unless the caller has captured steps into a graph of its own: then
  * nsteps steps leave the state in the buffer that nsteps swaps leave it in. */

@@ -207,22 +207,33 @@ bool column_ok(const lbm_column& c) {
 }
 
 // Batches from this size on take their method steps in pairs: 4 columns of 36 to 44 cells across, 0.8M
-// cells, 52 us per step one by one and 55 in pairs; 48 of 16 to 24, 1.1M, 70 and 69; 6 of 40 to 60, 2.2M,
-// 106 and 89; 48 of 24 to 96, 30M, 900 and 669; the nine tanks of Table 5, 7M, 246 and 175.
+// cells, 52 us per step one by one and 55 in pairs; 6 of 40 to 60, 2.2M, 106 and 89; 48 of 24 to 96, 30M, 900 and
+// 669; the nine tanks of Table 5, 7M, 246 and 175.
 constexpr size_t kBatchPairMinCells = 1u << 20;
+// The planes of narrow columns fill a small part of a workgroup, and their bubbles reach most of their cells, so
+// the plane a cell lies in must also hold this many bytes in the mean (of one population; with bubbles, and
+// without). Per step one by one and in pairs, one bubble each: FP32 300 columns of 12 to 20 cells across
+// 151 us and 161, 200 of 16 to 20 (1300 B) 135 and 135, 1000 of 16 to 24 (1600 B) 810 and 686, 100 of 20 to 24 123 and 110;
+// FP64 600 of 12 to 14 (1350 B) 255 and 283, 300 of 12 to 20 (2100 B) 236 and 214. No bubbles: FP32 300 of 12 to 20
+// (1050 B) 108 and 105, 1500 of 8 to 11 115 and 254; FP64 600 of 12 to 14 194 and 163, 1500 of 8 to 11 (720 B) 182 and 266.
+constexpr double kBatchPairMinPlane = 1536.0, kBatchPairMinPlaneLiquid = 1024.0;
 
 // As pairs_ok() of a single lattice, for every column.
 bool batch_pairs_ok(const lbm_column* cols, int ncols, size_t elem, int flags) {
   if (flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL)) return false;
   size_t total = 0;
+  double planes = 0.0;
+  bool bubbles = false;
   for (int c = 0; c < ncols; ++c) {
     for (int f = 0; f < 6; ++f)
       if (cols[c].bc[f] == LBM_BC_PERIODIC) return false;
     const size_t n = (size_t)cols[c].nx * cols[c].ny * cols[c].nz;
     if (19 * n * elem > 0xffffffffull) return false;
     total += n;
+    planes += (double)n * cols[c].nx * cols[c].ny * elem;
+    bubbles = bubbles || cols[c].nb > 0;
   }
-  return total >= kBatchPairMinCells;
+  return total >= kBatchPairMinCells && planes >= total * (bubbles ? kBatchPairMinPlane : kBatchPairMinPlaneLiquid);
 }
 
 // The workgroups of the two-step launch: a column's tiles are the cheapest of a lattice of its size, its
