@@ -144,9 +144,8 @@ typedef struct lbm_ctx lbm_ctx;
 #define LBM_MAX_STENCIL 64
 
 /* Sizes, in bytes, of one population buffer (19 x cells), of one vector field (3 x cells:
- * force or velocity) and of the scratch buffer (tile masks, reduction partials and, for lattices of
- * 3 2^18 cells (FP32; FP64 3 2^17) or more with walls on every face, one more population buffer that
- * pairs of method steps pass through, see lbm_run). */
+ * force or velocity) and of the scratch buffer (tile masks, reduction partials and, for lattices that
+ * lbm_run() may step in pairs, one more population buffer that those pass through). */
 lbm_status lbm_bytes_required(const lbm_desc* desc, size_t* pop_buffer_bytes,
                               size_t* field_bytes, size_t* scratch_bytes);
 
@@ -208,8 +207,9 @@ lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells);
  * forcing (13), BGK collision (14), Guo forcing (12), (15), streaming (16). Each step reads the
  * force field where bubbles have spread force (or everywhere with LBM_FLAG_STATIC_FORCE),
  * writes the collision velocity U of eq. (13) there (or everywhere with LBM_FLAG_WRITE_U_ALL)
- * and clears the force it used. Lattices of 9 2^16 cells (FP32; FP64 2^17) or more advance two steps per
- * launch where nsteps allows (with one cell per thread, lbm_set_launch), the same results bit for bit. A launch
+ * and clears the force it used. Lattices of 9 2^16 cells (FP32; FP64 2^17) or more, unless so narrow
+ * that single steps are faster, advance two steps per launch where nsteps allows (with one cell per thread,
+ * lbm_set_launch), the same results bit for bit. A launch
  * swaps the two population buffers, whether it takes one step or two (lbm_state_buffer names the current one);
  * once the caller has bound buffers (lbm_bind_buffers) or captured steps into a graph of its own, nsteps steps
  * leave the state in the buffer that nsteps swaps leave it in. */
@@ -275,7 +275,7 @@ lbm_status lbm_check(lbm_ctx* ctx);
  * while params, soa and nb stay the same. graph_steps must be even (the step alternates two
  * population buffers), 0 runs every step eagerly. Graph capture needs a non-NULL stream. Lattices of
  * 3 2^18 cells (FP32; FP64 3 2^17) or more with walls on every face (no flag but LBM_FLAG_PLAIN_SOA,
- * one cell per thread, not the exact-time coupling) take their steps in pairs: the rows and planes the bubbles reach one
+ * one cell per thread, not the exact-time coupling) take their steps in pairs where that is faster: the rows and planes the bubbles reach one
  * step at a time, the others both steps in one launch; the same results bit for bit; as for
  * lbm_step(), a pair swaps the population buffers once, unless the caller has bound buffers or captured steps. */
 lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* params, const bubble_soa* soa, int32_t nb,

@@ -38,14 +38,27 @@ bool desc_ok(const lbm_desc* d) {
   return true;
 }
 
-// Lattices whose method steps lbm_run() takes in pairs (step2.hip): walls on every face, 32-bit byte
-// offsets, no flag that has every cell read its force or write its velocity.
-bool pairs_ok(const lbm_desc* d) {
-  for (int f = 0; f < 6; ++f)
-    if (d->bc[f] == LBM_BC_PERIODIC) return false;
-  const size_t cells = (size_t)d->nx * d->ny * d->nz, elem = d->precision == LBM_FP32_SHIFTED ? 4 : 8;
-  return cells >= lbm::pair_min_cells(elem) && 19 * cells * elem <= 0xffffffffull &&
-         !(d->flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL));
+lbm::Geom geom_of(const lbm_desc* d) {
+  lbm::Geom G;
+  memset(&G, 0, sizeof(G));
+  G.nx = d->nx;
+  G.ny = d->ny;
+  G.nz = d->nz;
+  G.N = (uint32_t)d->nx * d->ny * d->nz;
+  G.plane = (uint32_t)d->nx * d->ny;
+  lbm::set_layout(G, (d->flags & LBM_FLAG_PLAIN_SOA) != 0);
+  const size_t elem = d->precision == LBM_FP32_SHIFTED ? 4 : 8;
+  lbm::set_stores(G, elem, 19 * (size_t)G.N * elem);
+  for (int f = 0; f < 6; ++f) G.bc[f] = d->bc[f];
+  return G;
+}
+
+// The two-step launches of a lattice. With a flag that has every cell read its force or write its velocity
+// lbm_run() takes single steps.
+lbm::Pairs pairs_of(const lbm_desc* d) {
+  lbm::Pairs p = lbm::choose_pairs(geom_of(d), d->precision == LBM_FP32_SHIFTED ? 4 : 8);
+  if (d->flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL)) p.serial = p.overlapped = false;
+  return p;
 }
 
 Layout layout_of(const lbm_desc* d) {
@@ -76,7 +89,8 @@ Layout layout_of(const lbm_desc* d) {
   // the middle buffer of pairs of method steps, for the lattices that can take them
   L.mid = L.init;
   const size_t elem = d->precision == LBM_FP32_SHIFTED ? 4 : 8;
-  L.total = L.init + (pairs_ok(d) ? align_up(19 * (size_t)cells * elem) : 0);
+  const lbm::Pairs p = pairs_of(d);
+  L.total = L.init + (p.serial || p.overlapped ? align_up(19 * (size_t)cells * elem) : 0);
   return L;
 }
 
@@ -133,16 +147,8 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   if (!c) return LBM_EDEVICE;
   c->desc = *desc;
   const Layout L = layout_of(desc);
+  c->geom = geom_of(desc);
   lbm::Geom& G = c->geom;
-  G.nx = desc->nx;
-  G.ny = desc->ny;
-  G.nz = desc->nz;
-  G.N = (uint32_t)desc->nx * desc->ny * desc->nz;
-  G.plane = (uint32_t)desc->nx * desc->ny;
-  lbm::set_layout(G, (desc->flags & LBM_FLAG_PLAIN_SOA) != 0);
-  const size_t elem = desc->precision == LBM_FP32_SHIFTED ? 4 : 8;
-  lbm::set_stores(G, elem, 19 * (size_t)G.N * elem);
-  for (int f = 0; f < 6; ++f) G.bc[f] = desc->bc[f];
   G.tnx = (int)L.tnx;
   G.tny = (int)L.tny;
   c->general = false;
@@ -179,11 +185,8 @@ lbm_status lbm_init(const lbm_desc* desc, void* pops_a, void* pops_b, void* forc
   c->traj_rows = 0;
   c->traj_row = reinterpret_cast<uint32_t*>(s + L.traj_row);
   c->slab = reinterpret_cast<uint32_t*>(s + L.slab);
-  c->pops[2] = pairs_ok(desc) ? s + L.mid : nullptr;
-  if (G.N < lbm::step2_min_cells(c->elem) || !lbm::bb_fast_ok(G, c->elem) ||
-      !lbm::choose_tiles2(G, c->elem, lbm::kCus, &c->tiles2) ||
-      !lbm::choose_tiles2(G, c->elem, lbm::kCusBeside, &c->tiles2_beside))
-    c->tiles2 = c->tiles2_beside = lbm::Tiles2{};
+  c->pairs = pairs_of(desc);
+  c->pops[2] = c->pairs.serial || c->pairs.overlapped ? s + L.mid : nullptr;
   c->nred = L.nred;
   c->bins_clean = false;
   c->stream = static_cast<hipStream_t>(stream);
@@ -295,7 +298,7 @@ lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells) {
       return LBM_EDEVICE;
     if (w[1] == 0) return LBM_OK;
     // as slab_box() has it: whole force tiles, rows in multiples of the pass's tiles
-    const int64_t t = lbm::kTile, oy = ctx->tiles2_beside.oy;
+    const int64_t t = lbm::kTile, oy = ctx->pairs.beside.oy;
     const int64_t za = std::max<int64_t>(0, (int32_t)(lbm::kSlabBase - w[0])) / t * t;
     const int64_t zb = std::min<int64_t>(ctx->geom.nz, ((int64_t)w[1] + t - 1) / t * t);
     const int64_t ya = std::max<int64_t>(0, (int32_t)(lbm::kSlabBase - w[2])) / t * t / oy * oy;
@@ -367,9 +370,14 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x) {
   return LBM_OK;
 }
 
+// A caller that captures steps has its graph name the buffers of now.
+static void note_capture(lbm_ctx* ctx) {
+  if (ctx->pairs.alone.ox != 0 && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
+}
+
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
   if (!ctx || nsteps < 0) return LBM_EINVAL;
-  if (lbm::can_step2(ctx) && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
+  note_capture(ctx);
   auto one = [&] { return lbm::launch_step(ctx); };
   hipError_t e = hipSuccess;
   // a force spread by a bubble half belongs to the first step
@@ -377,7 +385,7 @@ lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
     e = one();
     --nsteps;
   }
-  if (e == hipSuccess && lbm::can_step2(ctx))
+  if (e == hipSuccess && ctx->pairs.liquid && lbm::can_step2(ctx))
     return from_hip(lbm::steps_in_pairs(ctx->hs, ctx->in_order, ctx->pops[2] != nullptr, nsteps,
                                         [&] { return lbm::launch_step2(ctx, nullptr); }, one));
   for (int32_t i = 0; i < nsteps && e == hipSuccess; ++i) e = one();
@@ -416,15 +424,15 @@ lbm_status bubble_half(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s
   return from_hip(lbm::launch_bubbles(ctx, p, s, nb, overlap, in_run, slab, slab_clear));
 }
 
-// lbm_run() takes the method steps of this lattice in pairs (the exact-time coupling reads the whole
-// state between the two).
-bool can_pair(const lbm_ctx* ctx, const bubble_params* p) {
-  return ctx->pops[2] && lbm::can_step2(ctx) && !(p->coupling & LBM_COUPLING_EXACT_TIME);
-}
-
 // Pairs run the bubble kernels beside the liquid's two steps.
 bool pair_beside(const lbm_ctx* ctx, int32_t nb) {
   return ctx->overlap && nb > 0 && nb <= lbm::kPairBesideMaxBubbles && lbm::can_overlap(ctx);
+}
+
+// lbm_run() takes its steps in pairs (the exact-time coupling reads the whole state between the two).
+bool can_pair(const lbm_ctx* ctx, const bubble_params* p, int32_t nb) {
+  if (!ctx->pops[2] || !lbm::can_step2(ctx) || (p->coupling & LBM_COUPLING_EXACT_TIME)) return false;
+  return nb == 0 ? ctx->pairs.liquid : pair_beside(ctx, nb) ? ctx->pairs.overlapped : ctx->pairs.serial;
 }
 
 // Two method steps (see step2.hip).
@@ -551,13 +559,13 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
   ctx->hs.marked = ctx->hs.slab_marked = false;  // the bubble state may have changed since the last call
   const lbm_status ok = check_half(ctx, p, s, nb);
   if (ok != LBM_OK && nsteps > 0) return ok;
-  if (lbm::can_step2(ctx) && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
+  note_capture(ctx);
   auto one = [&]() -> lbm_status {
     const lbm_status st = bubble_half(ctx, p, s, nb, true);
     return st == LBM_OK ? from_hip(lbm::launch_step(ctx)) : st;
   };
   auto steps = [&](int32_t n) -> lbm_status {
-    if (can_pair(ctx, p))
+    if (can_pair(ctx, p, nb))
       return lbm::steps_in_pairs(ctx->hs, ctx->in_order, true, n, [&] { return step_pair(ctx, p, s, nb); }, one);
     lbm_status st = LBM_OK;
     for (int32_t i = 0; i < n && st == LBM_OK; ++i) st = one();

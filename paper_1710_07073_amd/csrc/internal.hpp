@@ -16,6 +16,12 @@ namespace lbm {
 struct Tiles2 {
   uint32_t ox, oy, ntx, nty, nchunk;
 };
+// A lattice's two-step launches: the tiles with the chip to itself and beside the bubble kernels, and which steps
+// they take (lbm_step; lbm_run with the parts of a pair one after the other, and overlapped).
+struct Pairs {
+  Tiles2 alone, beside;
+  bool liquid, serial, overlapped;
+};
 
 // Host-side step state of a context: which buffers and masks the next launches use.
 struct HostState {
@@ -46,7 +52,7 @@ struct lbm_ctx {
   void* force;
   void* vel;
   uint32_t* slab;  // slab words, kSlabWords per pair parity
-  lbm::Tiles2 tiles2, tiles2_beside;  // with the chip to itself, and beside the bubble kernels
+  lbm::Pairs pairs;
   // Two tile masks, one byte per 8^3 tile (force present / velocity needed). bubbles_step()
   // writes mask[flag_cur ^ 1] and makes it current; each liquid step reads mask[flag_cur] and
   // clears the other one for the next bubble step.
@@ -289,11 +295,8 @@ constexpr int kPairBesideMaxBubbles = 256;
 // Lattices from this size on overlap the bubble kernels with the liquid step by default.
 constexpr uint32_t kOverlapMinCells = 1u << 22;
 
-// Lattices from these sizes on are advanced two steps per launch, alone and with bubbles. Alone, the
-// shorter chunks of a small lattice lose to their halo planes. Per step, one by one and in pairs:
-// 48 x 48 x 144 FP32 10.3 us and 12.0, 64 x 64 x 128 13.8 and 14.7, 60 x 60 x 180 17.9 and 16.1,
-// 64 x 64 x 192 19.7 and 15.0; 32 x 64 x 64 FP64 with periodic axes 15.1 and 12.4, 48 x 48 x 144 18.2 and 14.8.
-// With bubbles the slab launch comes on top (about 5 us per pair).
+// Lattices from these sizes on may be advanced two steps per launch, alone and with bubbles; whether they are
+// follows from choose_pairs().
 constexpr uint32_t step2_min_cells(size_t elem) { return elem == 4 ? 9u << 16 : 1u << 17; }
 constexpr uint32_t pair_min_cells(size_t elem) { return elem == 4 ? 3u << 18 : 3u << 17; }
 
@@ -316,7 +319,9 @@ hipError_t launch_bulk(lbm_ctx* c);
 // step2.hip
 // Tiles for a launch on so many compute units.
 bool choose_tiles2(const Geom& G, size_t elem, uint32_t cus, Tiles2* best);
-// The liquid can be advanced two steps per launch.
+// The two-step launches of a lattice (its extents, faces and choice of stores).
+Pairs choose_pairs(const Geom& G, size_t elem);
+// The launch shape is that of the two-step launches.
 bool can_step2(const lbm_ctx* c);
 // Two liquid steps in one launch. slab (null: no bubbles, no force but a static one): the slab
 // words of the pair of method steps this launch ends.

@@ -71,6 +71,42 @@ bool choose_tiles2(const Geom& G, size_t elem, uint32_t cus, Tiles2* best) {
   return cost < 1e30;
 }
 
+// Microseconds of a launch of two steps and of two launches of one, fitted to 360 lattices of 0.13 to 3 million
+// cells (FP32 and FP64, walls, free-slip tops and periodic axes, 4 to 3000 cells wide; all but 3 % of the
+// choices between the two are the faster one or within 10 % of it). A workgroup takes as long for a plane however
+// few threads it has, so narrow lattices lose: 8 x 8 x 20000 FP32 with a free-slip top 233 us against 59 us,
+// 16 x 16 x 4000 59 and 50, 32 x 32 x 800 58 and 42; 64 x 64 x 192 30 and 35 with walls, 38 and 38 with that top,
+// 37 and 44 periodic; 128 x 100 x 100 41 and 56; 48 x 48 x 144 FP64 29 and 35, 64 x 64 x 192 49 and 68.
+Pairs choose_pairs(const Geom& G, size_t elem) {
+  Pairs p = {};
+  if (G.N < step2_min_cells(elem) || !bb_fast_ok(G, elem) || !choose_tiles2(G, elem, kCus, &p.alone) ||
+      !choose_tiles2(G, elem, kCusBeside, &p.beside)) {
+    p.alone = p.beside = Tiles2{};
+    return p;
+  }
+  bool walls = true, periodic = false;
+  for (int f = 0; f < 6; ++f) {
+    walls = walls && G.bc[f] == BC_BB;
+    periodic = periodic || G.bc[f] == BC_PER;
+  }
+  const double mb = 38e-6 * elem;  // a step's bytes per cell, in millions
+  const double chunk = p.alone.nchunk == 1 ? G.nz + 1.0 : div_up(G.nz, p.alone.nchunk) + 2.0;
+  const double planes = div_up(p.alone.ntx * p.alone.nty * p.alone.nchunk, kCus) * chunk;
+  const double two = (walls ? 8.0 : 7.0) + (walls ? 1.7 : 2.55) * planes + (G.stream1 ? 0.125 : 0.07) * mb * G.N;
+  const double rate = G.stream1 ? (periodic ? 0.24 : 0.16) : periodic ? 0.14 : walls ? 0.112 : 0.127;
+  const double singles = 2.0 * ((periodic ? 7.0 : 5.0) + rate * mb * G.N);
+  p.liquid = two < singles;
+  if (periodic || G.N < pair_min_cells(elem)) return p;
+  // with bubbles: the slab's two steps on top, of rows across all x (2000 x 8 x 60 FP32, one bubble: 95 us in a
+  // pair, 79 in two steps; 64 x 64 x 200 74 and 75, with a free-slip top 81 and 78; 72 x 72 x 216 81 and 90, 86 and
+  // 92). Overlapped single steps take some 30 us a pair longer than serial ones (the region launch and the
+  // waits), overlapped pairs do not: 64 x 64 x 200 71 and 102.
+  const double slab = 3.0 + 0.3 * mb * G.nx * std::min(G.ny, 16) * std::min(G.nz, 16);
+  p.serial = two + slab < singles;
+  p.overlapped = two + slab < singles + 30.0;
+  return p;
+}
+
 namespace {
 
 template <typename T, int FACES, bool FORCE>
@@ -91,7 +127,7 @@ hipError_t launch_typed(lbm_ctx* c, const uint32_t* slab, bool bulk) {
   A.ntiles = c->ntiles;
   A.dirty = c->hs.flag_clean[c->hs.flag_cur] ? 0 : 1;
   A.bulk = bulk ? 1 : 0;
-  A.L = bulk ? c->tiles2_beside : c->tiles2;
+  A.L = bulk ? c->pairs.beside : c->pairs.alone;
   const uint32_t n = A.L.ntx * A.L.nty * A.L.nchunk;
   hipLaunchKernelGGL((k_step2<T, FACES, FORCE>), dim3(n), dim3(step2_threads<T>()), 0, c->stream, A);
   return hipGetLastError();
@@ -119,7 +155,7 @@ hipError_t launch_slab_typed(lbm_ctx* c, const uint32_t* slab, int part, hipStre
   const SlabArgs<T> A = {static_cast<const T*>(src), static_cast<T*>(dst), static_cast<T*>(c->force),
                          static_cast<T*>(c->vel), c->tiles[c->hs.flag_cur], c->tiles[c->hs.flag_cur ^ 1], slab, G,
                          (T)c->desc.omega, c->desc.flags, c->ntiles,
-                         part == SLAB_FIRST ? c->tiles2.oy : c->tiles2_beside.oy, part};
+                         part == SLAB_FIRST ? c->pairs.alone.oy : c->pairs.beside.oy, part};
   hipLaunchKernelGGL((k_slab<T, FS>), dim3(std::min(div_up(G.N, 256), 2048u)), dim3(256),
                      part == SLAB_FIRST_WHOLE ? 0 : step_lds(c), s, A);
   return hipGetLastError();
@@ -139,7 +175,7 @@ hipError_t launch_slab_part(lbm_ctx* c, const uint32_t* slab, int part, hipStrea
 }  // namespace
 
 bool can_step2(const lbm_ctx* c) {
-  return c->tiles2.ox != 0 && c->step_vec == 1;
+  return c->pairs.alone.ox != 0 && c->step_vec == 1;
 }
 
 hipError_t launch_step2(lbm_ctx* c, const uint32_t* slab) {
