@@ -172,10 +172,12 @@ hipError_t moments_typed(lbm_ctx* c, void* rho, void* u) {
 
 template <typename T, int FACES>
 hipError_t populations_typed(lbm_ctx* c, void* out) {
-  // a copy of the state (128 x 128 x 512 FP32 208 us, 6.1 TB/s, in the 5 workgroups per compute unit the
-  // liquid step runs with; 223 us uncapped, 220 in 3)
+  // A copy of the state. Beyond the caches in the 5 workgroups per compute unit the FP32 liquid step runs with
+  // (128 x 128 x 512 FP32 209 us, 6.1 TB/s, 224 us uncapped, 206 us in 3, but 330 us with periodic axes along y and
+  // z; FP64 441, 447 and 429 us, 447, 474 and 466 us); uncapped where it fits in them (64 x 64 x 192 with such
+  // axes 17.5 us, 19.5 in 5).
   hipLaunchKernelGGL((k_populations<T, FACES>), dim3(div_up(c->geom.N, kThreads)), dim3(kThreads),
-                     occupancy_lds(c->lds_per_cu, kDefaultStepWgsF32), c->stream,
+                     c->geom.stream1 ? occupancy_lds(c->lds_per_cu, 5) : 0, c->stream,
                      static_cast<const T*>(c->pops[c->hs.cur]), static_cast<T*>(out), c->geom);
   return hipGetLastError();
 }
