@@ -811,8 +811,8 @@ __global__ __launch_bounds__(kBlock, FUSE ? 2 : 1) void k_interp(Geo geo, Bubble
 // branches. With the library's log, exp, tanh, division and square root, in one lane, a sub-step took
 // 1.2 us, most of it these; it takes 0.5 us.
 
-// a / b and sqrt(a): the hardware approximation, two Newton steps and a residual correction. An a that
-// overflowed stays infinite (or a NaN), so that a bubble that runs away still ends in a position that is reported.
+// a / b and sqrt(a): the hardware approximation, two Newton steps and a residual correction. The root of an a that
+// overflowed is a NaN.
 __device__ __forceinline__ double quick_div(double a, double b) {
   double r = __builtin_amdgcn_rcp(b);
   r = fma(r, fma(-b, r, 1.0), r);
@@ -827,9 +827,12 @@ __device__ __forceinline__ double quick_sqrt(double a) {
   g = fma(g, r, g);
   h = fma(h, r, h);
   g = fma(fma(-g, g, a), h, g);
-  g = fma(fma(-g, g, a), h, g);
-  return a < INFINITY ? g : a;
+  return fma(fma(-g, g, a), h, g);
 }
+
+// ln 2 in two parts (the reduction of Cody and Waite): a multiple of the first, 42 bits long, is exact for the
+// exponents that occur, the second is the rest of it.
+constexpr double kLn2Hi = 0x1.62e42fefa3800p-1, kLn2Lo = 0x1.ef35793c76730p-45;
 
 // exp(f) - 1 for |f| <= ln(2)/2 by its Taylor series to f^14 (the next term is below 1e-18 of f).
 __device__ __forceinline__ double expm1_small(double f) {
@@ -856,8 +859,7 @@ __device__ __forceinline__ double quick_log(double a) {
   const double a4 = fma(t, 2.0 / 21.0, 2.0 / 19.0);
   const double b0 = fma(a1, t2, a0), b1 = fma(a3, t2, a2);
   const double series = fma(fma(a4, t4, b1), t4, b0);  // log m = 2 s + s t series
-  constexpr double ln2_hi = 0x1.62e42fefa3800p-1, ln2_lo = 0x1.ef35793c76730p-45;
-  return fma((double)e, ln2_hi, fma((double)e, ln2_lo, fma(s * t, series, s + s)));
+  return fma((double)e, kLn2Hi, fma((double)e, kLn2Lo, fma(s * t, series, s + s)));
 }
 
 // v of the lanes of the quad that SEL names (two bits per lane).
@@ -886,18 +888,19 @@ __device__ __forceinline__ void drag_lift(const BubbleConst& k, int q, double ub
   const double ux = quad<kQuad0>(ur), uy = quad<kQuad1>(ur), uz = quad<kQuad2>(ur);
   const double mag = quick_sqrt(fma(ux, ux, fma(uy, uy, uz * uz)));
   const double Re = mag * k.re_scale;
-  constexpr double ln2_hi = 0x1.62e42fefa3800p-1, ln2_lo = 0x1.ef35793c76730p-45;
   // exponents: 0.687 log Re, and 0.242 Re up to where tanh rounds to 1
-  const double y = q == 1 ? 2.0 * fmin(0.121 * Re, 25.0) : 0.687 * quick_log(fmin(fmax(Re, 1e-290), 1e290));
+  const double y = q == 1 ? 2.0 * fmin(0.121 * Re, 25.0) : 0.687 * quick_log(fmax(Re, 1e-290));
   const double n = rint(y * 1.4426950408889634074);
-  const double f = fma(-n, ln2_lo, fma(-n, ln2_hi, y));
+  const double f = fma(-n, kLn2Lo, fma(-n, kLn2Hi, y));
   const double p = __builtin_amdgcn_ldexp(1.0, (int)n), e = expm1_small(f);
   const double w = fma(p, e, p - 1.0);
   const double value = q == 1 ? quick_div(w, w + 2.0) : fma(p, e, p);
   const double pw = quad<kQuad0>(value), th = quad<kQuad1>(value);
   const double viscous = fmin(k.visc24 * fma(k.cd_k, pw, 1.0), k.visc48);
   const double visc = Re < k.re_sat ? viscous : k.visc48;
-  const double cdu = fmax(visc, k.shape * mag);
+  // not a maximum, which would drop a NaN: a bubble that runs away ends in a position that is reported
+  const double form = k.shape * mag;
+  const double cdu = form < visc ? visc : form;
   const double rising = fmin(0.288 * th, k.f_lift);
   const double cl = k.Eod < 4.0 ? rising : (k.Eod <= 10.0 ? k.f_lift : -0.29);
   FD = k.drag * cdu * ur;

@@ -5,17 +5,12 @@
 
 #include "collide.hpp"
 #include "step2_cell.hpp"
+#include "wave.hpp"
 
 namespace lbm {
 namespace {
 
 constexpr int kThreads = 256;
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 // The 19 populations arriving at a cell. With walls only (and 32-bit byte offsets) as the
 // liquid step pulls them: with the general pull k_moments was held by its address arithmetic.
