@@ -95,10 +95,9 @@ struct lbm_ctx {
   uint32_t step_bx;  // threads per workgroup along x (the workgroup has 256 threads)
   int32_t step_wgs;  // at most this many liquid-step workgroups per compute unit (0: no cap)
   uint32_t lds_per_cu;  // LDS bytes of one compute unit
-  // captured method steps (lbm_run), with the host state their replay leaves. Four: an odd number of pairs
-  // flips the population buffers and the slab words, so it takes two graphs, and the first replay of a call
-  // two more, as no box is marked ahead then. (Ten steps overlapped on 128 x 128 x 512 FP32 in graphs of 4 pairs
-  // and two single steps, which need half as many: 1986 us against 1905, each graph more 0.1 to 0.5 ms once.)
+  // captured method steps (lbm_run), with the host state their replay leaves. Four: graphs of 2 and 6 steps are of an
+  // odd number of pairs, which flips the population buffers and the slab words, so two belong together, and the
+  // first replay of a call takes two more, as no box is marked ahead then.
   lbm::GraphCache<lbm::HostState, 4> graph;
   // device address of the library's own per-bubble workspace on this context's device
   // (bubbles_step_static_work), null if it could not be resolved
