@@ -898,12 +898,11 @@ __device__ __forceinline__ void drag_lift(const BubbleConst& k, int q, double ub
   const double pw = quad<kQuad0>(value), th = quad<kQuad1>(value);
   const double viscous = fmin(k.visc24 * fma(k.cd_k, pw, 1.0), k.visc48);
   const double visc = Re < k.re_sat ? viscous : k.visc48;
-  // not a maximum, which would drop a NaN: a bubble that runs away ends in a position that is reported
-  const double form = k.shape * mag;
-  const double cdu = form < visc ? visc : form;
+  const double cdu = fmax(visc, k.shape * mag);
   const double rising = fmin(0.288 * th, k.f_lift);
   const double cl = k.Eod < 4.0 ? rising : (k.Eod <= 10.0 ? k.f_lift : -0.29);
-  FD = k.drag * cdu * ur;
+  // the maximum drops a NaN, this keeps it: a bubble that runs away ends in a position that is reported
+  FD = k.drag * cdu * fma(mag, 0.0, ur);
   FL = k.lift * cl * (quad<kQuadNext>(ur) * wl2 - quad<kQuadAfter>(ur) * wl1);
 }
 
