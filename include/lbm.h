@@ -449,9 +449,9 @@ typedef struct {
 
 typedef struct lbm_batch lbm_batch;
 
-/* Batches of 2^20 cells or more with walls on every face, whose columns are not narrow (planes of 1536 bytes per
- * population in the mean over the cells, 1024 without bubbles), also take a middle buffer as large as one state
- * in scratch (two steps per launch, see lbm_batch_step). */
+/* Batches of 2^20 cells or more with walls on every face, a state of at most 64 GiB and columns that are not narrow
+ * (planes of 1536 bytes per population in the mean over the cells, 1024 without bubbles) also take a middle
+ * buffer as large as one state in scratch (two steps per launch, see lbm_batch_step). */
 lbm_status lbm_batch_bytes_required(const lbm_column* cols, int32_t ncols, int32_t precision,
                                     size_t* pool_bytes, size_t* scratch_bytes);
 /* Lay the columns out in pool, initialise every population to g = 0 and the fields to 0. The call

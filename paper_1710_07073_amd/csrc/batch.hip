@@ -218,7 +218,12 @@ constexpr size_t kBatchPairMinCells = 1u << 20;
 // (1050 B) 108 and 105, 1500 of 8 to 11 115 and 254; FP64 600 of 12 to 14 194 and 163, 1500 of 8 to 11 (720 B) 182 and 266.
 constexpr double kBatchPairMinPlane = 1536.0, kBatchPairMinPlaneLiquid = 1024.0;
 
-// As pairs_ok() of a single lattice, for every column.
+// States beyond this size take no middle buffer: pool and scratch are 2.3 times the state without one and 3.3 times
+// with, so a batch of up to this size still fits the 288 GB, and a larger one that fitted before does too.
+constexpr size_t kBatchPairMaxState = (size_t)64 << 30;
+
+// Batches whose method steps go in pairs: walls on every face, 32-bit byte offsets in each column, no flag that
+// has every cell read its force or write its velocity.
 bool batch_pairs_ok(const lbm_column* cols, int ncols, size_t elem, int flags) {
   if (flags & (LBM_FLAG_STATIC_FORCE | LBM_FLAG_WRITE_U_ALL)) return false;
   size_t total = 0;
@@ -233,6 +238,7 @@ bool batch_pairs_ok(const lbm_column* cols, int ncols, size_t elem, int flags) {
     planes += (double)n * cols[c].nx * cols[c].ny * elem;
     bubbles = bubbles || cols[c].nb > 0;
   }
+  if (19 * total * elem > kBatchPairMaxState) return false;
   return total >= kBatchPairMinCells && planes >= total * (bubbles ? kBatchPairMinPlane : kBatchPairMinPlaneLiquid);
 }
 

@@ -29,3 +29,8 @@ def test_pairs_by_size(shape, count, precision, nb, pairs):
     prec = L.LBM_FP32_SHIFTED if precision == "f32" else L.LBM_FP64_SHIFTED
     assert _has_middle(shape, count, prec, nb) == pairs
     assert not _has_middle(shape, count, prec, nb, (BB,) * 4 + (PER, PER))
+
+
+def test_no_middle_buffer_that_keeps_a_batch_off_the_card():
+    assert _has_middle((128, 128, 512), 100, L.LBM_FP32_SHIFTED, 1)      # 59 GiB a state
+    assert not _has_middle((128, 128, 512), 120, L.LBM_FP32_SHIFTED, 1)  # 71 GiB
