@@ -185,8 +185,8 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x);
  * first step of the rows and planes they reach beside the two steps of everything else, and with
  * more bubbles the parts of a pair run one after the other. Work
  * enqueued on the caller's stream after bubbles_step() sees the bubble results. Results are identical to the
- * serial step bit for bit. A bubble that moves more than two cells in one step would leave the region; that
- * is reported by lbm_check() / moments() with sums as LBM_EUNSUPPORTED. Not allowed while a
+ * serial step bit for bit. A bubble that moves more than two cells in one step (four in the two
+ * of a pair) may leave the region, which is whole tiles of 8 cells; that is reported by lbm_check() / moments() with sums as LBM_EUNSUPPORTED. Not allowed while a
  * bubble half awaits its lbm_step(). available (nullable) reports whether the current
  * configuration can overlap. */
 lbm_status lbm_set_overlap(lbm_ctx* ctx, int32_t enable);
@@ -195,7 +195,8 @@ lbm_status lbm_get_overlap(lbm_ctx* ctx, int32_t* enabled, int32_t* available);
 /* Timing hook for profiling: start and end (hipEvent_t, each nullable) are recorded on the
  * caller's stream immediately before and after the next liquid launch that updates the lattice
  * away from the bubbles (the bulk launch of an overlapped step, made by bubbles_step(), else the
- * whole liquid step). One-shot: the events are forgotten after that launch. The caller owns the events. */
+ * whole liquid step; of steps taken in pairs, by lbm_step() with two or more or by lbm_run(), the launch of
+ * two of them). One-shot: the events are forgotten after that launch. The caller owns the events. */
 lbm_status lbm_time_next_step(lbm_ctx* ctx, void* start, void* end);
 
 /* Cells in the region of the last overlapped step or pair of steps (0 if none since the last serial

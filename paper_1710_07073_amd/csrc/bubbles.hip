@@ -1548,8 +1548,11 @@ __global__ __launch_bounds__(256) void k_mark_slab(OneColumn geo, BubbleArgs A, 
   slab_note(slab, 2, wz.lo - 1 - 2 * kRegionMargin, wz.hi + 1 + 2 * kRegionMargin);
 }
 
-// Tiles up to which a lattice's gather takes four workgroups per tile. (On
-// 256 x 256 x 768 with 20 000 bubbles, 98 304 tiles, a workgroup per tile took 212 us against 79 us.)
+// Tiles up to which a lattice's gather takes four workgroups per tile. Whole method steps with a wavefront per tile
+// and this way, the bubbles in the lower seventh of the column and spread over it: 192 tiles, 300 bubbles 77 us and 42,
+// 45 and 34; 648 tiles, 300 bubbles 51 and 40, 41 and 43, 1500 127 and 67, 57 and 52; 1024 tiles, 300 bubbles 49 and 43,
+// 45 and 51, 1500 107 and 66, 55 and 60; 1536 tiles, 300 bubbles 51 and 50, 50 and 61, 1500 99 and 68, 61 and 70; 4000
+// tiles, 1500 bubbles 96 and 97, 94 and 126.
 constexpr uint32_t kGatherWideTiles = 1024;
 
 // Workgroups of the many-column gather (their wavefronts take the noted tiles in turn).
