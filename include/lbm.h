@@ -212,8 +212,8 @@ lbm_status lbm_region_cells(lbm_ctx* ctx, int64_t* cells);
  * that single steps are faster, advance two steps per launch where nsteps allows (with one cell per thread,
  * lbm_set_launch), the same results bit for bit. A launch
  * swaps the two population buffers, whether it takes one step or two (lbm_state_buffer names the current one);
- * once the caller has bound buffers (lbm_bind_buffers) or captured steps into a graph of its own, nsteps steps
- * leave the state in the buffer that nsteps swaps leave it in. */
+ * once the caller has bound buffers (lbm_bind_buffers), or captured steps or a call that reads the state into a graph
+ * of its own, nsteps steps leave the state in the buffer that nsteps swaps leave it in. */
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps);
 
 /* Bubble half of one step of Algorithm 1 for nb bubbles (forward coupling eq. (20) of the

@@ -94,6 +94,11 @@ Layout layout_of(const lbm_desc* d) {
   return L;
 }
 
+// A caller that captures has its graph name the population buffers of now.
+void note_capture(lbm_ctx* ctx) {
+  if (ctx->pairs.alone.ox != 0 && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
+}
+
 lbm_status from_hip(hipError_t e) { return e == hipSuccess ? LBM_OK : LBM_EDEVICE; }
 
 }  // namespace
@@ -370,11 +375,6 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x) {
   return LBM_OK;
 }
 
-// A caller that captures steps has its graph name the buffers of now.
-static void note_capture(lbm_ctx* ctx) {
-  if (ctx->pairs.alone.ox != 0 && lbm::caller_captures(ctx->stream)) ctx->in_order = true;
-}
-
 lbm_status lbm_step(lbm_ctx* ctx, int32_t nsteps) {
   if (!ctx || nsteps < 0) return LBM_EINVAL;
   note_capture(ctx);
@@ -456,6 +456,7 @@ lbm_status step_pair(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, 
 }  // namespace
 
 lbm_status bubbles_step(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, int32_t nb) {
+  if (ctx) note_capture(ctx);  // the exact-time coupling reads the state
   return bubble_half(ctx, p, s, nb, false);
 }
 
@@ -465,6 +466,7 @@ lbm_status bubbles_step_static_work(lbm_ctx* ctx, const bubble_params* p, const 
   if (!ctx->static_work) return LBM_EDEVICE;
   bubble_soa w = *s;
   w.work = ctx->static_work;
+  note_capture(ctx);
   return bubble_half(ctx, p, &w, nb, false);
 }
 
@@ -484,6 +486,7 @@ lbm_status lbm_check(lbm_ctx* ctx) {
 
 lbm_status moments(lbm_ctx* ctx, void* rho_out, void* u_out, double* sums_out) {
   if (!ctx) return LBM_EINVAL;
+  note_capture(ctx);
   if (lbm::launch_moments(ctx, rho_out, u_out, sums_out != nullptr) != hipSuccess) return LBM_EDEVICE;
   if (!sums_out) return LBM_OK;
   struct {
@@ -506,6 +509,7 @@ lbm_status moments(lbm_ctx* ctx, void* rho_out, void* u_out, double* sums_out) {
 
 lbm_status lbm_populations(lbm_ctx* ctx, void* out) {
   if (!ctx || !out) return LBM_EINVAL;
+  note_capture(ctx);
   return from_hip(lbm::launch_populations(ctx, out));
 }
 
@@ -524,12 +528,14 @@ lbm_status lbm_bind_buffers(lbm_ctx* ctx, void* state, void* next_state, void* v
 
 lbm_status lbm_state_buffer(lbm_ctx* ctx, void** out) {
   if (!ctx || !out) return LBM_EINVAL;
+  note_capture(ctx);
   *out = ctx->pops[ctx->hs.cur];
   return LBM_OK;
 }
 
 lbm_status lbm_checkpoint(lbm_ctx* ctx, void* state_out, void* vel_out) {
   if (!ctx || !state_out || !vel_out || ctx->hs.pending) return LBM_EINVAL;
+  note_capture(ctx);
   const size_t n = (size_t)ctx->geom.N * ctx->elem;
   hipError_t e = hipMemcpyAsync(state_out, ctx->pops[ctx->hs.cur], 19 * n, hipMemcpyDeviceToDevice,
                                 ctx->stream);
@@ -540,6 +546,7 @@ lbm_status lbm_checkpoint(lbm_ctx* ctx, void* state_out, void* vel_out) {
 
 lbm_status lbm_restore(lbm_ctx* ctx, const void* state, const void* vel) {
   if (!ctx || !state || !vel || ctx->hs.pending) return LBM_EINVAL;
+  note_capture(ctx);
   const size_t n = (size_t)ctx->geom.N * ctx->elem;
   hipError_t e = hipMemcpyAsync(ctx->pops[ctx->hs.cur], state, 19 * n, hipMemcpyDeviceToDevice,
                                 ctx->stream);

@@ -28,7 +28,7 @@ struct BatchState {
 
 struct lbm_batch {
   lbm::BatchState hs;
-  bool in_order;    // the caller captured steps (see lbm_ctx)
+  bool in_order;    // the caller captured steps or the state (see lbm_ctx)
   int ncols;
   int32_t precision;
   size_t elem;
@@ -883,6 +883,7 @@ lbm_status lbm_batch_sums(lbm_batch* b, double* sums) {
 
 lbm_status lbm_batch_populations(lbm_batch* b, int32_t col, void* out) {
   if (!b || col < 0 || col >= b->ncols || !out) return LBM_EINVAL;
+  if (caller_captures(b->stream)) b->in_order = true;
   const ColumnDev* dc = b->dev + col;
   const uint32_t N = b->host[col].G.N;
   if (b->elem == 4) {
@@ -905,6 +906,7 @@ lbm_status lbm_batch_populations(lbm_batch* b, int32_t col, void* out) {
 
 lbm_status lbm_batch_column(lbm_batch* b, int32_t col, void** state, void** force, void** vel) {
   if (!b || col < 0 || col >= b->ncols) return LBM_EINVAL;
+  if (caller_captures(b->stream)) b->in_order = true;
   if (state) *state = b->host[col].pops[b->hs.cur];
   if (force) *force = b->host[col].F;
   if (vel) *vel = b->host[col].U;

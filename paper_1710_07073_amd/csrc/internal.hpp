@@ -71,8 +71,8 @@ struct lbm_ctx {
   uint32_t* tcount;
   uint32_t* tlist;
   lbm::HostState hs;
-  // the caller bound buffers of its own or captured steps: graphs and pointers of its own name the buffers, so
-  // that from then on n steps leave the state where n single steps do
+  // the caller bound buffers of its own, or captured a call that names the population buffers: its graphs and
+  // pointers go on naming them, so that from then on n steps leave the state where n single steps do
   bool in_order;
   bool overlap;               // overlap enabled (lbm_set_overlap)
   hipStream_t side;           // null if it could not be created (overlap then unavailable)

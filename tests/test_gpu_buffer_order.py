@@ -120,3 +120,36 @@ def test_callers_graph_of_batch_steps_replays(n):
         b.step(1)
     for x, y in zip(_columns(a), _columns(b)):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("what", ["populations", "moments", "checkpoint", "state buffer"])
+def test_callers_graph_that_reads_the_state(what):
+    """A captured export shows the state after any even number of steps, as it does after single ones."""
+    stream = torch.cuda.Stream()
+    a = _sim(TOP, stream, 3)
+    out = [torch.zeros_like(a.pops[0]), torch.zeros_like(a.vel)]
+    torch.cuda.synchronize()
+
+    def export():
+        if what == "populations":
+            L.lbm_populations(a.ctx, out[0].data_ptr())
+        elif what == "moments":
+            L.moments(a.ctx, None, out[1].data_ptr(), False)
+        elif what == "checkpoint":
+            L.lbm_checkpoint(a.ctx, out[0].data_ptr(), out[1].data_ptr())
+        else:
+            out[0].copy_(a.pops[0] if L.lbm_state_buffer(a.ctx) == a.pops[0].data_ptr() else a.pops[1])
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        export()
+    with torch.cuda.stream(stream):
+        for n in (2, 4, 6, 2):
+            _advance(a, "run", n)
+            graph.replay()
+            stream.synchronize()
+            got = [t.clone() for t in out]
+            export()
+            stream.synchronize()
+            assert torch.isfinite(got[0]).all() and any(t.abs().max() > 0 for t in got)
+            assert all(torch.equal(x, y) for x, y in zip(got, out)), n
