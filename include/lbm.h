@@ -185,10 +185,10 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, int32_t* vec, int32_t* block_x);
  * first step of the rows and planes they reach beside the two steps of everything else, and with
  * more bubbles the parts of a pair run one after the other. Work
  * enqueued on the caller's stream after bubbles_step() sees the bubble results. Results are identical to the
- * serial step bit for bit. A bubble that moves more than two cells in one step (four in the two
- * of a pair) may leave the region, which is whole tiles of 8 cells; that is reported by lbm_check() / moments() with sums as LBM_EUNSUPPORTED. Not allowed while a
- * bubble half awaits its lbm_step(). available (nullable) reports whether the current
- * configuration can overlap. */
+ * serial step bit for bit. A bubble that moves more than two cells in one step (four in the two of a
+ * pair) may leave the region, which is of whole 8-cell tiles; if it does, lbm_check() / moments() with sums
+ * report it as LBM_EUNSUPPORTED. Not allowed while a bubble half awaits its lbm_step(). available
+ * (nullable) reports whether the current configuration can overlap. */
 lbm_status lbm_set_overlap(lbm_ctx* ctx, int32_t enable);
 lbm_status lbm_get_overlap(lbm_ctx* ctx, int32_t* enabled, int32_t* available);
 
