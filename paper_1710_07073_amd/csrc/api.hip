@@ -603,7 +603,7 @@ lbm_status lbm_run(lbm_ctx* ctx, const bubble_params* p, const bubble_soa* s, in
     const lbm::GraphKey key = lbm::GraphKey::of(p, s, nb, pre.cur, pre.flag_cur, graph_steps, mode);
     lbm_status st_cap = LBM_OK;
     bool captured = false;
-    hipError_t e = ctx->graph.ensure(key, ctx->stream,
+    hipError_t e = ctx->graph.ensure(key, ctx->stream, ctx->overlap && nb > 0 && lbm::can_overlap(ctx),
                                      [&]() -> hipError_t {
                                        st_cap = steps(graph_steps, single);
                                        return st_cap == LBM_OK ? hipSuccess : hipErrorInvalidValue;

@@ -834,7 +834,7 @@ lbm_status lbm_batch_run(lbm_batch* b, const bubble_params* p, const bubble_soa*
     const GraphKey key = GraphKey::of(p, s, nb, b->hs.cur, b->hs.flag_cur, graph_steps, mode);
     const BatchState pre = b->hs;
     bool captured = false;
-    hipError_t e = b->graph.ensure(key, b->stream, [&]() { return enqueue(graph_steps); }, &captured);
+    hipError_t e = b->graph.ensure(key, b->stream, false, [&]() { return enqueue(graph_steps); }, &captured);
     // a capture only records the launches (and a failed one ran nothing): back to the state before it,
     // then replay
     if (captured) b->graph.post() = b->hs;

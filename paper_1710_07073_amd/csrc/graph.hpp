@@ -74,9 +74,11 @@ class GraphCache {
     for (Slot& s : slot_) retire(s);
   }
 
-  // Capture `enqueue` on stream s unless a graph for the same key exists.
+  // Capture `enqueue` on stream s unless a graph for the same key exists. forked: on a second stream too; such a
+  // graph is captured once no other replays (a process that captured and replaced hundreds of them during
+  // replays has ended in a segmentation fault inside the runtime, for a reason that was not found).
   template <class F>
-  hipError_t ensure(const GraphKey& key, hipStream_t s, F&& enqueue, bool* captured) {
+  hipError_t ensure(const GraphKey& key, hipStream_t s, bool forked, F&& enqueue, bool* captured) {
     *captured = false;
     int k = -1;
     for (int i = 0; i < N; ++i)
@@ -93,6 +95,7 @@ class GraphCache {
     cur_ = k;
     slot.used = ++clock_;
     retire(slot);
+    if (forked) wait();
     clear_old();
     hipError_t e = hipEventCreateWithFlags(&slot.g.done, hipEventDisableTiming);
     if (e != hipSuccess) return e;
@@ -139,6 +142,12 @@ class GraphCache {
   void retire(Slot& s) {
     if (s.g.exec) old_[nold_++] = s.g;
     s.g = GraphExec{};
+  }
+  // Waits for the end of every replay.
+  void wait() {
+    for (Slot& s : slot_)
+      if (s.g.exec) (void)hipEventSynchronize(s.g.done);
+    for (int i = 0; i < nold_; ++i) (void)hipEventSynchronize(old_[i].done);
   }
   // Destroys the old graphs whose last replay has ended; waits for the oldest ones if there are many.
   void clear_old() {

@@ -13,9 +13,12 @@ lbm::GraphKey key(int cur, int spar, bool marked) {
 }
 
 template <class Cache>
-void replay(Cache& c, const lbm::GraphKey& k) {
+void replay(Cache& c, const lbm::GraphKey& k, bool forked = false) {
   bool captured = false;
-  c.ensure(k, nullptr, [] { return hipSuccess; }, &captured);
+  c.ensure(k, nullptr, forked, [] { return hipSuccess; }, &captured);
+  if (captured && forked)
+    for (FakeGraph* g : fake.live)
+      if (g->ended < g->launches) ++fake.captured_during;
   c.launch(nullptr);
 }
 
@@ -39,18 +42,18 @@ void flips() {
 }
 
 // New keys faster than replays end, resets in between, and the cache gone during the last.
-void storm() {
+void storm(bool forked) {
   fake = FakeHip{};
   {
     lbm::GraphCache<int, 4> c;
     for (int i = 0; i < 200; ++i) {
-      replay(c, key(i, 0, false));
+      replay(c, key(i, 0, false), forked);
       if (i % 7 == 3) c.reset();
       if (i % 50 == 49)
         for (FakeGraph* g : fake.live) g->ended = g->launches;
     }
-    printf("storm: captures %d, destroyed while running %d, waited %d\n", fake.captures, fake.destroyed_running,
-           fake.waits > 0);
+    printf("storm: captures %d, destroyed while running %d, waited %d, captured during replays %d\n", fake.captures,
+           fake.destroyed_running, fake.waits > 0, fake.captured_during);
   }
   printf("  at the end: live %d, destroyed while running %d\n", (int)fake.live.size() - fake.destroyed,
          fake.destroyed_running);
@@ -61,6 +64,7 @@ void storm() {
 int main() {
   flips<4>();
   flips<2>();
-  storm();
+  storm(false);
+  storm(true);
   return 0;
 }

@@ -20,7 +20,7 @@ using hipGraphExec_t = FakeGraph*;
 using hipEvent_t = FakeEvent*;
 
 struct FakeHip {
-  int captures = 0, destroyed = 0, destroyed_running = 0, waits = 0;
+  int captures = 0, destroyed = 0, destroyed_running = 0, waits = 0, captured_during = 0;
   FakeGraph* last = nullptr;
   std::vector<FakeGraph*> live;
 };
